@@ -1,23 +1,43 @@
 // The FP32 phase of a single solve as ONE cooperative launch, for instances
-// whose FP32 cost fits in the LDS of the whole GPU (about 40 MB on 256 CUs:
+// whose FP32 kernel fits in the LDS of the whole GPU (about 40 MB on 256 CUs:
 // 20000 x 400 needs 32 MB). Each workgroup (one per CU) owns a contiguous
-// block of rows, fills its LDS with their costs once (read from the matrix,
-// or regenerated from positions), and then runs Sinkhorn iterations
-// (Sec. III-B, the alternating row and column updates of the dual
-// potentials) until the device-side stop rule fires. Iteration k:
+// block of rows and holds their stabilised Gibbs kernel in LDS: with reference
+// potentials G, E_ij = exp((G_j - C_ij) / eps - m_i) in FP32 (arguments in FP64,
+// from the matrix or regenerated from positions; m_i the row's largest). It
+// then runs Sinkhorn iterations (Sec. III-B) in the scaling form on that kernel
+// until the device-side stop rule fires. Iteration k:
 //
-//   1. row update of the workgroup's rows from the LDS tile: f_i, the row
-//      residual of the previous iterate and the column partials of the
-//      half-iterate (FP32 exponentials, FP64 arguments, FP64 sums across
-//      lanes, rows and workgroups), published to an exchange buffer;
+//   1. row update of the workgroup's rows: S_i = sum_j E_ij v_j (the row scaling
+//      is a_i / S_i), the row residual of the previous iterate, a_i |S_i^k /
+//      S_i^(k-1) - 1|, and the column partials sum_i E_ij a_i / S_i (FP32
+//      products, FP64 sums across lanes, waves and workgroups), published to
+//      an exchange buffer;
 //   2. workgroup w owns the blocks of 8 consecutive columns w, w + nb, ...:
 //      it collects their partials from every workgroup, sums them in a fixed
-//      order and publishes the new g_j; workgroup 0 also sums the residuals
-//      and publishes the stop decision;
-//   3. every workgroup collects the new g and the decision.
+//      order and publishes v_j = b_j / sum; the last workgroup also sums the
+//      residuals and publishes the stop decision;
+//   3. every workgroup collects the new v and the decision.
 //
-// Only O(I + J) potentials and O(nb J) partials move per iteration; the
-// I x J cost is read once per launch instead of once per iteration.
+// A cell costs two multiply-adds per iteration and no exponential; those run
+// only when a reference is taken (C is then read again):
+//   - at the first iteration, and again when a scaling leaves [2^-40, 2^40],
+//     with FP32 exponentials;
+//   - once the residual is below 1e-5 (for targets below the FP32 noise of
+//     about 4e-8 of residual), with FP64 exponentials and FP64 sums R_i of the
+//     rows and of the columns. From there on the iteration adds only the
+//     change against the reference, S_i = R_i + sum_j E_ij (v_j - 1) and likewise
+//     for the columns, so its FP32 rounding is 2^-24 of |v - 1| instead of
+//     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
+//     cost were needed before.
+//
+// What bounds it: the exchange. With the exponentials in every iteration the
+// row update alone took 4.8 us of the 9.6 us per iteration at 20000 x 400;
+// the whole solve with its plan went 555 -> 463 us, and the distance cost at
+// that size (over 1200 iterations, 200 of them FP64 sweeps before) 15.7 -> 8.0
+// ms.
+//
+// Only O(I + J) scalings and O(nb J) partials move per iteration; the I x J cost
+// is read two or three times per launch instead of once per iteration.
 //
 // Exchange without fences or barriers. On this GPU the L2 of an XCD is not
 // coherent with the other XCDs' L2s, and an agent-scope release writes a
@@ -129,11 +149,11 @@ __device__ bool poll_tagged(const double* base, int64_t stride, int n, int k, do
 struct PersistArgs {
     int64_t I;
     int J;
-    int Jp;   // LDS row stride of the cost tile (ncl * LPR; padding reads +inf)
+    int Jp;   // LDS row stride of the kernel tile (ncl * LPR; padding holds 0)
     int ncl;  // cells per lane of a row: column q LPR + sub for q < ncl (<= CPL)
     int rpw;  // rows per workgroup: a whole number of wave steps
     int max_spin;
-    int hold_iter;  // > 0: at iteration k0 + hold_iter of the launch no new g is published, so
+    int hold_iter;  // > 0: at iteration k0 + hold_iter of the launch no new v is published, so
                     // every wait after it ends by giving up (exercises that path); else 0
     double stall_below;
     const double* a;
@@ -145,33 +165,97 @@ struct PersistArgs {
     const SolveParams* prm;
 };
 
-// Dynamic LDS of k_persist in bytes (the layout the kernel carves): the
-// tile, a slack of (CPL - ncl) LPR floats after it, then the row and column
-// vectors.
 // Column blocks each workgroup owns at most (workgroup w owns w, w + nb, ...).
 __host__ __device__ inline int persist_owned_blocks(int nb, int J) {
     const int nblk = (J + kColBlock - 1) / kColBlock;
     return (nblk + nb - 1) / nb;
 }
+// Dynamic LDS of k_persist in bytes (the layout the kernel carves): the
+// tile, a slack of (CPL - ncl) LPR floats after it, then the column vectors
+// (G, v), the row vectors (a, m, R, S), b and the reference column sums of
+// the owned columns, x and the fold buffer of the column partials (FP32 partials of all waves at
+// once up to 512 columns, of half of them for wider rows).
 __host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int waves, int slack, int nb) {
     const size_t Jr2 = (size_t)((J + 1) & ~1), Jr4 = (size_t)((J + 3) & ~3);
-    return ((size_t)rpw * Jp + (size_t)slack) * 4 + Jr2 * 8 + 6 * (size_t)rpw * 8 +
-           (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + (size_t)waves * Jr4 * 4;
+    return ((size_t)rpw * Jp + (size_t)slack) * 4 + 2 * Jr2 * 8 + 4 * (size_t)rpw * 8 +
+           2 * (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + Jr4 * 4 +
+           (size_t)(J > 512 ? waves / 2 : waves) * Jr4 * 4;
+}
+
+// Kinds of iteration of the cooperative phase (the same in every workgroup).
+enum : int { kItAbs32 = 0, kItPlain = 1, kItAbs64 = 2, kItDelta = 3 };
+// Decision codes: bit 0 stop, bit 1 take the FP64 reference next.
+constexpr int kDecStop = 1, kDecRef64 = 2;
+// The FP64 reference is taken once the residual is below this: the scalings
+// then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
+// residuals down to about 1e-12, far below the FP32 noise (4e-8) of the plain
+// sums; an earlier switch would buy nothing, a later one comes too close to
+// that noise.
+constexpr double kRef64Below = 1e-5;
+// A plain reference is renewed when a scaling leaves [2^-40, 2^40]: an entry
+// flushed to zero in FP32 (below 2^-126 of its row's largest) then stands for
+// less than 2^-46 of any row or column sum.
+constexpr double kScaleMax = 0x1p40;
+// The delta sums keep |v - 1| below this (else the FP64 reference is renewed).
+constexpr double kDeltaMax = 0.125;
+
+// The stop rule of the cooperative phase, run by one lane: like the fast mode
+// of bookkeep, except that a solve whose target lies below the FP32 noise
+// (stall_below) goes on past it: the plain sums are left for the FP64 reference
+// and its delta sums (returned as kDecRef64), whose residuals are good to about
+// 1e-6 of the residual r_ref at which the reference was taken and are therefore
+// compared with tol itself. Long delta phases (a slowly converging instance
+// whose scalings drift far from the reference) renew the reference.
+__device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, double& r_ref,
+                                             int& k_ref) {
+    const int k = c->iter + 1;
+    const double r = c->has_prev ? rsum / c->mass : pinf64();
+    const bool bad = c->numeric_bad || (c->has_prev && !isfinite(r));
+    c->r_last = r;
+    c->iter = k;
+    c->has_prev = 1;
+    c->last_fp64 = 0;
+    const double target = c->tol_fast > 0.0 ? c->tol_fast : c->tol;
+    const bool fine = kind == kItAbs64 || kind == kItDelta;  // residuals of the FP64 reference
+    double mn = pinf64();
+    int nfin = 0;
+    for (int q = 0; q < 4; ++q)
+        if (isfinite(c->r_hist[q])) { mn = fmin(mn, c->r_hist[q]); ++nfin; }
+    const double noise = fine ? 1e-6 * r_ref : target >= stall_below ? stall_below : 0.0;
+    const bool stall = (nfin >= 1) && isfinite(r) && (r < noise) && (r > 0.95 * mn);
+    for (int q = 3; q > 0; --q) c->r_hist[q] = c->r_hist[q - 1];
+    c->r_hist[0] = r;
+    const bool met = r < target && (fine || target >= stall_below);
+    const bool at_check = c->check_every <= 1 || k % c->check_every == 0;
+    int code = 0;
+    if (kind == kItAbs64) k_ref = k;
+    if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kRef64Below)) {
+        r_ref = r;
+        code = kDecRef64;
+    }
+    if ((at_check && (met || stall)) || k >= c->max_iter) c->stop = 1;
+    if (bad) {
+        c->numeric_bad = 1;
+        c->done = 1;
+        c->stop = 1;
+        c->result_iter = k;
+    }
+    return (c->stop | c->done) ? kDecStop : code;
 }
 
 // Lane layout: a row is handled by LPR lanes (32 or 64); lane `sub` owns
 // columns q LPR + sub, q < CPL, so consecutive lanes read consecutive LDS
 // words, each at a constant offset from the row (one address per row step).
-// Every cell is processed without a branch (branches around LDS reads would
-// serialise their latencies): cells q >= ncl read on into the next row of
-// the tile, or into a +inf slack after it, and get g = -inf: a zero term
-// (finite or +inf costs only, never a NaN). A wave advances R = 64 / LPR rows
-// per step.
+// Every cell is processed without a branch: cells q >= ncl read on into the
+// next row of the tile, or into a zero slack after it, and get x = 0. A wave
+// advances R = 64 / LPR rows per step.
 template <class Src, int CPL, int LPR, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
     extern __shared__ double sm[];
     constexpr int R = kWave / LPR;
     constexpr int T = WAVES * kWave;
+    constexpr int U = CPL <= 16 ? 2 : 1;  // row steps in flight
+    static_assert(WAVES == 8, "the fold and the owner layout assume 8 waves");
     const int J = A.J, Jp = A.Jp, rpw = A.rpw, ncl = A.ncl;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int sub = lane % LPR, rg = lane / LPR;
@@ -179,22 +263,25 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     const int64_t r0 = (int64_t)blk * rpw;
     const int nrows = (int)max((int64_t)0, min((int64_t)rpw, A.I - r0));
     const int Jr2 = (J + 1) & ~1, Jr4 = (J + 3) & ~3;
-    const int slack = (CPL - ncl) * LPR;  // (a multiple of 32 floats: graw stays 8-byte aligned)
+    const int slack = (CPL - ncl) * LPR;  // (a multiple of 32 floats: what follows stays 8-byte aligned)
     float* tile = reinterpret_cast<float*>(sm);
-    double* graw = reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);
-    double* fl = graw + Jr2;   // f_i of the current iterate
-    double* al = fl + rpw;     // a_i
-    double* lal = al + rpw;    // ln a_i
-    double* lse = lal + rpw;   // log2 sum_j 2^(g_j kk - C_ij kk) of the last row update
-    double* shf = lse + rpw;   // shift of the row's exponentials in this row update
-    double* rsum = shf + rpw;  // sum of those exponentials
-    double* lbl = rsum + rpw;  // ln b_j of the owned columns (8 per owned block)
+    double* gl = reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);  // G_j of the reference
+    double* vl = gl + Jr2;    // v_j = exp((g_j - G_j) / eps)
+    double* al = vl + Jr2;    // a_i
+    double* ml = al + rpw;    // m_i: the shift of row i's stored kernel entries (log2)
+    double* Rl = ml + rpw;    // R_i = sum_j E_ij, FP64 (delta sums only)
+    double* Sl = Rl + rpw;    // S_i = sum_j E_ij v_j of the last row update
     const int nown = persist_owned_blocks(nb, J);
-    float* red = reinterpret_cast<float*>(lbl + (size_t)kColBlock * nown);
+    double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block)
+    double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the FP64 reference
+    float* xl = reinterpret_cast<float*>(cl + (size_t)kColBlock * nown);  // v_j, or v_j - 1 for delta sums, in FP32
+    float* red = xl + Jr4;
     __shared__ Ctl cs;  // decision workgroup: the control block for the whole launch
+    __shared__ double e2tab[64];
     __shared__ double wres[WAVES];
     __shared__ double ored[WAVES][kColBlock];  // per-wave column sums of an owned block
     __shared__ uint32_t s_dec;
+    __shared__ int s_flag[2];  // by iteration parity: 1 a wait gave up, 2 not finite, 4 out of range (plain), 8 (delta)
 
     const XchLayout X = persist_xch_layout(nb, J);
     double* part = A.xch + X.part;
@@ -202,192 +289,274 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     double* gx = A.xch + X.gx;
     uint64_t* dec = reinterpret_cast<uint64_t*>(A.xch + X.dec);
     uint64_t* abort_word = reinterpret_cast<uint64_t*>(A.xch + X.abort_);
-    const int rep = blk % kReplicas;  // the replica of g and of the decision this workgroup reads
+    const int rep = blk % kReplicas;  // the replica of v and of the decision this workgroup reads
 
     Ctl* ctl = A.ctl;
     if (ctl->stop | ctl->done) return;  // the same words for every workgroup
     const int k0 = ctl->iter;
     int has_prev = ctl->has_prev;
     const double kk = A.prm->kk, eps = A.prm->eps, inv_eps = 1.0 / A.prm->eps;
-    const float kk32 = (float)kk;
 
-    // 1. this workgroup's rows of C in FP32 (the FP64 cost rounded once);
-    //    padding columns and rows past I hold +inf (a zero plan entry)
-    src.stage(reinterpret_cast<double*>(red), J);  // per-column source data (positions)
-    __syncthreads();
-    const double* stage = reinterpret_cast<const double*>(red);
-    // (the tile's cells in row-major order, eight loads in flight per thread)
-    const int ntile = rpw * Jp;
-    for (int e0 = 0; e0 < ntile; e0 += 8 * T) {
-        typename Src::template Raw<1> raw[8];
-        int lr8[8], j8[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * T + (int)threadIdx.x;
-            lr8[u] = e / Jp;
-            j8[u] = e - lr8[u] * Jp;
-            if (e < ntile && lr8[u] < nrows && j8[u] < J) raw[u] = src.template load<1>(src.row(r0 + lr8[u]), j8[u], J);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * T + (int)threadIdx.x;
-            if (e < ntile) {
-                float c = __builtin_huge_valf();
-                if (lr8[u] < nrows && j8[u] < J) {
-                    const int64_t i = r0 + lr8[u];
-                    // (the FP64 cost rounded once: for costs regenerated from
-                    // positions the tile then holds exactly the materialised
-                    // FP32 cost, so the FP32 phase iterates on that problem)
-                    c = (float)src.template cost<true, 1>(src.row(i), raw[u], 0, i, j8[u], stage);
-                }
-                tile[e] = c;
-            }
-        }
-    }
-    for (int e = threadIdx.x; e < slack; e += T) tile[(size_t)rpw * Jp + e] = __builtin_huge_valf();
-    // 2. the rows' a_i, ln a_i and current f_i; the current g
-    const double* f_in = A.f[k0 & 1];
+    exp2_tab_fill(e2tab);
     for (int lr = threadIdx.x; lr < rpw; lr += T) {
-        const bool ok = lr < nrows;
-        const double ai = ok ? A.a[r0 + lr] : 0.0;
-        al[lr] = ai;
-        lal[lr] = ok ? log(ai) : 0.0;
-        fl[lr] = (ok && has_prev) ? f_in[r0 + lr] : 0.0;
-        lse[lr] = 0.0;
+        al[lr] = lr < nrows ? A.a[r0 + lr] : 0.0;
+        ml[lr] = 0.0;
+        Rl[lr] = Sl[lr] = 1.0;
     }
     const double* g_in = A.g[k0 & 1];
-    for (int j = threadIdx.x; j < J; j += T) graw[j] = g_in[j];
+    for (int j = threadIdx.x; j < J; j += T) {
+        gl[j] = g_in[j];
+        vl[j] = 1.0;
+    }
     for (int e = threadIdx.x; e < kColBlock * nown; e += T) {
         const int j = (blk + (e / kColBlock) * nb) * kColBlock + e % kColBlock;
-        lbl[e] = j < J ? log(A.b[j]) : 0.0;
+        bl[e] = j < J ? A.b[j] : 1.0;
+        cl[e] = 0.0;
     }
+    for (int e = threadIdx.x; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0.0f;
+    if (threadIdx.x < 2) s_flag[threadIdx.x] = 0;
     // the decision workgroup (the last one: with fewer column blocks than
     // workgroups it owns none) sums the residuals and takes the stop decision
     const int dblk = nb - 1;
     if (blk == dblk && threadIdx.x == 0) cs = *ctl;
-    __syncthreads();
+    double r_ref = 0.0;  // (the deciding lane's)
+    int k_ref = 0;
 
-    // g_j kk of this lane's columns (-inf past J)
-    double gk[CPL];
-    auto load_g = [&]() {
+    const int steps = rpw / (WAVES * R);
+    double res = 0.0;  // this lane's part of the row residual of the previous iterate
+    int k = k0;
+
+    // Row update of an iteration that takes a new reference G = g: the kernel
+    // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i the row maximum,
+    // from FP64 arguments, stored in FP32. The exponentials are FP32, or with
+    // P64 FP64; the column partials sum_i E_ij a_i / S_i then are FP64, too.
+    auto absorb = [&](auto& ac) {
+        using E = std::decay_t<decltype(ac[0])>;
+        constexpr bool P64 = sizeof(E) == 8;
+        double* stage = reinterpret_cast<double*>(red);
+        src.stage(stage, J);
+        for (int j = threadIdx.x; j < J; j += T) {
+            gl[j] += eps * log(vl[j]);
+            vl[j] = 1.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) ac[q] = 0;
+        res = 0.0;
+        // (a row's loads are issued one step ahead)
+        typename Src::template Raw<1> nraw[CPL];
+        auto fetch = [&](int st) {
+            const int lr = (st * WAVES + w) * R + rg;
+            auto row = src.row(r0 + (lr < nrows ? lr : 0));
+#pragma unroll
+            for (int q = 0; q < CPL; ++q)
+                if (q < ncl) nraw[q] = src.template load<1>(row, q * LPR + sub, J);
+        };
+        if (nrows > 0) fetch(0);
+        for (int st = 0; st < steps && nrows > 0; ++st) {
+            const int lr = (st * WAVES + w) * R + rg;
+            const bool vrow = lr < nrows;
+            const int64_t i = r0 + (vrow ? lr : 0);
+            typename Src::template Raw<1> raw[CPL];
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) raw[q] = nraw[q];
+            if (st + 1 < steps) fetch(st + 1);
+            auto row = src.row(i);
+            double t[CPL];
+            float mx = -__builtin_huge_valf();
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) {
+                t[q] = -pinf64();
+                const int j = q * LPR + sub;
+                if (q < ncl && j < J && vrow) t[q] = (gl[j] - src.template cost<true, 1>(row, raw[q], 0, i, j, stage)) * kk;
+                mx = fmaxf(mx, (float)t[q]);
+            }
+            const double m = fmax((double)group_max<LPR>(mx), -1e300);
+            E ev[CPL];
+            E s = 0, s2 = 0;  // even and odd cells: two shorter add chains
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) {
+                const double d = t[q] - m;
+                if constexpr (P64) ev[q] = exp2_tab(fmax(d, -2000.0), e2tab);  // (2^-2000 is 0)
+                else ev[q] = exp2_f32((float)d);
+                if (q & 1) s2 += ev[q];
+                else s += ev[q];
+            }
+            const double S = group_sum<LPR>((double)(s + s2));
+            const double ai = al[lr];
+            E wq = 0;
+            if (vrow) {
+                if constexpr (P64) wq = ai / S;
+                else wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+            }
+            float* trow = tile + (size_t)lr * Jp + sub;
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) {
+                ac[q] = fma(ev[q], wq, ac[q]);
+                if (q < ncl) trow[q * LPR] = (float)ev[q];
+            }
+            if (sub == 0 && vrow) {
+                if (has_prev) {  // (f of the previous iterate: from the buffers at the launch's start)
+                    const double la = log(ai);
+                    const double fp = k == k0 + 1 ? A.f[k0 & 1][r0 + lr] : eps * (la - kLn2 * (ml[lr] + log2(Sl[lr])));
+                    res += ai * fabs(expm1((fp - eps * (la - kLn2 * (m + log2(S)))) * inv_eps));
+                }
+                ml[lr] = m;
+                Rl[lr] = S;
+                Sl[lr] = S;
+            }
+        }
+        __syncthreads();  // (the fold reuses the staged source data's LDS)
+    };
+
+    // Row update against the stored kernel: S_i = sum_j E_ij v_j, or from the
+    // FP64 reference S_i = R_i + sum_j E_ij (v_j - 1), whose FP32 rounding scales
+    // with |v - 1|; the column partials sum_i E_ij a_i / S_i, or their change
+    // against the reference, sum_i E_ij (a_i / S_i - a_i / R_i).
+    auto rows = [&](auto delta, float (&acc)[CPL]) {
+        constexpr bool D = decltype(delta)::value;
+        float x[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
             const int j = q * LPR + sub;
-            gk[q] = (q < ncl && j < J) ? graw[j] * kk : -pinf64();
+            x[q] = (q < ncl && j < J) ? xl[j] : 0.0f;
+        }
+        res = 0.0;
+        auto step = [&](int st, auto nu) {
+            constexpr int N = decltype(nu)::value;
+            float ev[N][CPL], s[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const float* trow = tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp + sub;
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) ev[u][q] = trow[q * LPR];
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) {
+                    if (q & 1) s1 = fmaf(ev[u][q], x[q], s1);
+                    else s0 = fmaf(ev[u][q], x[q], s0);
+                }
+                s[u] = s0 + s1;
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int lr = ((st + u) * WAVES + w) * R + rg;
+                const bool vrow = lr < nrows;
+                const double d = group_sum<LPR>((double)s[u]);
+                const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
+                const double S = D ? Rr + d : d;
+                float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+                if constexpr (D) wq *= -(float)d * __builtin_amdgcn_rcpf((float)Rr);
+                if (!vrow) wq = 0.0f;
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[u][q], wq, acc[q]);
+                if (sub == 0 && vrow) {
+                    res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
+                    Sl[lr] = S;
+                }
+            }
+        };
+        int st = 0;
+        for (; st + U <= steps; st += U) step(st, std::integral_constant<int, U>{});
+        if constexpr (U > 1)
+            for (; st < steps; ++st) step(st, std::integral_constant<int, 1>{});
+    };
+
+    // The workgroup's column partials: the row groups of a wave (lanes
+    // sub + LPR r share columns), then the waves in FP64; calls out(c, sum)
+    // for this thread's columns. The residual's wave sums go to wres.
+    auto fold = [&](auto& ac, auto&& out) {
+        using E = std::decay_t<decltype(ac[0])>;
+        E* rb = reinterpret_cast<E*>(red);
+        if constexpr (LPR == 32) {
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) ac[q] = xor32_sum(ac[q]);
+        }
+        const double rw = wave_sum(res);
+        if (lane == 0) wres[w] = rw;
+        constexpr int NW = WAVES * 4 / ((LPR == 64 ? 2 : 1) * (int)sizeof(E));  // waves per round
+        constexpr int NC = LPR == 32 ? 1 : 4;  // columns per thread
+        double t[NC];
+#pragma unroll
+        for (int u = 0; u < NC; ++u) t[u] = 0.0;
+#pragma unroll
+        for (int w0 = 0; w0 < WAVES; w0 += NW) {
+            if (w0 > 0) __syncthreads();  // the previous round's sums are taken
+            if (w >= w0 && w < w0 + NW && rg == 0) {
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) {
+                    const int j = q * LPR + sub;
+                    if (q < ncl && j < J) rb[(w - w0) * Jr4 + j] = ac[q];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NC; ++u) {
+                const int c = u * T + (int)threadIdx.x;
+                if (c < J) {
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) t[u] += (double)rb[q * Jr4 + c];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int c = u * T + (int)threadIdx.x;
+            if (c < J) out(c, t[u]);
         }
     };
-    load_g();
 
-    const int steps = rpw / (WAVES * R);
-    int k = k0;
+    __syncthreads();
+    int kind = kItAbs32;
     bool ok = true;
-    bool exact_shift = true;  // first row update of the launch: shift by the row maximum
     for (;;) {
         ++k;
         const int P = k & 1;
-        // ---- 1. row update from the LDS tile
-        float acc[CPL];
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) acc[q] = 0.0f;
-        // Each row's (shift, sum) goes to LDS; after the steps one thread per
-        // row finishes f_i, the next shift and the residual term (the FP64
-        // logarithm and expm1 then run once per row, on every lane).
-        for (int st = 0; st < steps; ++st) {
-            const int lr0 = (st * WAVES + w) * R;
-            const int lr = lr0 + rg;
-            const bool vrow = lr < nrows;
-            const float* trow = tile + (size_t)lr * Jp + sub;
-            float cv[CPL];
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) cv[q] = trow[q * LPR];
-            // shift: the row's previous log-sum-exp (any value near the row
-            // maximum keeps the FP32 exponentials in range), or the maximum
-            double m = lse[lr];
-            float ev[CPL];
-            float s = 0.0f, s2 = 0.0f;  // even and odd cells: two shorter add chains
-            bool redo = exact_shift;
-            if (!redo) {
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    const double t = fma((double)cv[q], -kk, gk[q]) - m;
-                    const float e = exp2_f32((float)t);
-                    ev[q] = e;
-                    if (q & 1) s2 += e;
-                    else s += e;
-                }
-            }
-            double S = group_sum<LPR>((double)(s + s2));
-            // a sum far from 1 means the shift drifted too far from the row
-            // maximum for FP32 exponentials: redo the wave's rows with the maximum
-            redo = __any(redo || (vrow && !(S >= 0x1p-100 && S <= 0x1p100)));
-            if (redo) {
-                // (the costs are read from LDS again: otherwise the compiler
-                // keeps the FP64 arguments of every cell live across this
-                // rare branch, which costs the common path its registers)
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) cv[q] = trow[q * LPR];
-                float mx = -__builtin_huge_valf();
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) mx = fmaxf(mx, fmaf(cv[q], -kk32, (float)gk[q]));
-                m = fmax((double)group_max<LPR>(mx), -1e300);
-                s = 0.0f;
-                s2 = 0.0f;
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    const double t = fma((double)cv[q], -kk, gk[q]) - m;
-                    const float e = exp2_f32((float)t);
-                    ev[q] = e;
-                    if (q & 1) s2 += e;
-                    else s += e;
-                }
-                S = group_sum<LPR>((double)(s + s2));
-            }
-            // column partials of the half-iterate plan, pi_ij = e_ij a_i / S_i
-            const float wq = vrow ? (float)al[lr] * __builtin_amdgcn_rcpf((float)S) : 0.0f;
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[q], wq, acc[q]);
-            if (sub == 0 && vrow) {
-                shf[lr] = m;
-                rsum[lr] = S;
-            }
-        }
-        exact_shift = false;
-        // ---- the workgroup's partials: fold the row groups of a wave (lanes
-        //      sub + LPR r share columns), then the waves in FP64, published
-        //      as one contiguous row of the partial buffer
-        if constexpr (LPR == 32) {
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) acc[q] = xor32_sum(acc[q]);
-        }
-        if (rg == 0) {
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
-                const int j = q * LPR + sub;
-                if (q < ncl && j < J) red[w * Jr4 + j] = acc[q];
-            }
-        }
-        __syncthreads();
-        // the rows of this workgroup: f_i, the next shift, the residual term
-        double res = 0.0;
-        for (int lr = threadIdx.x; lr < nrows; lr += T) {
-            const double L2 = shf[lr] + log2(rsum[lr]);
-            const double fi = eps * (lal[lr] - kLn2 * L2);
-            if (has_prev) res += al[lr] * fabs(expm1((fl[lr] - fi) * inv_eps));
-            fl[lr] = fi;
-            lse[lr] = L2;
-        }
-        res = wave_sum(res);
-        if (lane == 0) wres[w] = res;
-        __syncthreads();
+        const bool fine = kind == kItAbs64 || kind == kItDelta;  // v - 1 is what the next delta sums need
+        const bool hold = k - k0 == A.hold_iter;
+        // v_j of this workgroup from the exchange (or, alone, from its own
+        // sums), with the flags that choose the next iteration's kind
+        int flag = 0;
+        auto take_v = [&](int j, double v) {
+            vl[j] = v;
+            xl[j] = (float)(fine ? v - 1.0 : v);
+            if (!(v > 0.0) || !isfinite(v)) flag |= 2;
+            if (!(v >= 1.0 / kScaleMax && v <= kScaleMax)) flag |= 4;
+            if (!(fabs(v - 1.0) <= kDeltaMax)) flag |= 8;
+        };
+        // column update v_j = b_j / sum_i E_ij a_i / S_i of owned column slot e
+        auto col_v = [&](int e, double sum) {
+            if (kind == kItDelta) sum += cl[e];
+            return bl[e] / sum;
+        };
         double* prow = part + ((size_t)P * nb + blk) * X.Jp;
-        for (int c = threadIdx.x; c < J; c += T) {
-            double t = 0.0;
+        auto out = [&](int c, double t) {
+            if (nb == 1) {
+                take_v(c, col_v(c, t));
+                if (kind == kItAbs64) cl[c] = t;
+            } else {
+                put_agent(prow + c, tag_value(t, k));
+            }
+        };
+
+        // ---- 1. row update and the workgroup's column partials
+        if (kind == kItAbs64) {
+            double ac[CPL];
+            absorb(ac);
+            fold(ac, out);
+        } else {
+            float ac[CPL];
 #pragma unroll
-            for (int q = 0; q < WAVES; ++q) t += (double)red[q * Jr4 + c];
-            put_agent(prow + c, tag_value(t, k));
+            for (int q = 0; q < CPL; ++q) ac[q] = 0.0f;
+            if (kind == kItAbs32) absorb(ac);
+            else if (kind == kItDelta) rows(std::true_type{}, ac);
+            else rows(std::false_type{}, ac);
+            fold(ac, out);
         }
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == T - 1 && nb > 1) {
             double r = 0.0;
 #pragma unroll
             for (int q = 0; q < WAVES; ++q) r += wres[q];
@@ -396,31 +565,35 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
 
         bool fail = false;
         if (blk == dblk && w == WAVES - 1) {  // residual of iterate k - 1 and the stop rule
-            double x[4];
-            if (!poll_tagged(rpart + (size_t)P * nb, 1, nb, k, x, abort_word, A.max_spin)) {
+            double x[4] = {0.0, 0.0, 0.0, 0.0};
+            if (nb == 1) {
+                if (lane < WAVES) x[0] = wres[lane];
+                fail = hold;
+            } else if (!poll_tagged(rpart + (size_t)P * nb, 1, nb, k, x, abort_word, A.max_spin)) {
                 fail = true;
-            } else {
+            }
+            if (!fail) {
                 double r = 0.0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) r += x[u];
                 r = wave_sum(r);
-                int stop = 0;
-                if (lane == 0) {
-                    bookkeep(&cs, r, kModeFast, A.stall_below);
-                    stop = (cs.stop | cs.done) ? 1 : 0;
+                int code = 0;
+                if (lane == 0) code = bookkeep_coop(&cs, r, kind, A.stall_below, r_ref, k_ref);
+                code = __shfl(code, 0, kWave);
+                if (nb == 1) {
+                    if (lane == 0) s_dec = (uint32_t)code;
+                } else if (lane < kReplicas) {
+                    put_agent(dec + ((size_t)P * kReplicas + lane) * 8, ((uint64_t)k << 2) | (uint64_t)code);
                 }
-                stop = __shfl(stop, 0, kWave);
-                const uint64_t d = ((uint64_t)k << 2) | (uint64_t)stop;
-                if (lane < kReplicas) put_agent(dec + ((size_t)P * kReplicas + lane) * 8, d);
             }
         }
 
         // ---- 2. column update of the owned blocks of kColBlock columns: thread
         //      t takes column t % 8 of producers t / 8 + 64 u (whole lines per
-        //      wave), sums them in a fixed order, publishes the new g in every
-        //      replica
-        for (int o = blk, oi = 0; o * kColBlock < J; o += nb, ++oi) {
+        //      wave), sums them in a fixed order, publishes v in every replica
+        for (int o = blk, oi = 0; nb > 1 && o * kColBlock < J; o += nb, ++oi) {
             static_assert(T == 512, "the owner layout assumes 512 threads");
+            if (oi > 0) __syncthreads();  // ored still holds the previous block
             const int c = threadIdx.x & (kColBlock - 1), pb = threadIdx.x >> 3;
             const int j = o * kColBlock + c;
             const bool cv = j < J;
@@ -456,38 +629,32 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             if (threadIdx.x < kColBlock * kReplicas) {
                 const int cc = threadIdx.x & (kColBlock - 1), r = threadIdx.x >> 3;
                 const int jj = o * kColBlock + cc;
-                if (jj < J && k - k0 != A.hold_iter) {
+                if (jj < J && !hold) {
                     double csum = 0.0;
 #pragma unroll
                     for (int q = 0; q < WAVES; ++q) csum += ored[q][cc];
-                    const double gn = graw[jj] + eps * (lbl[oi * kColBlock + cc] - log(csum));
-                    put_agent(gx + ((size_t)P * kReplicas + r) * X.Gs + jj, tag_value(gn, k));
+                    const int e = oi * kColBlock + cc;
+                    put_agent(gx + ((size_t)P * kReplicas + r) * X.Gs + jj, tag_value(col_v(e, csum), k));
+                    if (kind == kItAbs64 && r == 0) cl[e] = csum;
                 }
             }
-            __syncthreads();  // ored is reused by the next block
         }
-        __syncthreads();  // the combine above still reads the old g from LDS
 
-        // ---- 3. the new g and the decision, from this workgroup's replica:
-        //      every wave polls 64 columns at a time (one load per lane in
-        //      flight: short poll rounds), the last wave also the decision
-        bool bad = false;
-        if (!fail) {
-            const double* gk_new = gx + ((size_t)P * kReplicas + rep) * X.Gs;
+        // ---- 3. v and the decision, from this workgroup's replica: every wave
+        //      polls 64 columns at a time (one load per lane in flight: short
+        //      poll rounds), the last wave also the decision
+        if (!fail && nb > 1) {
+            const double* vx = gx + ((size_t)P * kReplicas + rep) * X.Gs;
             for (int j0 = w * kWave; j0 < J; j0 += WAVES * kWave) {
                 double x[1];
-                if (!poll_tagged(gk_new + j0, 1, min(J - j0, kWave), k, x, abort_word, A.max_spin)) {
+                if (!poll_tagged(vx + j0, 1, min(J - j0, kWave), k, x, abort_word, A.max_spin)) {
                     fail = true;
                     break;
                 }
-                const int j = j0 + lane;
-                if (j < J) {
-                    graw[j] = x[0];
-                    bad |= !isfinite(x[0]);
-                }
+                if (j0 + lane < J) take_v(j0 + lane, x[0]);
             }
         }
-        if (w == WAVES - 1 && lane == 0 && !fail) {
+        if (w == WAVES - 1 && lane == 0 && !fail && nb > 1) {
             const uint64_t* dp = dec + ((size_t)P * kReplicas + rep) * 8;
             uint64_t d = get_agent(dp);
             int spin = 0;
@@ -502,11 +669,19 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
             s_dec = (uint32_t)(d & 3);
         }
-        if (__syncthreads_or(fail)) { ok = false; break; }
-        const bool bad_any = __syncthreads_or(bad);
+        if (fail) flag |= 1;
+        for (int bit = 1; bit <= 8; bit <<= 1)
+            if (__any(flag & bit) && lane == 0) atomicOr(&s_flag[P], bit);
+        __syncthreads();
+        const int fl = s_flag[P];
+        const uint32_t code = s_dec;
+        // (the other parity's flags were last read before this iteration's
+        // barriers, and are next set after the next iteration's first)
+        if (threadIdx.x == 0) s_flag[P ^ 1] = 0;
+        if (fl & 1) { ok = false; break; }
         has_prev = 1;
-        if (s_dec || bad_any) {
-            if (bad_any && blk == dblk && threadIdx.x == 0) {
+        if ((code & kDecStop) || (fl & 2)) {
+            if ((fl & 2) && blk == dblk && threadIdx.x == 0) {
                 cs.numeric_bad = 1;
                 cs.done = 1;
                 cs.stop = 1;
@@ -514,16 +689,18 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
             break;
         }
-        load_g();
+        if (fine) kind = ((code & kDecRef64) || (fl & 8)) ? kItAbs64 : kItDelta;
+        else kind = (code & kDecRef64) ? kItAbs64 : (fl & 4) ? kItAbs32 : kItPlain;
     }
 
     // the final iterate k: f of the rows, g (workgroup 0) and the control block
     if (ok) {
         double* fo = A.f[k & 1];
-        for (int lr = threadIdx.x; lr < nrows; lr += T) fo[r0 + lr] = fl[lr];
+        for (int lr = threadIdx.x; lr < nrows; lr += T)
+            fo[r0 + lr] = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
         if (blk == 0) {
             double* go = A.g[k & 1];
-            for (int j = threadIdx.x; j < J; j += T) go[j] = graw[j];
+            for (int j = threadIdx.x; j < J; j += T) go[j] = gl[j] + eps * log(vl[j]);
         }
     }
     if (blk == dblk && threadIdx.x == 0) {
