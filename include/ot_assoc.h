@@ -14,7 +14,8 @@
  * form of the Lagrangian, Sec. III-B). The cost is either a dense matrix, a
  * rate matrix R_ij with C_ij = (1/R_ij) / scale (Sec. IV, cost choice (ii):
  * load per unit traffic), or device/RRH geometry from which the rates of the
- * downlink model of Sec. II-A are regenerated on the fly and never stored.
+ * downlink model of Sec. II-A are computed on the device, the caller passing
+ * no matrix.
  *
  * Conventions for every call
  *   - Return value: OT_OK (0), a warning (> 0) or an error (< 0). No
@@ -146,9 +147,11 @@ typedef struct {
                            maxSINR and Alg. 2 calls and the timers) is carved from it, so those
                            calls allocate no device memory; bytes beyond the required size stage
                            host-memory DENSE / RATES matrices (a host matrix that does not fit
-                           gives OT_ENOMEM). NULL (default): the library allocates one block of
-                           that size itself. The batch, snapshot and serving engines keep their
-                           own device pools either way. */
+                           gives OT_ENOMEM) and hold the FP64 cost of a GEOMETRY solve (8 I J bytes;
+                           where it does not fit, every pass regenerates it). NULL (default): the
+                           library allocates one block of that size itself, and those two on
+                           demand. The batch, snapshot and serving engines keep their own device
+                           pools either way. */
     size_t workspace_bytes; /* size of `workspace` (0 when workspace is NULL) */
     int snapshot_k_split;   /* ot_assoc_solve_snapshots: 1 (default) holds the stabilised kernel
                                in BF16 high and low parts (three BF16 products per GEMM step,
@@ -191,7 +194,9 @@ ot_status ot_assoc_workspace_size(int64_t I_max, int64_t J_max, size_t *bytes);
  * opt->device (opt NULL = defaults). Takes its device buffers from
  * opt->workspace when given, else allocates one block of
  * ot_assoc_workspace_size() bytes, plus (only without a caller workspace) an
- * I x ld staging matrix when a host-memory dense or rate cost is later passed.
+ * I x ld staging matrix when a host-memory dense or rate cost is later passed
+ * and the 8 I J bytes of a geometry solve's cost (at most half of the memory
+ * free at that time; else the cost is regenerated in every pass).
  * Errors: OT_EINVAL (I_max or J_max out of range, a workspace that is too
  * small or misaligned, check_every < 0), OT_ENOMEM, OT_EDEVICE. */
 ot_status ot_assoc_create(ot_assoc **h, int64_t I_max, int64_t J_max, const ot_assoc_options *opt);

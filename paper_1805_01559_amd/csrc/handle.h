@@ -73,6 +73,10 @@ struct ot_assoc {
     int* j1 = nullptr;
     void* stage = nullptr;  // host-memory dense / rate matrices are copied here
     size_t stage_bytes = 0;
+    double* mat = nullptr;  // FP64 cost of a geometry solve, I x J (grown on demand, or in the stage's room)
+    size_t mat_bytes = 0;
+    bool mat_held = false;     // the retained cost is in `mat` (else regenerated from the positions)
+    bool reuse_cost = false;   // the next solve takes the retained cost as it is (Alg. 2's solves after the first)
     bool stage_in_ws = false;  // the stage is the tail of a caller's workspace (never freed or grown)
     void* ws = nullptr;        // the single device block all fixed buffers are carved from
     void* work = nullptr;      // 2 (I_max + J_max) doubles of per-call work space (plan blocks, timers, Alg. 2)

@@ -283,11 +283,10 @@ bool launch_plan(const Shape& s, int64_t r0, int64_t r1, int J, const double* f,
 // Shape of the LDS-resident FP32 phase: one workgroup of kPersistWaves waves
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
-// Sources whose fast-sweep cost is an FP32 value (dense FP32, FP32 rates, the
-// FP32 geometry and distance functors): the tile holds exactly what the
-// streaming sweeps compute per cell.
+// Dense FP32, FP32 rates, distances, and geometry (as the FP64 matrix of a
+// solve that has room for it, else regenerated).
 template <class Src>
-constexpr bool persist_source() { return Src::kTag == 1 || Src::kTag == 3 || Src::kTag == 5 || Src::kTag == 6; }
+constexpr bool persist_source() { return Src::kTag != 4; }
 
 template <class Src>
 const void* persist_kernel(int lpr, int cpl) {

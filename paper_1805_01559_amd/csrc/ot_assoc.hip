@@ -273,6 +273,32 @@ ot_status ensure_stage(ot_assoc* h, size_t bytes) {
     return OT_OK;
 }
 
+// Room for the FP64 cost of an I x J geometry solve: the handle's own buffer
+// (at most half of the free device memory), or with a caller's workspace what
+// lies beyond its fixed buffers. False: the cost is regenerated in every pass.
+bool ensure_mat(ot_assoc* h, int64_t I, int64_t J) {
+    const size_t bytes = sizeof(double) * (size_t)I * (size_t)J;
+    if (!h->ws_owned) {
+        h->mat = (double*)h->stage;  // (kWsAlign-aligned; geometry costs stage nothing)
+        return h->stage && h->stage_bytes >= bytes;
+    }
+    if (h->mat && h->mat_bytes >= bytes) return true;
+    size_t fr = 0, tot = 0;
+    if (hipMemGetInfo(&fr, &tot) != hipSuccess || bytes > fr / 2) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (h->mat) otk_host::dev_free(h->mat);
+    h->mat = nullptr;
+    h->mat_bytes = 0;
+    if (otk_host::dev_malloc((void**)&h->mat, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        h->mat = nullptr;
+        return false;
+    }
+    h->mat_bytes = bytes;
+    return true;
+}
 
 // Brings the cost of `c` onto the device: host matrices are staged, device
 // matrices are referenced, positions are copied (and, for the geometry cost,
@@ -282,14 +308,17 @@ ot_status ensure_stage(ot_assoc* h, size_t bytes) {
 // of input_bad, and ends the solve on the device).
 enum { kCheckNone = 0, kCheckNow = 1, kCheckDeferred = 2 };
 
-ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check) {
+//
+// With `keep` (solves) a geometry cost is evaluated once, in FP64, into the
+// handle's buffer when there is room for it.
+ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check, bool keep = false) {
     const bool validate_values = check != kCheckNone;
     const bool now = check == kCheckNow;
     int* bad = now ? h->bad : &h->ctl->input_bad;
     const int bit = now ? 1 : 8;
     Ctl* ectl = now ? nullptr : h->ctl;
     const int64_t I = c->I, J = c->J, ld = ld_of(*c), n = I * J;
-    h->retained = false;
+    h->retained = h->mat_held = false;
     h->last = *c;
     if (c->kind != OT_COST_GEOMETRY && c->kind != OT_COST_EUCLID) {
         const size_t esz = c->dtype == OT_F32 ? 4 : 8;
@@ -354,14 +383,21 @@ ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check) {
     s.j1 = h->j1;
     s.k = geo_const(c->geom, c->scale);
     const dim3 pg((unsigned)((I + 3) / 4)), pb(256);
+    const bool mat = keep && ensure_mat(h, I, J);
+    auto prepass = [&](auto nch) {
+        constexpr int N = decltype(nch)::value;
+        if (mat) hipLaunchKernelGGL(k_geo_cost<N>, pg, pb, 0, h->stream, s, I, (int)J, h->mat);
+        else hipLaunchKernelGGL(k_geo_prepass<N>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1);
+    };
     switch (pow2_at_least((int)((J + 63) / 64))) {
-        case 1: hipLaunchKernelGGL(k_geo_prepass<1>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
-        case 2: hipLaunchKernelGGL(k_geo_prepass<2>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
-        case 4: hipLaunchKernelGGL(k_geo_prepass<4>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
-        case 8: hipLaunchKernelGGL(k_geo_prepass<8>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
-        case 16: hipLaunchKernelGGL(k_geo_prepass<16>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
-        default: hipLaunchKernelGGL(k_geo_prepass<32>, pg, pb, 0, h->stream, s, I, (int)J, h->s_all, h->s_ex, h->j1); break;
+        case 1: prepass(std::integral_constant<int, 1>{}); break;
+        case 2: prepass(std::integral_constant<int, 2>{}); break;
+        case 4: prepass(std::integral_constant<int, 4>{}); break;
+        case 8: prepass(std::integral_constant<int, 8>{}); break;
+        case 16: prepass(std::integral_constant<int, 16>{}); break;
+        default: prepass(std::integral_constant<int, 32>{}); break;
     }
+    h->mat_held = mat;
     HIPCHK(h, hipGetLastError());
     h->cost_dev = nullptr;
     h->retained = true;
@@ -388,6 +424,7 @@ ot_status with_retained(ot_assoc* h, F&& fn) {
         s.inv_scale = 1.0 / c.scale;
         return fn(s, (const void*)nullptr);
     }
+    if (h->mat_held) { DenseSrc<double> s{}; s.C = h->mat; s.ld = c.J; return fn(s, h->mat); }
     GeoSrc s{};
     s.dev_xy = h->xy_dev;
     s.rrh_xy = h->xy_rrh;
@@ -727,7 +764,8 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     PersistPlan pp;
     bool persisted = false;
     int coop_par = -1;  // buffers of the iterate the cooperative path checked
-    if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && persist_plan<Src>(h, I, J, pp))
+    if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && (Src::kTag != 2 || h->mat_held) &&
+        persist_plan<Src>(h, I, J, pp))
         if ((st = run_persist<Src>(h, src, I, J, pp, stall_below, persisted))) return st;
     h->last_persistent = persisted;
     if (persisted) {
@@ -922,6 +960,7 @@ void ot_assoc_destroy(ot_assoc* h) {
     for (auto& e : h->graphs) hipGraphExecDestroy(e.exec);
     if (h->ws && h->ws_owned) otk_host::dev_free(h->ws);
     if (h->stage && !h->stage_in_ws) otk_host::dev_free(h->stage);
+    if (h->mat && h->ws_owned) otk_host::dev_free(h->mat);
     if (h->ctl_h) hipHostFree(h->ctl_h);
     hipEvent_t evs[] = {h->ev_start, h->ev_stop, h->ev_slot[0], h->ev_slot[1], h->ev_coop[0], h->ev_coop[1]};
     for (auto e : evs)
@@ -1092,7 +1131,7 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
 
     Ctl fin = c;
     int result_iter = 0, result_par = 0;
-    st = upload_cost(h, cost, kCheckDeferred);
+    if (!(h->reuse_cost && h->retained)) st = upload_cost(h, cost, kCheckDeferred, true);
     if (!st)
         st = with_retained(h, [&](const auto& src, const void* data) -> ot_status {
             return solve_with(h, src, data, I, (int)J, tol, max_iter, fin, result_iter, result_par);
@@ -1631,7 +1670,10 @@ ot_status ot_assoc_adaptive(ot_assoc* h, const ot_cost_desc* cost, const double*
     struct WantLoads {
         ot_assoc* h;
         bool prev;
-        ~WantLoads() { h->want_loads = prev; }
+        ~WantLoads() {
+            h->want_loads = prev;
+            h->reuse_cost = false;
+        }
     } want_guard{h, h->want_loads};
     h->want_loads = true;
     ot_cost_desc dc = *cost;
@@ -1663,6 +1705,7 @@ ot_status ot_assoc_adaptive(ot_assoc* h, const ot_cost_desc* cost, const double*
         ot_assoc_result res{};
         st = ot_assoc_solve(h, &dc, a_d, q_d, eps, tol, max_iter, k > 0 ? 1 : 0, &res);
         if (st < 0) return failed(st);
+        h->reuse_cost = true;  // (the same cost throughout this call, checked by its first solve)
         ++solves;
         iters += res.iterations;
         if ((st = ot_assoc_rrh_loads(h, loads.data(), OT_MEM_HOST))) return failed(st);

@@ -9,14 +9,14 @@
 namespace otk {
 
 // ------------------------------------------------------- geometry set-up --
-// One wavefront per device: the strongest RRH j1 (lowest index on ties),
-// s_all = sum_j pg_ij + n0n and s_ex = sum_{j != j1} pg_ij + n0n (FP64,
-// per-lane index order, then a fixed butterfly).
+// One wavefront per device: the gains pg of its links (column ch 64 + lane in
+// pg[ch]), the strongest RRH j1 (lowest index on ties), s_all = sum_j pg_ij + n0n
+// and s_ex = sum_{j != j1} pg_ij + n0n (FP64, per-lane index order, then a
+// fixed butterfly), the same in every lane.
 template <int NCH>
-__device__ __forceinline__ void geo_prepass_row(const GeoSrc& src, int64_t i, int J, const float2* xy, int lane,
-                                                double* s_all, double* s_ex, int* j1) {
+__device__ __forceinline__ void geo_row_sums(const GeoSrc& src, int64_t i, int J, const float2* xy, int lane,
+                                             double (&pg)[NCH], double& s_all, double& s_ex, int& j1) {
     const float2 p = reinterpret_cast<const float2*>(src.dev_xy)[i];
-    double pg[NCH];
     double bv = -1.0;
     int bj = 0x7fffffff;
 #pragma unroll
@@ -47,12 +47,46 @@ __device__ __forceinline__ void geo_prepass_row(const GeoSrc& src, int64_t i, in
             if (j != bj) se += pg[ch];
         }
     }
-    sa = wave_sum(sa);
-    se = wave_sum(se);
+    s_all = wave_sum(sa) + src.k.n0n;
+    s_ex = wave_sum(se) + src.k.n0n;
+    j1 = bj;
+}
+
+template <int NCH>
+__device__ __forceinline__ void geo_prepass_row(const GeoSrc& src, int64_t i, int J, const float2* xy, int lane,
+                                                double* s_all, double* s_ex, int* j1) {
+    double pg[NCH], sa, se;
+    int bj;
+    geo_row_sums<NCH>(src, i, J, xy, lane, pg, sa, se, bj);
     if (lane == 0) {
-        s_all[i] = sa + src.k.n0n;
-        s_ex[i] = se + src.k.n0n;
+        s_all[i] = sa;
+        s_ex[i] = se;
         j1[i] = bj;
+    }
+}
+
+// The FP64 geometry cost of a whole solve in one pass (C: I x J row-major):
+// the gains that the interference sums need are at hand in registers, so a
+// cell takes one hash, one normal draw and one logarithm more. The passes over
+// the cost that follow (references, polish, check, plan) then read it where
+// each regenerated it at about 500 VALU lane-instructions per cell. Bound by
+// those of this one pass.
+template <int NCH>
+__global__ __launch_bounds__(256) void k_geo_cost(GeoSrc src, int64_t I, int J, double* C) {
+    __shared__ float2 xy[2048];
+    for (int c = threadIdx.x; c < J; c += blockDim.x) xy[c] = reinterpret_cast<const float2*>(src.rrh_xy)[c];
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int64_t i = (int64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+    if (i >= I) return;
+    double pg[NCH], sa, se;
+    int bj;
+    geo_row_sums<NCH>(src, i, J, xy, lane, pg, sa, se, bj);
+    double* row = C + i * J;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        const int j = ch * 64 + lane;
+        if (j < J) row[j] = src.k.cscale / log1p(pg[ch] / (j == bj ? se : sa - pg[ch]));
     }
 }
 
