@@ -75,6 +75,8 @@ struct ot_assoc {
     size_t stage_bytes = 0;
     double* mat = nullptr;  // FP64 cost of a geometry solve, I x J (grown on demand, or in the stage's room)
     size_t mat_bytes = 0;
+    float* ker = nullptr;   // stored kernel of the streamed cooperative phase (likewise)
+    size_t ker_bytes = 0;
     bool mat_held = false;     // the retained cost is in `mat` (else regenerated from the positions)
     bool reuse_cost = false;   // the next solve takes the retained cost as it is (Alg. 2's solves after the first)
     bool stage_in_ws = false;  // the stage is the tail of a caller's workspace (never freed or grown)

@@ -1,9 +1,9 @@
 // Kernel launchers of the single-instance path: the launch shape of the
 // iteration, check and plan kernels, the template ladders that map a shape
 // onto a kernel instantiation, and the cooperative kernel of a cost source.
-// Their kernel instantiations are compiled in launch_dense.hip,
-// launch_rates.hip and launch_geo.hip (one cost source family each, built in
-// parallel); ot_assoc.hip declares them with OT_LAUNCHERS(extern, ...).
+// Their kernel instantiations are compiled in launch_*.hip, the cooperative
+// kernels' in coop_*.hip (one cost source family each, built in parallel);
+// ot_assoc.hip declares them with OT_LAUNCHERS(extern, ...), OT_COOP(extern, ...).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,7 +19,10 @@ namespace otk_launch {
 using namespace otk;
 
 constexpr int kMaxNb = 1024;  // workgroups per sweep (partial rows)
-constexpr int kPersistWaves = 8;
+// Waves per workgroup of the cooperative kernels: rows of more than 1024
+// columns hold 32 FP64 column partials per lane while a reference is taken,
+// more than the 256 registers of a wave when two share a SIMD.
+constexpr int persist_waves(int J) { return J <= 1024 ? 8 : 4; }
 
 inline int pow2_at_least(int n) {
     int p = 1;
@@ -280,7 +283,7 @@ bool launch_plan(const Shape& s, int64_t r0, int64_t r1, int J, const double* f,
 }
 
 
-// Shape of the LDS-resident FP32 phase: one workgroup of kPersistWaves waves
+// Shape of the LDS-resident FP32 phase: one workgroup of persist_waves waves
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 // Dense FP32, FP32 rates, distances, and geometry (as the FP64 matrix of a
@@ -288,23 +291,37 @@ bool launch_plan(const Shape& s, int64_t r0, int64_t r1, int J, const double* f,
 template <class Src>
 constexpr bool persist_source() { return Src::kTag != 4; }
 
+// The streamed form takes the sources of persist_source except the geometry
+// functor: without room for its FP64 cost there is none for the kernel.
 template <class Src>
-const void* persist_kernel(int lpr, int cpl) {
-    if constexpr (!persist_source<Src>()) {
-        return nullptr;
-    } else {
-    if (lpr == 32) {
-        switch (cpl) {
-            case 2: return (const void*)k_persist<Src, 2, 32, kPersistWaves>;
-            case 4: return (const void*)k_persist<Src, 4, 32, kPersistWaves>;
-            case 8: return (const void*)k_persist<Src, 8, 32, kPersistWaves>;
-            case 13: return (const void*)k_persist<Src, 13, 32, kPersistWaves>;
-            default: return (const void*)k_persist<Src, 16, 32, kPersistWaves>;
+constexpr bool stream_source() { return persist_source<Src>() && Src::kTag != 5; }
+
+template <class Src>
+const void* persist_kernel(int lpr, int cpl, bool gm) {
+    constexpr int W = 8;
+    if constexpr (stream_source<Src>()) {
+        if (gm) {
+            if (lpr == 32) return cpl == 4 ? (const void*)k_persist<Src, 4, 32, W, true>
+                                : cpl == 8 ? (const void*)k_persist<Src, 8, 32, W, true>
+                                           : (const void*)k_persist<Src, 16, 32, W, true>;
+            return cpl == 16 ? (const void*)k_persist<Src, 16, 64, W, true> : (const void*)k_persist<Src, 32, 64, persist_waves(2048), true>;
         }
     }
-    if (cpl == 16) return (const void*)k_persist<Src, 16, 64, kPersistWaves>;
-    return (const void*)k_persist<Src, 32, 64, kPersistWaves>;
+    if constexpr (persist_source<Src>()) {
+        if (gm) return nullptr;
+        if (lpr == 32) {
+            switch (cpl) {
+                case 2: return (const void*)k_persist<Src, 2, 32, W, false>;
+                case 4: return (const void*)k_persist<Src, 4, 32, W, false>;
+                case 8: return (const void*)k_persist<Src, 8, 32, W, false>;
+                case 13: return (const void*)k_persist<Src, 13, 32, W, false>;
+                default: return (const void*)k_persist<Src, 16, 32, W, false>;
+            }
+        }
+        if (cpl == 16) return (const void*)k_persist<Src, 16, 64, W, false>;
+        return (const void*)k_persist<Src, 32, 64, persist_waves(2048), false>;
     }
+    return nullptr;
 }
 
 }  // namespace otk_launch
@@ -323,5 +340,7 @@ const void* persist_kernel(int lpr, int cpl) {
                                                         float*, const S&, hipStream_t);                            \
     EXT template bool otk_launch::launch_plan<S, double>(const otk_launch::Shape&, int64_t, int64_t, int,           \
                                                          const double*, const double*, const otk::SolveParams*,    \
-                                                         double*, const S&, hipStream_t);                          \
-    EXT template const void* otk_launch::persist_kernel<S>(int, int);
+                                                         double*, const S&, hipStream_t);
+
+// The cooperative kernels of cost source S (coop_*.hip).
+#define OT_COOP(EXT, S) EXT template const void* otk_launch::persist_kernel<S>(int, int, bool);

@@ -44,6 +44,12 @@ OT_LAUNCHERS(extern, RatesSrc<float>)
 OT_LAUNCHERS(extern, RatesSrc<double>)
 OT_LAUNCHERS(extern, GeoSrc)
 OT_LAUNCHERS(extern, EuclidSrc)
+OT_COOP(extern, DenseSrc<float>)
+OT_COOP(extern, DenseSrc<double>)
+OT_COOP(extern, RatesSrc<float>)
+OT_COOP(extern, RatesSrc<double>)
+OT_COOP(extern, GeoSrc)
+OT_COOP(extern, EuclidSrc)
 
 using otk_launch::kMaxNb;
 
@@ -273,31 +279,50 @@ ot_status ensure_stage(ot_assoc* h, size_t bytes) {
     return OT_OK;
 }
 
-// Room for the FP64 cost of an I x J geometry solve: the handle's own buffer
-// (at most half of the free device memory), or with a caller's workspace what
-// lies beyond its fixed buffers. False: the cost is regenerated in every pass.
-bool ensure_mat(ot_assoc* h, int64_t I, int64_t J) {
-    const size_t bytes = sizeof(double) * (size_t)I * (size_t)J;
+// Device memory a solve may use beyond the fixed buffers, in `*p` (room for
+// *have bytes): the handle's own buffer, grown on demand (to at most half of the
+// free device memory), or with a caller's workspace what lies beyond its
+// fixed buffers and `skip` bytes. False: there is none, and the solve runs
+// the form that needs none.
+bool ensure_room(ot_assoc* h, void** p, size_t* have, size_t bytes, size_t skip) {
     if (!h->ws_owned) {
-        h->mat = (double*)h->stage;  // (kWsAlign-aligned; geometry costs stage nothing)
-        return h->stage && h->stage_bytes >= bytes;
+        skip = (skip + kWsAlign - 1) / kWsAlign * kWsAlign;
+        if (!h->stage || h->stage_bytes < skip + bytes) return false;
+        *p = (char*)h->stage + skip;
+        return true;
     }
-    if (h->mat && h->mat_bytes >= bytes) return true;
+    if (*p && *have >= bytes) return true;
     size_t fr = 0, tot = 0;
-    if (hipMemGetInfo(&fr, &tot) != hipSuccess || bytes > fr / 2) {
+    if (hipMemGetInfo(&fr, &tot) != hipSuccess || bytes > (fr + *have) / 2) {
         (void)hipGetLastError();
         return false;
     }
-    if (h->mat) otk_host::dev_free(h->mat);
-    h->mat = nullptr;
-    h->mat_bytes = 0;
-    if (otk_host::dev_malloc((void**)&h->mat, bytes) != hipSuccess) {
+    if (*p) otk_host::dev_free(*p);
+    *p = nullptr;
+    *have = 0;
+    if (otk_host::dev_malloc(p, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        h->mat = nullptr;
+        *p = nullptr;
         return false;
     }
-    h->mat_bytes = bytes;
+    *have = bytes;
     return true;
+}
+
+// Room for the FP64 cost of an I x J geometry solve (which stages nothing else).
+bool ensure_mat(ot_assoc* h, int64_t I, int64_t J) {
+    return ensure_room(h, (void**)&h->mat, &h->mat_bytes, sizeof(double) * (size_t)I * (size_t)J, 0);
+}
+
+// Room for the stored kernel of the streamed cooperative phase: beside the
+// kept geometry cost or the staged host matrix.
+bool ensure_ker(ot_assoc* h, size_t bytes) {
+    const ot_cost_desc& c = h->last;
+    const size_t cells = (size_t)c.I * (size_t)(c.kind == OT_COST_DENSE || c.kind == OT_COST_RATES ? ld_of(c) : c.J);
+    size_t skip = 0;
+    if (h->mat_held) skip = 8 * cells;
+    else if (h->cost_dev && h->cost_dev == h->stage) skip = cells * (c.dtype == OT_F32 ? 4 : 8);
+    return ensure_room(h, (void**)&h->ker, &h->ker_bytes, bytes, skip);
 }
 
 // Brings the cost of `c` onto the device: host matrices are staged, device
@@ -608,17 +633,18 @@ struct Solver {
 };
 
 // ------------------------------------------------------ cooperative phase --
-// Shape of the LDS-resident FP32 phase: one workgroup of kPersistWaves waves
+// Shape of the LDS-resident FP32 phase: one workgroup of p.waves waves
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 
 struct PersistPlan {
-    int lpr = 0, cpl = 0, ncl = 0, rpw = 0, nb = 0, Jp = 0;
+    int lpr = 0, cpl = 0, ncl = 0, rpw = 0, nb = 0, Jp = 0, waves = 8;
     size_t lds = 0;
+    bool gm = false;  // the streamed form: the stored kernel in device memory
 };
 
 template <class Src>
-bool persist_plan(const ot_assoc* h, int64_t I, int J, PersistPlan& p) {
+bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     if (!persist_source<Src>() || h->num_cu < 1 || h->lds_max < 1 || I < 1 || !h->xch) return false;
     // cells per lane: the smallest instantiated width that covers the row
     if (J <= 512) {
@@ -631,16 +657,26 @@ bool persist_plan(const ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     } else {
         return false;
     }
-    const int slots = kPersistWaves * (64 / p.lpr);  // rows per wave step of the workgroup
+    p.waves = persist_waves(J);
+    const int slots = p.waves * (64 / p.lpr);  // rows per wave step of the workgroup
     const int64_t per = (int64_t)h->num_cu * slots;
     const int64_t steps = (I + per - 1) / per;
     p.ncl = (J + p.lpr - 1) / p.lpr;
     p.Jp = p.ncl * p.lpr;
     p.rpw = (int)(steps * slots);
     p.nb = (int)((I + p.rpw - 1) / p.rpw);
-    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, kPersistWaves, (p.cpl - p.ncl) * p.lpr, p.nb);
+    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, (p.cpl - p.ncl) * p.lpr, p.nb);
     // (a little LDS stays for the kernel's static arrays)
-    return p.nb <= h->num_cu && p.nb <= kMaxCoopGroups && p.lds + 2048 <= (size_t)h->lds_max;
+    if (p.nb > h->num_cu || p.nb > kMaxCoopGroups) return false;
+    if (p.lds + 2048 <= (size_t)h->lds_max) return true;
+    // too large for LDS: the kernel in device memory, 16 bytes per lane (up to
+    // 128, 256 and 512 columns for 32 lanes, 1024 and 2048 for 64)
+    if (!stream_source<Src>()) return false;
+    p.gm = true;
+    p.cpl = J <= 128 ? 4 : J <= 256 ? 8 : J <= 1024 ? 16 : 32;
+    p.Jp = (J + 3) & ~3;
+    p.lds = persist_lds_bytes(p.rpw, J, 0, p.waves, 0, p.nb);
+    return p.lds + 2048 <= (size_t)h->lds_max && ensure_ker(h, sizeof(float) * (size_t)I * p.Jp);
 }
 
 // Issues the cooperative FP32 phase. `launched` is false (and nothing is
@@ -650,13 +686,13 @@ template <class Src>
 ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const PersistPlan& p, double stall_below,
                       bool& launched) {
     launched = false;
-    const void* kern = persist_kernel<Src>(p.lpr, p.cpl);
+    const void* kern = persist_kernel<Src>(p.lpr, p.cpl, p.gm);
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) != hipSuccess) {
         (void)hipGetLastError();
         return OT_OK;
     }
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kPersistWaves * 64, p.lds) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, p.waves * 64, p.lds) != hipSuccess ||
         (int64_t)per_cu * h->num_cu < p.nb) {
         (void)hipGetLastError();
         return OT_OK;
@@ -684,6 +720,7 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.xch = h->xch;
     A.ctl = h->ctl;
     A.prm = h->prm;
+    A.tile = h->ker;
     // (the solve's init launch has zeroed the exchange block, unless it
     // could not know that this launch would follow)
     if (!h->xch_zeroed) {
@@ -695,7 +732,7 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     Src sv = src;
     void* args[] = {(void*)&A, (void*)&sv};
     if (h->ev_coop[0]) HIPCHK(h, hipEventRecord(h->ev_coop[0], h->stream));
-    const hipError_t e = hipLaunchCooperativeKernel(kern, dim3((unsigned)p.nb), dim3(kPersistWaves * 64), args,
+    const hipError_t e = hipLaunchCooperativeKernel(kern, dim3((unsigned)p.nb), dim3(p.waves * 64), args,
                                                     (unsigned)p.lds, h->stream);
     if (e == hipErrorCooperativeLaunchTooLarge) {
         (void)hipGetLastError();
@@ -767,7 +804,7 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && (Src::kTag != 2 || h->mat_held) &&
         persist_plan<Src>(h, I, J, pp))
         if ((st = run_persist<Src>(h, src, I, J, pp, stall_below, persisted))) return st;
-    h->last_persistent = persisted;
+    h->last_persistent = persisted && !pp.gm;
     if (persisted) {
         // polish decided on the device, then the check: one host wait
         const int np = std::max(0, h->opt.polish_iters);
@@ -961,6 +998,7 @@ void ot_assoc_destroy(ot_assoc* h) {
     if (h->ws && h->ws_owned) otk_host::dev_free(h->ws);
     if (h->stage && !h->stage_in_ws) otk_host::dev_free(h->stage);
     if (h->mat && h->ws_owned) otk_host::dev_free(h->mat);
+    if (h->ker && h->ws_owned) otk_host::dev_free(h->ker);
     if (h->ctl_h) hipHostFree(h->ctl_h);
     hipEvent_t evs[] = {h->ev_start, h->ev_stop, h->ev_slot[0], h->ev_slot[1], h->ev_coop[0], h->ev_coop[1]};
     for (auto e : evs)

@@ -20,13 +20,11 @@
 //
 // A cell costs two multiply-adds per iteration and no exponential; those run
 // only when a reference is taken (C is then read again):
-//   - at the first iteration, and again when a scaling leaves [2^-40, 2^40],
-//     with FP32 exponentials;
+//   - at the first iteration, and again when a scaling leaves [2^-40, 2^40];
 //   - once the residual is below 1e-5 (for targets below the FP32 noise of
-//     about 4e-8 of residual), with FP64 exponentials and FP64 sums R_i of the
-//     rows and of the columns. From there on the iteration adds only the
-//     change against the reference, S_i = R_i + sum_j E_ij (v_j - 1) and likewise
-//     for the columns, so its FP32 rounding is 2^-24 of |v - 1| instead of
+//     about 4e-8 of residual). From there on the iteration adds to the FP64 sums
+//     R_i of the reference, and likewise to those of its columns, only the
+//     change against it, S_i = R_i + sum_j E_ij (v_j - 1), so its FP32 rounding is 2^-24 of |v - 1| instead of
 //     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
 //     cost were needed before.
 //
@@ -149,7 +147,8 @@ __device__ bool poll_tagged(const double* base, int64_t stride, int n, int k, do
 struct PersistArgs {
     int64_t I;
     int J;
-    int Jp;   // LDS row stride of the kernel tile (ncl * LPR; padding holds 0)
+    int Jp;   // row stride of the kernel tile (in LDS ncl * LPR, in device memory J rounded up
+              // to 4; the padding holds 0)
     int ncl;  // cells per lane of a row: column q LPR + sub for q < ncl (<= CPL)
     int rpw;  // rows per workgroup: a whole number of wave steps
     int max_spin;
@@ -163,6 +162,7 @@ struct PersistArgs {
     double* xch;   // exchange block (persist_exchange_doubles)
     Ctl* ctl;
     const SolveParams* prm;
+    float* tile;   // the stored kernel in device memory, I x Jp (streamed form only)
 };
 
 // Column blocks each workgroup owns at most (workgroup w owns w, w + nb, ...).
@@ -171,7 +171,8 @@ __host__ __device__ inline int persist_owned_blocks(int nb, int J) {
     return (nblk + nb - 1) / nb;
 }
 // Dynamic LDS of k_persist in bytes (the layout the kernel carves): the
-// tile, a slack of (CPL - ncl) LPR floats after it, then the column vectors
+// tile of rpw rows of stride Jp (Jp = 0: the tile is in device memory), a slack
+// of (CPL - ncl) LPR floats after it, then the column vectors
 // (G, v), the row vectors (a, m, R, S), b and the reference column sums of
 // the owned columns, x and the fold buffer of the column partials (FP32 partials of all waves at
 // once up to 512 columns, of half of them for wider rows).
@@ -182,27 +183,29 @@ __host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int 
            (size_t)(J > 512 ? waves / 2 : waves) * Jr4 * 4;
 }
 
-// Kinds of iteration of the cooperative phase (the same in every workgroup).
-enum : int { kItAbs32 = 0, kItPlain = 1, kItAbs64 = 2, kItDelta = 3 };
-// Decision codes: bit 0 stop, bit 1 take the FP64 reference next.
-constexpr int kDecStop = 1, kDecRef64 = 2;
-// The FP64 reference is taken once the residual is below this: the scalings
+// Kinds of iteration of the cooperative phase (the same in every workgroup):
+// a reference taken for plain sums, plain sums, one taken for delta sums,
+// delta sums.
+enum : int { kItRef = 0, kItPlain = 1, kItRefDelta = 2, kItDelta = 3 };
+// Decision codes: bit 0 stop, bit 1 take a reference for delta sums next.
+constexpr int kDecStop = 1, kDecRefDelta = 2;
+// Delta sums begin once the residual is below this: the scalings
 // then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
 // residuals down to about 1e-12, far below the FP32 noise (4e-8) of the plain
 // sums; an earlier switch would buy nothing, a later one comes too close to
 // that noise.
-constexpr double kRef64Below = 1e-5;
-// A plain reference is renewed when a scaling leaves [2^-40, 2^40]: an entry
+constexpr double kDeltaBelow = 1e-5;
+// A reference for plain sums is renewed when a scaling leaves [2^-40, 2^40]: an entry
 // flushed to zero in FP32 (below 2^-126 of its row's largest) then stands for
 // less than 2^-46 of any row or column sum.
 constexpr double kScaleMax = 0x1p40;
-// The delta sums keep |v - 1| below this (else the FP64 reference is renewed).
+// The delta sums keep |v - 1| below this (else the reference is renewed).
 constexpr double kDeltaMax = 0.125;
 
 // The stop rule of the cooperative phase, run by one lane: like the fast mode
 // of bookkeep, except that a solve whose target lies below the FP32 noise
-// (stall_below) goes on past it: the plain sums are left for the FP64 reference
-// and its delta sums (returned as kDecRef64), whose residuals are good to about
+// (stall_below) goes on past it: the plain sums are left for delta sums
+// (returned as kDecRefDelta), whose residuals are good to about
 // 1e-6 of the residual r_ref at which the reference was taken and are therefore
 // compared with tol itself. Long delta phases (a slowly converging instance
 // whose scalings drift far from the reference) renew the reference.
@@ -216,7 +219,7 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
     c->has_prev = 1;
     c->last_fp64 = 0;
     const double target = c->tol_fast > 0.0 ? c->tol_fast : c->tol;
-    const bool fine = kind == kItAbs64 || kind == kItDelta;  // residuals of the FP64 reference
+    const bool fine = kind == kItRefDelta || kind == kItDelta;  // residuals of delta sums
     double mn = pinf64();
     int nfin = 0;
     for (int q = 0; q < 4; ++q)
@@ -228,10 +231,10 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
     const bool met = r < target && (fine || target >= stall_below);
     const bool at_check = c->check_every <= 1 || k % c->check_every == 0;
     int code = 0;
-    if (kind == kItAbs64) k_ref = k;
-    if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kRef64Below)) {
+    if (kind == kItRefDelta) k_ref = k;
+    if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kDeltaBelow)) {
         r_ref = r;
-        code = kDecRef64;
+        code = kDecRefDelta;
     }
     if ((at_check && (met || stall)) || k >= c->max_iter) c->stop = 1;
     if (bad) {
@@ -249,31 +252,38 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
 // Every cell is processed without a branch: cells q >= ncl read on into the
 // next row of the tile, or into a zero slack after it, and get x = 0. A wave
 // advances R = 64 / LPR rows per step.
-template <class Src, int CPL, int LPR, int WAVES>
+//
+// GM: the streamed form, for instances whose kernel does not fit in LDS. The
+// tile is in device memory and every iteration reads it once, 16 bytes per
+// lane (lane `sub` owns columns (q / 4 LPR + sub) 4 + q % 4), PD row steps ahead
+// (64 - 128 KB in flight per CU). Bound by that read.
+template <class Src, int CPL, int LPR, int WAVES, bool GM>
 __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
     extern __shared__ double sm[];
     constexpr int R = kWave / LPR;
     constexpr int T = WAVES * kWave;
     constexpr int U = CPL <= 16 ? 2 : 1;  // row steps in flight
-    static_assert(WAVES == 8, "the fold and the owner layout assume 8 waves");
-    const int J = A.J, Jp = A.Jp, rpw = A.rpw, ncl = A.ncl;
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int sub = lane % LPR, rg = lane / LPR;
+    static_assert(WAVES >= 4 && WAVES <= 8, "at least one wave per publishing column block, wres and ored sized for 8");
+    int J = A.J, Jp = A.Jp, ncl = A.ncl;
+    const int rpw = A.rpw;
+    int tid = (int)threadIdx.x;
+    int lane = tid & (kWave - 1), w = tid / kWave;
+    int sub = lane % LPR, rg = lane / LPR;
     const int nb = (int)gridDim.x, blk = (int)blockIdx.x;
     const int64_t r0 = (int64_t)blk * rpw;
     const int nrows = (int)max((int64_t)0, min((int64_t)rpw, A.I - r0));
     const int Jr2 = (J + 1) & ~1, Jr4 = (J + 3) & ~3;
-    const int slack = (CPL - ncl) * LPR;  // (a multiple of 32 floats: what follows stays 8-byte aligned)
-    float* tile = reinterpret_cast<float*>(sm);
-    double* gl = reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);  // G_j of the reference
+    const int slack = GM ? 0 : (CPL - ncl) * LPR;  // (a multiple of 32 floats: what follows stays 8-byte aligned)
+    float* tile = GM ? A.tile + r0 * Jp : reinterpret_cast<float*>(sm);
+    double* gl = GM ? sm : reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);  // G_j of the reference
     double* vl = gl + Jr2;    // v_j = exp((g_j - G_j) / eps)
     double* al = vl + Jr2;    // a_i
     double* ml = al + rpw;    // m_i: the shift of row i's stored kernel entries (log2)
-    double* Rl = ml + rpw;    // R_i = sum_j E_ij, FP64 (delta sums only)
+    double* Rl = ml + rpw;    // R_i = sum_j E_ij of the FP64 entries
     double* Sl = Rl + rpw;    // S_i = sum_j E_ij v_j of the last row update
     const int nown = persist_owned_blocks(nb, J);
     double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block)
-    double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the FP64 reference
+    double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the reference (delta sums)
     float* xl = reinterpret_cast<float*>(cl + (size_t)kColBlock * nown);  // v_j, or v_j - 1 for delta sums, in FP32
     float* red = xl + Jr4;
     __shared__ Ctl cs;  // decision workgroup: the control block for the whole launch
@@ -298,27 +308,31 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     const double kk = A.prm->kk, eps = A.prm->eps, inv_eps = 1.0 / A.prm->eps;
 
     exp2_tab_fill(e2tab);
-    for (int lr = threadIdx.x; lr < rpw; lr += T) {
+    for (int lr = tid; lr < rpw; lr += T) {
         al[lr] = lr < nrows ? A.a[r0 + lr] : 0.0;
         ml[lr] = 0.0;
         Rl[lr] = Sl[lr] = 1.0;
     }
     const double* g_in = A.g[k0 & 1];
-    for (int j = threadIdx.x; j < J; j += T) {
+    for (int j = tid; j < J; j += T) {
         gl[j] = g_in[j];
         vl[j] = 1.0;
     }
-    for (int e = threadIdx.x; e < kColBlock * nown; e += T) {
+    for (int e = tid; e < kColBlock * nown; e += T) {
         const int j = (blk + (e / kColBlock) * nb) * kColBlock + e % kColBlock;
         bl[e] = j < J ? A.b[j] : 1.0;
         cl[e] = 0.0;
     }
-    for (int e = threadIdx.x; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0.0f;
-    if (threadIdx.x < 2) s_flag[threadIdx.x] = 0;
+    for (int e = tid; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0.0f;
+    // column of cell q of this lane: as the references are taken, and as the
+    // iterations read the tile
+    auto col_ref = [&](int q) { return q * LPR + sub; };
+    auto col_it = [&](int q) { return GM ? ((q / 4) * LPR + sub) * 4 + q % 4 : q * LPR + sub; };
+    if (tid < 2) s_flag[tid] = 0;
     // the decision workgroup (the last one: with fewer column blocks than
     // workgroups it owns none) sums the residuals and takes the stop decision
     const int dblk = nb - 1;
-    if (blk == dblk && threadIdx.x == 0) cs = *ctl;
+    if (blk == dblk && tid == 0) cs = *ctl;
     double r_ref = 0.0;  // (the deciding lane's)
     int k_ref = 0;
 
@@ -327,90 +341,102 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     int k = k0;
 
     // Row update of an iteration that takes a new reference G = g: the kernel
-    // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i the row maximum,
-    // from FP64 arguments, stored in FP32. The exponentials are FP32, or with
-    // P64 FP64; the column partials sum_i E_ij a_i / S_i then are FP64, too.
-    auto absorb = [&](auto& ac) {
-        using E = std::decay_t<decltype(ac[0])>;
-        constexpr bool P64 = sizeof(E) == 8;
+    // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i about the row maximum,
+    // in FP64 (the table-driven exponential), stored in FP32; S_i = R_i and the
+    // column partials sum_i E_ij a_i / S_i are sums of the FP64 entries.
+    auto take_reference = [&](double (&ac)[CPL]) {
+        constexpr bool kAhead = Src::kCheap && CPL <= 16;  // a row's loads one step ahead, where the registers allow it
         double* stage = reinterpret_cast<double*>(red);
         src.stage(stage, J);
-        for (int j = threadIdx.x; j < J; j += T) {
+        for (int j = tid; j < J; j += T) {
             gl[j] += eps * log(vl[j]);
             vl[j] = 1.0;
         }
+        // the previous row sums as logarithms (log2 sum_j exp((g_j - C_ij) / eps)),
+        // at the launch's start from f
+        for (int lr = tid; lr < nrows; lr += T)
+            Rl[lr] = k == k0 + 1 ? (has_prev ? (log(al[lr]) - A.f[k0 & 1][r0 + lr] * inv_eps) * kLog2e : 0.0)
+                                 : ml[lr] + log2(Sl[lr]);
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < CPL; ++q) ac[q] = 0;
-        res = 0.0;
-        // (a row's loads are issued one step ahead)
-        typename Src::template Raw<1> nraw[CPL];
-        auto fetch = [&](int st) {
+        typename Src::template Raw<1> nraw[kAhead ? CPL : 1];
+        [[maybe_unused]] auto fetch = [&](int st, auto& to) {
             const int lr = (st * WAVES + w) * R + rg;
             auto row = src.row(r0 + (lr < nrows ? lr : 0));
 #pragma unroll
             for (int q = 0; q < CPL; ++q)
-                if (q < ncl) nraw[q] = src.template load<1>(row, q * LPR + sub, J);
+                if (q < ncl) to[q] = src.template load<1>(row, q * LPR + sub, J);
         };
-        if (nrows > 0) fetch(0);
-        for (int st = 0; st < steps && nrows > 0; ++st) {
+        if constexpr (kAhead) fetch(0, nraw);
+        for (int st = 0; st < steps; ++st) {
             const int lr = (st * WAVES + w) * R + rg;
             const bool vrow = lr < nrows;
             const int64_t i = r0 + (vrow ? lr : 0);
-            typename Src::template Raw<1> raw[CPL];
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) raw[q] = nraw[q];
-            if (st + 1 < steps) fetch(st + 1);
-            auto row = src.row(i);
             double t[CPL];
             float mx = -__builtin_huge_valf();
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
+            auto row = src.row(i);
+            auto arg = [&](int q, const typename Src::template Raw<1>& raw) {
                 t[q] = -pinf64();
                 const int j = q * LPR + sub;
-                if (q < ncl && j < J && vrow) t[q] = (gl[j] - src.template cost<true, 1>(row, raw[q], 0, i, j, stage)) * kk;
+                if (q < ncl && j < J && vrow) t[q] = (gl[j] - src.template cost<true, 1>(row, raw, 0, i, j, stage)) * kk;
                 mx = fmaxf(mx, (float)t[q]);
+            };
+            if constexpr (kAhead) {
+                typename Src::template Raw<1> raw[CPL];
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) raw[q] = nraw[q];
+                if (st + 1 < steps) fetch(st + 1, nraw);
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) arg(q, raw[q]);
+            } else {
+                constexpr int G = CPL < 4 ? CPL : 4;  // cells at a time
+#pragma unroll
+                for (int q0 = 0; q0 < CPL; q0 += G) {
+                    typename Src::template Raw<1> raw[G];
+#pragma unroll
+                    for (int u = 0; u < G; ++u)
+                        if (q0 + u < CPL && q0 + u < ncl) raw[u] = src.template load<1>(row, (q0 + u) * LPR + sub, J);
+#pragma unroll
+                    for (int u = 0; u < G; ++u)
+                        if (q0 + u < CPL) arg(q0 + u, raw[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             const double m = fmax((double)group_max<LPR>(mx), -1e300);
-            E ev[CPL];
-            E s = 0, s2 = 0;  // even and odd cells: two shorter add chains
+            double s = 0, s2 = 0;  // even and odd cells: two shorter add chains
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
-                const double d = t[q] - m;
-                if constexpr (P64) ev[q] = exp2_tab(fmax(d, -2000.0), e2tab);  // (2^-2000 is 0)
-                else ev[q] = exp2_f32((float)d);
-                if (q & 1) s2 += ev[q];
-                else s += ev[q];
+                t[q] = exp2_tab(fmax(t[q] - m, -2000.0), e2tab);  // (2^-2000 is 0)
+                if (q & 1) s2 += t[q];
+                else s += t[q];
+                if constexpr (!kAhead)
+                    if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
-            const double S = group_sum<LPR>((double)(s + s2));
-            const double ai = al[lr];
-            E wq = 0;
-            if (vrow) {
-                if constexpr (P64) wq = ai / S;
-                else wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
-            }
+            const double S = group_sum<LPR>(s + s2);
+            const double wq = vrow ? al[lr] / S : 0.0;
             float* trow = tile + (size_t)lr * Jp + sub;
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
-                ac[q] = fma(ev[q], wq, ac[q]);
-                if (q < ncl) trow[q * LPR] = (float)ev[q];
+                ac[q] = fma(t[q], wq, ac[q]);
+                if (GM ? (vrow && q * LPR + sub < Jp) : q < ncl) trow[q * LPR] = (float)t[q];
             }
             if (sub == 0 && vrow) {
-                if (has_prev) {  // (f of the previous iterate: from the buffers at the launch's start)
-                    const double la = log(ai);
-                    const double fp = k == k0 + 1 ? A.f[k0 & 1][r0 + lr] : eps * (la - kLn2 * (ml[lr] + log2(Sl[lr])));
-                    res += ai * fabs(expm1((fp - eps * (la - kLn2 * (m + log2(S)))) * inv_eps));
-                }
                 ml[lr] = m;
-                Rl[lr] = S;
                 Sl[lr] = S;
             }
         }
-        __syncthreads();  // (the fold reuses the staged source data's LDS)
+        __syncthreads();  // (the fold also reuses the staged source data's LDS)
+        // |rowsum_i - a_i| of the previous iterate, from the change of the log-sum-exp
+        res = 0.0;
+        for (int lr = tid; lr < nrows; lr += T) {
+            if (has_prev) res += al[lr] * fabs(expm1(kLn2 * (ml[lr] + log2(Sl[lr]) - Rl[lr])));
+            Rl[lr] = Sl[lr];
+        }
     };
 
     // Row update against the stored kernel: S_i = sum_j E_ij v_j, or from the
-    // FP64 reference S_i = R_i + sum_j E_ij (v_j - 1), whose FP32 rounding scales
+    // reference's FP64 sums S_i = R_i + sum_j E_ij (v_j - 1), whose FP32 rounding scales
     // with |v - 1|; the column partials sum_i E_ij a_i / S_i, or their change
     // against the reference, sum_i E_ij (a_i / S_i - a_i / R_i).
     auto rows = [&](auto delta, float (&acc)[CPL]) {
@@ -418,57 +444,88 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         float x[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
-            const int j = q * LPR + sub;
-            x[q] = (q < ncl && j < J) ? xl[j] : 0.0f;
+            const int j = col_it(q);
+            x[q] = j < J ? xl[j] : 0.0f;
         }
         res = 0.0;
-        auto step = [&](int st, auto nu) {
-            constexpr int N = decltype(nu)::value;
-            float ev[N][CPL], s[N];
+        // the row's sum, its column partials and its residual term, from its cells
+        auto row_sum = [&](const float (&ev)[CPL]) {
+            float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-                const float* trow = tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp + sub;
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) ev[u][q] = trow[q * LPR];
+            for (int q = 0; q < CPL; ++q) {
+                if (q & 1) s1 = fmaf(ev[q], x[q], s1);
+                else s0 = fmaf(ev[q], x[q], s0);
             }
+            return s0 + s1;
+        };
+        auto finish = [&](int st, const float (&ev)[CPL], float s) {
+            const int lr = (st * WAVES + w) * R + rg;
+            const bool vrow = lr < nrows;
+            const double d = group_sum<LPR>((double)s);
+            const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
+            const double S = D ? Rr + d : d;
+            float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+            if constexpr (D) wq *= -(float)d * __builtin_amdgcn_rcpf((float)Rr);
+            if (!vrow) wq = 0.0f;
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-                float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    if (q & 1) s1 = fmaf(ev[u][q], x[q], s1);
-                    else s0 = fmaf(ev[u][q], x[q], s0);
-                }
-                s[u] = s0 + s1;
-            }
-#pragma unroll
-            for (int u = 0; u < N; ++u) {
-                const int lr = ((st + u) * WAVES + w) * R + rg;
-                const bool vrow = lr < nrows;
-                const double d = group_sum<LPR>((double)s[u]);
-                const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
-                const double S = D ? Rr + d : d;
-                float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
-                if constexpr (D) wq *= -(float)d * __builtin_amdgcn_rcpf((float)Rr);
-                if (!vrow) wq = 0.0f;
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[u][q], wq, acc[q]);
-                if (sub == 0 && vrow) {
-                    res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
-                    Sl[lr] = S;
-                }
+            for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[q], wq, acc[q]);
+            if (sub == 0 && vrow) {
+                res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
+                Sl[lr] = S;
             }
         };
-        int st = 0;
-        for (; st + U <= steps; st += U) step(st, std::integral_constant<int, U>{});
-        if constexpr (U > 1)
-            for (; st < steps; ++st) step(st, std::integral_constant<int, 1>{});
+        if constexpr (GM) {
+            constexpr int NV = CPL / 4;              // 16-byte loads per lane and step
+            constexpr int PD = 4;                    // steps in flight
+            float ev[PD][CPL];
+            auto fetch = [&](int p, int st) {
+                const int lr = (st * WAVES + w) * R + rg;
+                const float* trow = tile + (size_t)(lr < nrows ? lr : 0) * Jp + 4 * sub;
+#pragma unroll
+                for (int c = 0; c < NV; ++c) {
+                    float4 y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if ((c * LPR + sub) * 4 < Jp) y = *reinterpret_cast<const float4*>(trow + c * LPR * 4);
+                    ev[p][4 * c] = y.x; ev[p][4 * c + 1] = y.y; ev[p][4 * c + 2] = y.z; ev[p][4 * c + 3] = y.w;
+                }
+            };
+#pragma unroll
+            for (int p = 0; p < PD; ++p) fetch(p, p);  // (steps past the last read row 0 of the block)
+            for (int st = 0; st < steps; st += PD) {
+#pragma unroll
+                for (int p = 0; p < PD; ++p) {
+                    if (st + p < steps) {  // uniform
+                        const float s = row_sum(ev[p]);
+                        finish(st + p, ev[p], s);
+                        if (st + p + PD < steps) fetch(p, st + p + PD);
+                    }
+                }
+            }
+        } else {
+            auto step = [&](int st, auto nu) {
+                constexpr int N = decltype(nu)::value;
+                float ev[N][CPL], s[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const float* trow = tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp + sub;
+#pragma unroll
+                    for (int q = 0; q < CPL; ++q) ev[u][q] = trow[q * LPR];
+                }
+#pragma unroll
+                for (int u = 0; u < N; ++u) s[u] = row_sum(ev[u]);
+#pragma unroll
+                for (int u = 0; u < N; ++u) finish(st + u, ev[u], s[u]);
+            };
+            int st = 0;
+            for (; st + U <= steps; st += U) step(st, std::integral_constant<int, U>{});
+            if constexpr (U > 1)
+                for (; st < steps; ++st) step(st, std::integral_constant<int, 1>{});
+        }
     };
 
     // The workgroup's column partials: the row groups of a wave (lanes
     // sub + LPR r share columns), then the waves in FP64; calls out(c, sum)
     // for this thread's columns. The residual's wave sums go to wres.
-    auto fold = [&](auto& ac, auto&& out) {
+    auto fold = [&](auto& ac, auto&& col, auto&& out) {
         using E = std::decay_t<decltype(ac[0])>;
         E* rb = reinterpret_cast<E*>(red);
         if constexpr (LPR == 32) {
@@ -478,7 +535,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         const double rw = wave_sum(res);
         if (lane == 0) wres[w] = rw;
         constexpr int NW = WAVES * 4 / ((LPR == 64 ? 2 : 1) * (int)sizeof(E));  // waves per round
-        constexpr int NC = LPR == 32 ? 1 : 4;  // columns per thread
+        constexpr int NC = (CPL * LPR + T - 1) / T;  // columns per thread
         double t[NC];
 #pragma unroll
         for (int u = 0; u < NC; ++u) t[u] = 0.0;
@@ -488,14 +545,14 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             if (w >= w0 && w < w0 + NW && rg == 0) {
 #pragma unroll
                 for (int q = 0; q < CPL; ++q) {
-                    const int j = q * LPR + sub;
-                    if (q < ncl && j < J) rb[(w - w0) * Jr4 + j] = ac[q];
+                    const int j = col(q);
+                    if (j < J) rb[(w - w0) * Jr4 + j] = ac[q];
                 }
             }
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < NC; ++u) {
-                const int c = u * T + (int)threadIdx.x;
+                const int c = u * T + tid;
                 if (c < J) {
 #pragma unroll
                     for (int q = 0; q < NW; ++q) t[u] += (double)rb[q * Jr4 + c];
@@ -504,18 +561,22 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         }
 #pragma unroll
         for (int u = 0; u < NC; ++u) {
-            const int c = u * T + (int)threadIdx.x;
+            const int c = u * T + tid;
             if (c < J) out(c, t[u]);
         }
     };
 
     __syncthreads();
-    int kind = kItAbs32;
+    int kind = kItRef;
     bool ok = true;
     for (;;) {
         ++k;
         const int P = k & 1;
-        const bool fine = kind == kItAbs64 || kind == kItDelta;  // v - 1 is what the next delta sums need
+        // (made opaque here: else the per-column masks and addresses of every
+        // phase are computed once before the loop and kept, over a hundred
+        // scalar and vector registers that then spill)
+        asm volatile("" : "+v"(tid), "+v"(lane), "+v"(sub), "+v"(rg), "+s"(J), "+s"(Jp), "+s"(ncl));
+        const bool fine = kind == kItRefDelta || kind == kItDelta;  // v - 1 is what the next delta sums need
         const bool hold = k - k0 == A.hold_iter;
         // v_j of this workgroup from the exchange (or, alone, from its own
         // sums), with the flags that choose the next iteration's kind
@@ -536,27 +597,26 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         auto out = [&](int c, double t) {
             if (nb == 1) {
                 take_v(c, col_v(c, t));
-                if (kind == kItAbs64) cl[c] = t;
+                if (kind == kItRefDelta) cl[c] = t;
             } else {
                 put_agent(prow + c, tag_value(t, k));
             }
         };
 
         // ---- 1. row update and the workgroup's column partials
-        if (kind == kItAbs64) {
+        if (kind == kItRef || kind == kItRefDelta) {
             double ac[CPL];
-            absorb(ac);
-            fold(ac, out);
+            take_reference(ac);
+            fold(ac, col_ref, out);
         } else {
             float ac[CPL];
 #pragma unroll
             for (int q = 0; q < CPL; ++q) ac[q] = 0.0f;
-            if (kind == kItAbs32) absorb(ac);
-            else if (kind == kItDelta) rows(std::true_type{}, ac);
+            if (kind == kItDelta) rows(std::true_type{}, ac);
             else rows(std::false_type{}, ac);
-            fold(ac, out);
+            fold(ac, col_it, out);
         }
-        if (threadIdx.x == T - 1 && nb > 1) {
+        if (tid == T - 1 && nb > 1) {
             double r = 0.0;
 #pragma unroll
             for (int q = 0; q < WAVES; ++q) r += wres[q];
@@ -589,25 +649,25 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         }
 
         // ---- 2. column update of the owned blocks of kColBlock columns: thread
-        //      t takes column t % 8 of producers t / 8 + 64 u (whole lines per
-        //      wave), sums them in a fixed order, publishes v in every replica
+        //      t takes column t % 8 of producers t / 8 + (T / 8) u (whole lines
+        //      per wave), sums them in a fixed order, publishes v in every replica
         for (int o = blk, oi = 0; nb > 1 && o * kColBlock < J; o += nb, ++oi) {
-            static_assert(T == 512, "the owner layout assumes 512 threads");
+            constexpr int PB = T / kColBlock, NU = kMaxCoopGroups / PB;  // producers per round, rounds
             if (oi > 0) __syncthreads();  // ored still holds the previous block
-            const int c = threadIdx.x & (kColBlock - 1), pb = threadIdx.x >> 3;
+            const int c = tid & (kColBlock - 1), pb = tid / kColBlock;
             const int j = o * kColBlock + c;
             const bool cv = j < J;
-            double x[4];
+            double x[NU];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int pr = pb + 64 * u;
+            for (int u = 0; u < NU; ++u) {
+                const int pr = pb + PB * u;
                 x[u] = (cv && pr < nb) ? get_agent(part + ((size_t)P * nb + pr) * X.Jp + j) : tag_value(0.0, k);
             }
             int spin = 0;
             for (;;) {
                 bool pend = false;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) pend |= !has_tag(x[u], k);
+                for (int u = 0; u < NU; ++u) pend |= !has_tag(x[u], k);
                 if (!__any(pend)) break;
                 if ((++spin & 31) == 0 && (get_agent(abort_word) != 0 || spin > A.max_spin)) {
                     put_agent(abort_word, (uint64_t)1);
@@ -616,18 +676,20 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 }
                 __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (!has_tag(x[u], k)) x[u] = get_agent(part + ((size_t)P * nb + pb + 64 * u) * X.Jp + j);
+                for (int u = 0; u < NU; ++u)
+                    if (!has_tag(x[u], k)) x[u] = get_agent(part + ((size_t)P * nb + pb + PB * u) * X.Jp + j);
             }
             // (tag bits of the partials stay in the sum: a relative change below 2^-50)
-            double s = ((x[0] + x[1]) + x[2]) + x[3];
+            double s = x[0];
+#pragma unroll
+            for (int u = 1; u < NU; ++u) s += x[u];
             s += dpp_d<0x128>(s);  // lanes of one wave with the same column (producers
             s = xor16_sum(s);      // pb .. pb + 7 of this wave): lane l ^ 8, l ^ 16, l ^ 32
             s = xor32_sum(s);
             if (lane < kColBlock) ored[w][lane] = s;
             if (__syncthreads_or(fail)) { fail = true; break; }
-            if (threadIdx.x < kColBlock * kReplicas) {
-                const int cc = threadIdx.x & (kColBlock - 1), r = threadIdx.x >> 3;
+            if (tid < kColBlock * kReplicas) {
+                const int cc = tid & (kColBlock - 1), r = tid >> 3;
                 const int jj = o * kColBlock + cc;
                 if (jj < J && !hold) {
                     double csum = 0.0;
@@ -635,7 +697,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                     for (int q = 0; q < WAVES; ++q) csum += ored[q][cc];
                     const int e = oi * kColBlock + cc;
                     put_agent(gx + ((size_t)P * kReplicas + r) * X.Gs + jj, tag_value(col_v(e, csum), k));
-                    if (kind == kItAbs64 && r == 0) cl[e] = csum;
+                    if (kind == kItRefDelta && r == 0) cl[e] = csum;
                 }
             }
         }
@@ -677,11 +739,11 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         const uint32_t code = s_dec;
         // (the other parity's flags were last read before this iteration's
         // barriers, and are next set after the next iteration's first)
-        if (threadIdx.x == 0) s_flag[P ^ 1] = 0;
+        if (tid == 0) s_flag[P ^ 1] = 0;
         if (fl & 1) { ok = false; break; }
         has_prev = 1;
         if ((code & kDecStop) || (fl & 2)) {
-            if ((fl & 2) && blk == dblk && threadIdx.x == 0) {
+            if ((fl & 2) && blk == dblk && tid == 0) {
                 cs.numeric_bad = 1;
                 cs.done = 1;
                 cs.stop = 1;
@@ -689,21 +751,21 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
             break;
         }
-        if (fine) kind = ((code & kDecRef64) || (fl & 8)) ? kItAbs64 : kItDelta;
-        else kind = (code & kDecRef64) ? kItAbs64 : (fl & 4) ? kItAbs32 : kItPlain;
+        if (fine) kind = ((code & kDecRefDelta) || (fl & 8)) ? kItRefDelta : kItDelta;
+        else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
     // the final iterate k: f of the rows, g (workgroup 0) and the control block
     if (ok) {
         double* fo = A.f[k & 1];
-        for (int lr = threadIdx.x; lr < nrows; lr += T)
+        for (int lr = tid; lr < nrows; lr += T)
             fo[r0 + lr] = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
         if (blk == 0) {
             double* go = A.g[k & 1];
-            for (int j = threadIdx.x; j < J; j += T) go[j] = gl[j] + eps * log(vl[j]);
+            for (int j = tid; j < J; j += T) go[j] = gl[j] + eps * log(vl[j]);
         }
     }
-    if (blk == dblk && threadIdx.x == 0) {
+    if (blk == dblk && tid == 0) {
         if (!ok) {
             cs.sync_fail = 1;
             cs.done = 1;

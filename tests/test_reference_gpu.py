@@ -99,3 +99,30 @@ def test_geometry_kept_and_regenerated(A, oracle_lib, I, J):
         check(oracle_lib, C, L.a, L.b, eps, tol, f, g, res)
         P0 = oracle_lib.plan(C, f, g, eps)
         assert np.abs(P - P0).max() <= 1e-9 * P0.max()  # (the same FP64 cost up to its rounding, times 1 / eps)
+
+
+@pytest.mark.parametrize("I,J", [(75001, 128), (40003, 250), (20481, 400), (10005, 1000), (5201, 2045)])
+def test_streamed_kernel_above_the_lds(A, oracle_lib, I, J):
+    """Instances whose kernel does not fit in LDS: held in device memory when
+    there is room, else (a workspace without any) the chunked sweeps."""
+    import torch
+    print(f"\n[case] streamed kernel {I}x{J}", flush=True)
+    rng = np.random.default_rng(I + J)
+    C = rng.uniform(0.0, 1.0, (I, J)).astype(np.float32)
+    a, b = marginals(rng, I, J)
+    eps, tol = 0.05, 1e-8
+    Cd, ad, bd = (torch.from_numpy(x).cuda() for x in (C, a, b))
+    n = A.ot_assoc_workspace_size(I, J)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    plans = []
+    for opts in ({}, dict(workspace=ws.data_ptr(), workspace_bytes=n)):
+        with A.Solver(I, J, **opts) as s:
+            st, res = s.solve_dense(Cd, ad, bd, eps, tol, 3000)
+            f, g = s.potentials()
+        assert st == A.OT_OK and not res.flags & A.OT_RESULT_PERSISTENT
+        C64 = C.astype(np.float64)
+        chk = oracle_lib.plan_stats(C64, a, b, f, g, eps)
+        assert res.marginal_violation < tol and chk["marginal_violation"] < tol * 1.05
+        plans.append(oracle_lib.plan(C64, f, g, eps))
+    # both within the residual bar of one solution
+    assert np.abs(plans[0] - plans[1]).sum() <= 1e-6
