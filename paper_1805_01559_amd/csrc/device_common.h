@@ -143,6 +143,25 @@ __device__ __forceinline__ double group_sum(double v) {
     if constexpr (LPR >= 64) v = xor32_sum(v);
     return v;
 }
+// The same sums of N values at a time, level by level, so that the N
+// dependent chains overlap.
+template <int LPR, int N>
+__device__ __forceinline__ void group_sums(double (&v)[N]) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] += dpp_d<0xB1>(v[u]);
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] += dpp_d<0x4E>(v[u]);
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] += dpp_d<0x141>(v[u]);
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] += dpp_d<0x140>(v[u]);
+    if constexpr (LPR >= 32)
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = xor16_sum(v[u]);
+    if constexpr (LPR >= 64)
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = xor32_sum(v[u]);
+}
 template <int LPR>
 __device__ __forceinline__ float group_max(float v) {
     v = fmaxf(v, dpp_f<0xB1>(v));

@@ -665,7 +665,7 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     p.Jp = p.ncl * p.lpr;
     p.rpw = (int)(steps * slots);
     p.nb = (int)((I + p.rpw - 1) / p.rpw);
-    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, (p.cpl - p.ncl) * p.lpr, p.nb);
+    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, p.cpl * p.lpr, (p.cpl - p.ncl) * p.lpr, p.nb);
     // (a little LDS stays for the kernel's static arrays)
     if (p.nb > h->num_cu || p.nb > kMaxCoopGroups) return false;
     if (p.lds + 2048 <= (size_t)h->lds_max) return true;
@@ -675,7 +675,7 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     p.gm = true;
     p.cpl = J <= 128 ? 4 : J <= 256 ? 8 : J <= 1024 ? 16 : 32;
     p.Jp = (J + 3) & ~3;
-    p.lds = persist_lds_bytes(p.rpw, J, 0, p.waves, 0, p.nb);
+    p.lds = persist_lds_bytes(p.rpw, J, 0, p.waves, p.cpl * p.lpr, 0, p.nb);
     return p.lds + 2048 <= (size_t)h->lds_max && ensure_ker(h, sizeof(float) * (size_t)I * p.Jp);
 }
 

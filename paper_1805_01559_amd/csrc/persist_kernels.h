@@ -175,12 +175,13 @@ __host__ __device__ inline int persist_owned_blocks(int nb, int J) {
 // of (CPL - ncl) LPR floats after it, then the column vectors
 // (G, v), the row vectors (a, m, R, S), b and the reference column sums of
 // the owned columns, x and the fold buffer of the column partials (FP32 partials of all waves at
-// once up to 512 columns, of half of them for wider rows).
-__host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int waves, int slack, int nb) {
-    const size_t Jr2 = (size_t)((J + 1) & ~1), Jr4 = (size_t)((J + 3) & ~3);
+// once up to 512 columns, of half of them for wider rows), both of width
+// CPL LPR, so that a lane handles all its cells alike.
+__host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int waves, int width, int slack, int nb) {
+    const size_t Jr2 = (size_t)((J + 1) & ~1);
     return ((size_t)rpw * Jp + (size_t)slack) * 4 + 2 * Jr2 * 8 + 4 * (size_t)rpw * 8 +
-           2 * (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + Jr4 * 4 +
-           (size_t)(J > 512 ? waves / 2 : waves) * Jr4 * 4;
+           2 * (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + (size_t)width * 4 +
+           (size_t)(J > 512 ? waves / 2 : waves) * width * 4;
 }
 
 // Kinds of iteration of the cooperative phase (the same in every workgroup):
@@ -246,23 +247,24 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
     return (c->stop | c->done) ? kDecStop : code;
 }
 
-// Lane layout: a row is handled by LPR lanes (32 or 64); lane `sub` owns
-// columns q LPR + sub, q < CPL, so consecutive lanes read consecutive LDS
-// words, each at a constant offset from the row (one address per row step).
-// Every cell is processed without a branch: cells q >= ncl read on into the
-// next row of the tile, or into a zero slack after it, and get x = 0. A wave
-// advances R = 64 / LPR rows per step.
+// Lane layout: a row is handled by LPR lanes (32 or 64) of CPL cells each. The
+// iterations read it 16 bytes per lane (lane `sub` owns columns (c LPR + sub) 4
+// to + 3 of load c), the up to three cells past the last whole load word by
+// word (columns q LPR + sub). Every cell is processed without a branch: cells
+// past J read on into the next row of the tile, or into a zero slack after it,
+// and get x = 0. A wave advances R = 64 / LPR rows per step and takes U steps
+// together. References are taken with columns q LPR + sub, as the cost is read.
 //
 // GM: the streamed form, for instances whose kernel does not fit in LDS. The
-// tile is in device memory and every iteration reads it once, 16 bytes per
-// lane (lane `sub` owns columns (q / 4 LPR + sub) 4 + q % 4), PD row steps ahead
-// (64 - 128 KB in flight per CU). Bound by that read.
+// tile is in device memory and every iteration reads it once, PD row steps
+// ahead (64 - 128 KB in flight per CU). Bound by that read.
 template <class Src, int CPL, int LPR, int WAVES, bool GM>
 __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
-    extern __shared__ double sm[];
+    extern __shared__ __align__(16) float4 sm4[];  // (its 16-byte reads have to be aligned)
+    double* sm = reinterpret_cast<double*>(sm4);
     constexpr int R = kWave / LPR;
     constexpr int T = WAVES * kWave;
-    constexpr int U = CPL <= 16 ? 2 : 1;  // row steps in flight
+    constexpr int U = CPL <= 4 ? 8 : CPL <= 16 ? 5 : 1;  // row steps at a time (their sums' chains overlap)
     static_assert(WAVES >= 4 && WAVES <= 8, "at least one wave per publishing column block, wres and ored sized for 8");
     int J = A.J, Jp = A.Jp, ncl = A.ncl;
     const int rpw = A.rpw;
@@ -272,7 +274,8 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     const int nb = (int)gridDim.x, blk = (int)blockIdx.x;
     const int64_t r0 = (int64_t)blk * rpw;
     const int nrows = (int)max((int64_t)0, min((int64_t)rpw, A.I - r0));
-    const int Jr2 = (J + 1) & ~1, Jr4 = (J + 3) & ~3;
+    constexpr int WD = CPL * LPR;  // width of x and of the fold buffer
+    const int Jr2 = (J + 1) & ~1;
     const int slack = GM ? 0 : (CPL - ncl) * LPR;  // (a multiple of 32 floats: what follows stays 8-byte aligned)
     float* tile = GM ? A.tile + r0 * Jp : reinterpret_cast<float*>(sm);
     double* gl = GM ? sm : reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);  // G_j of the reference
@@ -285,13 +288,13 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block)
     double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the reference (delta sums)
     float* xl = reinterpret_cast<float*>(cl + (size_t)kColBlock * nown);  // v_j, or v_j - 1 for delta sums, in FP32
-    float* red = xl + Jr4;
+    float* red = xl + WD;
     __shared__ Ctl cs;  // decision workgroup: the control block for the whole launch
     __shared__ double e2tab[64];
     __shared__ double wres[WAVES];
     __shared__ double ored[WAVES][kColBlock];  // per-wave column sums of an owned block
     __shared__ uint32_t s_dec;
-    __shared__ int s_flag[2];  // by iteration parity: 1 a wait gave up, 2 not finite, 4 out of range (plain), 8 (delta)
+    __shared__ int s_flag[2];  // by iteration parity: 1 a wait gave up, 2 v not finite, 4 v out of the reference's range
 
     const XchLayout X = persist_xch_layout(nb, J);
     double* part = A.xch + X.part;
@@ -327,7 +330,9 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     // column of cell q of this lane: as the references are taken, and as the
     // iterations read the tile
     auto col_ref = [&](int q) { return q * LPR + sub; };
-    auto col_it = [&](int q) { return GM ? ((q / 4) * LPR + sub) * 4 + q % 4 : q * LPR + sub; };
+    constexpr int NV = CPL / 4;  // 16-byte loads of a lane and row step
+    auto col_it = [&](int q) { return q < 4 * NV ? ((q / 4) * LPR + sub) * 4 + q % 4 : q * LPR + sub; };
+    for (int j = tid; j < WD; j += T) xl[j] = 0.0f;
     if (tid < 2) s_flag[tid] = 0;
     // the decision workgroup (the last one: with fewer column blocks than
     // workgroups it owns none) sums the residuals and takes the stop decision
@@ -443,12 +448,8 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         constexpr bool D = decltype(delta)::value;
         float x[CPL];
 #pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            const int j = col_it(q);
-            x[q] = j < J ? xl[j] : 0.0f;
-        }
+        for (int q = 0; q < CPL; ++q) x[q] = xl[col_it(q)];  // (0 past J)
         res = 0.0;
-        // the row's sum, its column partials and its residual term, from its cells
         auto row_sum = [&](const float (&ev)[CPL]) {
             float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
@@ -458,35 +459,49 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
             return s0 + s1;
         };
-        auto finish = [&](int st, const float (&ev)[CPL], float s) {
-            const int lr = (st * WAVES + w) * R + rg;
-            const bool vrow = lr < nrows;
-            const double d = group_sum<LPR>((double)s);
-            const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
-            const double S = D ? Rr + d : d;
-            float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
-            if constexpr (D) wq *= -(float)d * __builtin_amdgcn_rcpf((float)Rr);
-            if (!vrow) wq = 0.0f;
+        // the cells of one row step of this lane: 16 bytes at a time, then word by word
+        auto load_row = [&](const float* trow, float (&ev)[CPL], bool whole) {
 #pragma unroll
-            for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[q], wq, acc[q]);
-            if (sub == 0 && vrow) {
+            for (int c = 0; c < NV; ++c) {
+                float4 y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (whole || (c * LPR + sub) * 4 < Jp) y = *reinterpret_cast<const float4*>(trow + (c * LPR + sub) * 4);
+                ev[4 * c] = y.x; ev[4 * c + 1] = y.y; ev[4 * c + 2] = y.z; ev[4 * c + 3] = y.w;
+            }
+#pragma unroll
+            for (int q = 4 * NV; q < CPL; ++q) ev[q] = trow[q * LPR + sub];
+        };
+        // N row steps at once, without a branch, so that the chains of their
+        // sums overlap: row sums, column partials and residual terms (rows past
+        // the range have a_i = 0 and a sum of 1)
+        auto finish = [&](int st, const auto& ev) {
+            constexpr int N = std::extent<std::remove_reference_t<decltype(ev)>>::value;
+            double d[N], Sn[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) d[u] = (double)row_sum(ev[u]);
+            group_sums<LPR>(d);
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int lr = ((st + u) * WAVES + w) * R + rg;
+                const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
+                const double S = D ? Rr + d[u] : (lr < nrows ? d[u] : 1.0);
+                float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+                if constexpr (D) wq *= -(float)d[u] * __builtin_amdgcn_rcpf((float)Rr);
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[u][q], wq, acc[q]);
                 res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
-                Sl[lr] = S;
+                Sn[u] = S;
+            }
+            if (sub == 0) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) Sl[((st + u) * WAVES + w) * R + rg] = Sn[u];
             }
         };
         if constexpr (GM) {
-            constexpr int NV = CPL / 4;              // 16-byte loads per lane and step
-            constexpr int PD = 4;                    // steps in flight
-            float ev[PD][CPL];
+            constexpr int PD = 4;  // steps in flight
+            float ev[PD][1][CPL];
             auto fetch = [&](int p, int st) {
                 const int lr = (st * WAVES + w) * R + rg;
-                const float* trow = tile + (size_t)(lr < nrows ? lr : 0) * Jp + 4 * sub;
-#pragma unroll
-                for (int c = 0; c < NV; ++c) {
-                    float4 y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if ((c * LPR + sub) * 4 < Jp) y = *reinterpret_cast<const float4*>(trow + c * LPR * 4);
-                    ev[p][4 * c] = y.x; ev[p][4 * c + 1] = y.y; ev[p][4 * c + 2] = y.z; ev[p][4 * c + 3] = y.w;
-                }
+                load_row(tile + (size_t)(lr < nrows ? lr : 0) * Jp, ev[p][0], false);
             };
 #pragma unroll
             for (int p = 0; p < PD; ++p) fetch(p, p);  // (steps past the last read row 0 of the block)
@@ -494,8 +509,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
 #pragma unroll
                 for (int p = 0; p < PD; ++p) {
                     if (st + p < steps) {  // uniform
-                        const float s = row_sum(ev[p]);
-                        finish(st + p, ev[p], s);
+                        finish(st + p, ev[p]);
                         if (st + p + PD < steps) fetch(p, st + p + PD);
                     }
                 }
@@ -503,23 +517,20 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         } else {
             auto step = [&](int st, auto nu) {
                 constexpr int N = decltype(nu)::value;
-                float ev[N][CPL], s[N];
+                float ev[N][CPL];
 #pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const float* trow = tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp + sub;
-#pragma unroll
-                    for (int q = 0; q < CPL; ++q) ev[u][q] = trow[q * LPR];
-                }
-#pragma unroll
-                for (int u = 0; u < N; ++u) s[u] = row_sum(ev[u]);
-#pragma unroll
-                for (int u = 0; u < N; ++u) finish(st + u, ev[u], s[u]);
+                for (int u = 0; u < N; ++u)
+                    load_row(tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp, ev[u], true);
+                finish(st, ev);
             };
             int st = 0;
             for (; st + U <= steps; st += U) step(st, std::integral_constant<int, U>{});
+            if constexpr (U > 2)
+                for (; st + 2 <= steps; st += 2) step(st, std::integral_constant<int, 2>{});
             if constexpr (U > 1)
                 for (; st < steps; ++st) step(st, std::integral_constant<int, 1>{});
         }
+        if (sub != 0) res = 0.0;  // (every lane of a row holds its term)
     };
 
     // The workgroup's column partials: the row groups of a wave (lanes
@@ -544,10 +555,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             if (w0 > 0) __syncthreads();  // the previous round's sums are taken
             if (w >= w0 && w < w0 + NW && rg == 0) {
 #pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    const int j = col(q);
-                    if (j < J) rb[(w - w0) * Jr4 + j] = ac[q];
-                }
+                for (int q = 0; q < CPL; ++q) rb[(w - w0) * WD + col(q)] = ac[q];
             }
             __syncthreads();
 #pragma unroll
@@ -555,7 +563,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 const int c = u * T + tid;
                 if (c < J) {
 #pragma unroll
-                    for (int q = 0; q < NW; ++q) t[u] += (double)rb[q * Jr4 + c];
+                    for (int q = 0; q < NW; ++q) t[u] += (double)rb[q * WD + c];
                 }
             }
         }
@@ -585,8 +593,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             vl[j] = v;
             xl[j] = (float)(fine ? v - 1.0 : v);
             if (!(v > 0.0) || !isfinite(v)) flag |= 2;
-            if (!(v >= 1.0 / kScaleMax && v <= kScaleMax)) flag |= 4;
-            if (!(fabs(v - 1.0) <= kDeltaMax)) flag |= 8;
+            if (fine ? !(fabs(v - 1.0) <= kDeltaMax) : !(v >= 1.0 / kScaleMax && v <= kScaleMax)) flag |= 4;
         };
         // column update v_j = b_j / sum_i E_ij a_i / S_i of owned column slot e
         auto col_v = [&](int e, double sum) {
@@ -687,7 +694,9 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             s = xor16_sum(s);      // pb .. pb + 7 of this wave): lane l ^ 8, l ^ 16, l ^ 32
             s = xor32_sum(s);
             if (lane < kColBlock) ored[w][lane] = s;
-            if (__syncthreads_or(fail)) { fail = true; break; }
+            if (fail && lane == 0) atomicOr(&s_flag[P], 1);
+            __syncthreads();
+            if (s_flag[P] & 1) { fail = true; break; }
             if (tid < kColBlock * kReplicas) {
                 const int cc = tid & (kColBlock - 1), r = tid >> 3;
                 const int jj = o * kColBlock + cc;
@@ -732,8 +741,10 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             s_dec = (uint32_t)(d & 3);
         }
         if (fail) flag |= 1;
-        for (int bit = 1; bit <= 8; bit <<= 1)
-            if (__any(flag & bit) && lane == 0) atomicOr(&s_flag[P], bit);
+        if (__any(flag)) {  // (rare; one LDS atomic per wave, not one per lane)
+            const int f = (__any(flag & 1) ? 1 : 0) | (__any(flag & 2) ? 2 : 0) | (__any(flag & 4) ? 4 : 0);
+            if (lane == 0) atomicOr(&s_flag[P], f);
+        }
         __syncthreads();
         const int fl = s_flag[P];
         const uint32_t code = s_dec;
@@ -751,7 +762,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
             break;
         }
-        if (fine) kind = ((code & kDecRefDelta) || (fl & 8)) ? kItRefDelta : kItDelta;
+        if (fine) kind = ((code & kDecRefDelta) || (fl & 4)) ? kItRefDelta : kItDelta;
         else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
