@@ -78,6 +78,7 @@ struct ot_assoc {
     float* ker = nullptr;   // stored kernel of the streamed cooperative phase (likewise)
     size_t ker_bytes = 0;
     bool mat_held = false;     // the retained cost is in `mat` (else regenerated from the positions)
+    bool validate_pending = false;  // the retained matrix's values are still to be checked by this solve
     bool reuse_cost = false;   // the next solve takes the retained cost as it is (Alg. 2's solves after the first)
     bool stage_in_ws = false;  // the stage is the tail of a caller's workspace (never freed or grown)
     void* ws = nullptr;        // the single device block all fixed buffers are carved from

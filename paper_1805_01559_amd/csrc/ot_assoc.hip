@@ -325,6 +325,32 @@ bool ensure_ker(ot_assoc* h, size_t bytes) {
     return ensure_room(h, (void**)&h->ker, &h->ker_bytes, bytes, skip);
 }
 
+// The value check of a matrix (launched): non-finite costs, rates that are not
+// finite and positive.
+void launch_validate(ot_assoc* h, const ot_cost_desc* c, const void* data, int* bad, int bit, Ctl* ctl) {
+    const int64_t I = c->I, ld = ld_of(*c);
+    const int J = (int)c->J;
+    const int grid = (int)std::min<int64_t>(4096, (I * J + 255) / 256);
+    auto go = [&](auto kern, auto* x) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, h->stream, x, I, J, ld, bad, bit, ctl); };
+    if (c->dtype == OT_F32) {
+        if (c->kind == OT_COST_DENSE) go(k_validate<float, false>, (const float*)data);
+        else go(k_validate<float, true>, (const float*)data);
+    } else {
+        if (c->kind == OT_COST_DENSE) go(k_validate<double, false>, (const double*)data);
+        else go(k_validate<double, true>, (const double*)data);
+    }
+}
+
+// The deferred value check of the retained matrix, for a solve whose first
+// pass does not make it; a rejected one ends the solve on the device.
+ot_status validate_matrix(ot_assoc* h) {
+    if (!h->validate_pending) return OT_OK;
+    h->validate_pending = false;
+    launch_validate(h, &h->last, h->cost_dev, &h->ctl->input_bad, 8, h->ctl);
+    HIPCHK(h, hipGetLastError());
+    return OT_OK;
+}
+
 // Brings the cost of `c` onto the device: host matrices are staged, device
 // matrices are referenced, positions are copied (and, for the geometry cost,
 // its per-device set-up pass runs). Afterwards the handle can rebuild the source without the caller.
@@ -343,7 +369,7 @@ ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check, bool keep =
     const int bit = now ? 1 : 8;
     Ctl* ectl = now ? nullptr : h->ctl;
     const int64_t I = c->I, J = c->J, ld = ld_of(*c), n = I * J;
-    h->retained = h->mat_held = false;
+    h->retained = h->mat_held = h->validate_pending = false;
     h->last = *c;
     if (c->kind != OT_COST_GEOMETRY && c->kind != OT_COST_EUCLID) {
         const size_t esz = c->dtype == OT_F32 ? 4 : 8;
@@ -356,22 +382,13 @@ ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check, bool keep =
             HIPCHK(h, hipMemcpyAsync(h->stage, data, bytes, hipMemcpyHostToDevice, h->stream));
             data = h->stage;
         }
-        if (validate_values) {
-            if (now) HIPCHK(h, hipMemsetAsync(h->bad, 0, sizeof(int), h->stream));
-            const int grid = (int)std::min<int64_t>(4096, (n + 255) / 256);
-            const int Ji = (int)J;
-            if (c->dtype == OT_F32) {
-                if (c->kind == OT_COST_DENSE) hipLaunchKernelGGL((k_validate<float, false>), dim3(grid), dim3(256), 0, h->stream, (const float*)data, I, Ji, ld, bad, bit, ectl);
-                else hipLaunchKernelGGL((k_validate<float, true>), dim3(grid), dim3(256), 0, h->stream, (const float*)data, I, Ji, ld, bad, bit, ectl);
-            } else {
-                if (c->kind == OT_COST_DENSE) hipLaunchKernelGGL((k_validate<double, false>), dim3(grid), dim3(256), 0, h->stream, (const double*)data, I, Ji, ld, bad, bit, ectl);
-                else hipLaunchKernelGGL((k_validate<double, true>), dim3(grid), dim3(256), 0, h->stream, (const double*)data, I, Ji, ld, bad, bit, ectl);
-            }
+        h->validate_pending = validate_values && !now;  // (by the solve's first pass, or validate_matrix)
+        if (now) {
+            HIPCHK(h, hipMemsetAsync(h->bad, 0, sizeof(int), h->stream));
+            launch_validate(h, c, data, h->bad, 1, nullptr);
             int hbad = 0;
-            if (now) {
-                HIPCHK(h, hipMemcpyAsync(&hbad, h->bad, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-                HIPCHK(h, hipStreamSynchronize(h->stream));
-            }
+            HIPCHK(h, hipMemcpyAsync(&hbad, h->bad, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+            HIPCHK(h, hipStreamSynchronize(h->stream));
             if (hbad)
                 return fail(h, OT_EINVAL, c->kind == OT_COST_DENSE ? "cost matrix has non-finite entries"
                                                                   : "rate matrix has entries that are not finite and positive");
@@ -637,6 +654,8 @@ struct Solver {
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 
+constexpr int64_t kSoloSteps = 8;
+
 struct PersistPlan {
     int lpr = 0, cpl = 0, ncl = 0, rpw = 0, nb = 0, Jp = 0, waves = 8;
     size_t lds = 0;
@@ -660,9 +679,15 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     p.waves = persist_waves(J);
     const int slots = p.waves * (64 / p.lpr);  // rows per wave step of the workgroup
     const int64_t per = (int64_t)h->num_cu * slots;
-    const int64_t steps = (I + per - 1) / per;
+    int64_t steps = (I + per - 1) / per;
     p.ncl = (J + p.lpr - 1) / p.lpr;
     p.Jp = p.ncl * p.lpr;
+    // one workgroup where it has at most kSoloSteps row steps: a step costs about
+    // 0.1 us per iteration, the two hops of the exchange that it saves 2 us
+    const int64_t solo = (I + slots - 1) / slots;
+    if (solo <= kSoloSteps && persist_lds_bytes((int)(solo * slots), J, p.Jp, p.waves, p.cpl * p.lpr,
+                                                (p.cpl - p.ncl) * p.lpr, 1) + 2048 <= (size_t)h->lds_max)
+        steps = solo;
     p.rpw = (int)(steps * slots);
     p.nb = (int)((I + p.rpw - 1) / p.rpw);
     p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, p.cpl * p.lpr, (p.cpl - p.ncl) * p.lpr, p.nb);
@@ -721,6 +746,13 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.ctl = h->ctl;
     A.prm = h->prm;
     A.tile = h->ker;
+    A.validate = h->validate_pending ? 1 : 0;
+    // (Alg. 2's solves sum the loads; their plans are not asked for)
+    A.loads = h->want_loads && J <= kFusedLoadsJ ? h->loads : nullptr;
+    A.plan_out = (A.loads || I * J > h->plan_cap) ? nullptr : h->plan_out;
+    A.plan_f64 = h->plan_dtype == OT_F64 ? 1 : 0;
+    h->loads_fresh = A.loads != nullptr;
+    h->plan_fresh = A.plan_out != nullptr;
     // (the solve's init launch has zeroed the exchange block, unless it
     // could not know that this launch would follow)
     if (!h->xch_zeroed) {
@@ -732,8 +764,10 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     Src sv = src;
     void* args[] = {(void*)&A, (void*)&sv};
     if (h->ev_coop[0]) HIPCHK(h, hipEventRecord(h->ev_coop[0], h->stream));
-    const hipError_t e = hipLaunchCooperativeKernel(kern, dim3((unsigned)p.nb), dim3(p.waves * 64), args,
-                                                    (unsigned)p.lds, h->stream);
+    // (a single workgroup waits for no other)
+    const hipError_t e = p.nb == 1 ? hipLaunchKernel(kern, dim3(1), dim3(p.waves * 64), args, p.lds, h->stream)
+                                   : hipLaunchCooperativeKernel(kern, dim3((unsigned)p.nb), dim3(p.waves * 64), args,
+                                                                (unsigned)p.lds, h->stream);
     if (e == hipErrorCooperativeLaunchTooLarge) {
         (void)hipGetLastError();
         return OT_OK;
@@ -773,17 +807,9 @@ static __global__ void k_log_a(const double* a, int64_t I, double* la) {
         la[i] = log(a[i]);
 }
 
-// Moves iterate (f, g) between buffer pairs in one launch.
-static __global__ void k_copy_fg(double* fd, const double* fs, int64_t I, double* gd, const double* gs, int J) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < I; i += (int64_t)gridDim.x * blockDim.x)
-        fd[i] = fs[i];
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < J; j += gridDim.x * blockDim.x) gd[j] = gs[j];
-}
-
 // The three phases of a solve. `c` enters with the initial control state and
 // leaves with the final one; result_iter names the returned iterate and
-// result_par the parity of the buffers that hold it (the iteration's parity,
-// except after the cooperative path's check: see there).
+// result_par the parity of the buffers that hold it.
 template <class Src>
 ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, int J, double tol, int32_t max_iter,
                      Ctl& c, int& result_iter, int& result_par) {
@@ -800,26 +826,18 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     bool checked = false;
     PersistPlan pp;
     bool persisted = false;
-    int coop_par = -1;  // buffers of the iterate the cooperative path checked
     if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && (Src::kTag != 2 || h->mat_held) &&
         persist_plan<Src>(h, I, J, pp))
         if ((st = run_persist<Src>(h, src, I, J, pp, stall_below, persisted))) return st;
     h->last_persistent = persisted && !pp.gm;
-    if (persisted) {
-        // polish decided on the device, then the check: one host wait
-        const int np = std::max(0, h->opt.polish_iters);
-        const unsigned gb = (unsigned)std::min<int64_t>(64, (std::max<int64_t>(I, J) + 255) / 256);
-        hipLaunchKernelGGL(k_polish_gate, dim3(gb), dim3(256), 0, h->stream, h->ctl, h->f[0], h->f[1], h->g[0],
-                           h->g[1], I, J, tol, stall_below, np);
-        if (np > 0 && (st = S.issue_chunk<Src, true>(src, 0, np, kModePolish, 0.0))) return st;
-        // the iterate sits in the buffers of parity np & 1 whatever its
-        // iteration number (the gate put it there): it is checked and
-        // returned from there, and moved to the buffers of its iteration's
-        // parity only if more sweeps follow
-        if ((st = S.run_check(src, np, c))) return st;
-        coop_par = np & 1;
+    if (persisted) {  // the launch has checked its iterate (one host wait)
+        h->validate_pending = false;
+        if ((st = S.snapshot(0)) || (st = S.wait(0))) return st;
+        c = h->ctl_h[0];
         checked = true;
-        h->last_fast_iters = c.iter - c.fp64_iters;  // (the solve starts at iteration 0)
+        h->last_fast_iters = c.iter;  // (the solve starts at iteration 0)
+    } else if ((st = validate_matrix(h))) {
+        return st;
     } else if (h->opt.precision == OT_PREC_FP32) {
         hipLaunchKernelGGL(k_log_a, dim3((unsigned)std::min<int64_t>(1024, (I + 255) / 256)), dim3(256), 0, h->stream,
                            (const double*)h->a, I, h->la);
@@ -839,7 +857,7 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     }
     if (c.done) {  // inputs rejected, or a numeric failure in the fast phase
         result_iter = c.result_iter;
-        result_par = coop_par >= 0 ? coop_par : result_iter & 1;
+        result_par = result_iter & 1;
         h->loads_fresh = h->plan_fresh = false;
         return OT_OK;
     }
@@ -851,12 +869,8 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
         return OT_OK;
     }
     result_iter = c.iter;
-    result_par = coop_par >= 0 ? coop_par : result_iter & 1;
+    result_par = result_iter & 1;
     if (!(c.chk_violation < tol) && c.iter < max_iter) {
-        if (coop_par >= 0 && ((c.iter ^ coop_par) & 1))  // (the FP64 sweeps start from parity c.iter & 1)
-            hipLaunchKernelGGL(k_copy_fg, dim3((unsigned)std::min<int64_t>(256, (I + 255) / 256)), dim3(256), 0,
-                               h->stream, h->f[c.iter & 1], (const double*)h->f[coop_par], I, h->g[c.iter & 1],
-                               (const double*)h->g[coop_par], J);
         if ((st = S.run_phase<Src, true>(src, kModeExact, chunk, 0.0, c))) return st;
         const int k = c.done ? c.result_iter : c.iter;
         const Ctl loop = c;

@@ -94,9 +94,11 @@ constexpr int kMaxCoopGroups = 256; // workgroups of a cooperative launch (an ow
 //                          between replicas)
 //   dec   [2][kReplicas][8]   (iteration << 2) | stop, as uint64, one line per replica
 //   abort [8]              uint64, nonzero once a poll gave up
+//   fin   [7 x kMaxCoopGroups]  scalars of the final check: five per workgroup,
+//                          two per column block, tagged 1 once written
 struct XchLayout {
     int Jp, Gs;
-    size_t part, rpart, gx, dec, abort_, total;
+    size_t part, rpart, gx, dec, abort_, fin, total;
 };
 __host__ __device__ inline XchLayout persist_xch_layout(int nb, int J) {
     XchLayout L;
@@ -107,7 +109,8 @@ __host__ __device__ inline XchLayout persist_xch_layout(int nb, int J) {
     L.gx = L.rpart + ((size_t)2 * nb + 7) / 8 * 8;
     L.dec = L.gx + (size_t)2 * kReplicas * L.Gs;
     L.abort_ = L.dec + (size_t)2 * kReplicas * 8;
-    L.total = L.abort_ + 8;
+    L.fin = L.abort_ + 8;
+    L.total = L.fin + 7 * kMaxCoopGroups;
     return L;
 }
 __host__ __device__ inline size_t persist_exchange_doubles(int nb, int J) { return persist_xch_layout(nb, J).total; }
@@ -163,6 +166,10 @@ struct PersistArgs {
     Ctl* ctl;
     const SolveParams* prm;
     float* tile;   // the stored kernel in device memory, I x Jp (streamed form only)
+    int validate;  // the first reference also checks the matrix (OT_EINVAL on a bad entry)
+    void* plan_out;  // I x J plan the final check writes, or null
+    int plan_f64;
+    double* loads;   // J: RRH loads the final check sums, or null
 };
 
 // Column blocks each workgroup owns at most (workgroup w owns w, w + nb, ...).
@@ -292,6 +299,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     __shared__ Ctl cs;  // decision workgroup: the control block for the whole launch
     __shared__ double e2tab[64];
     __shared__ double wres[WAVES];
+    __shared__ double wst[WAVES][7];  // the final check's scalars
     __shared__ double ored[WAVES][kColBlock];  // per-wave column sums of an owned block
     __shared__ uint32_t s_dec;
     __shared__ int s_flag[2];  // by iteration parity: 1 a wait gave up, 2 v not finite, 4 v out of the reference's range
@@ -342,6 +350,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     int k_ref = 0;
 
     const int steps = rpw / (WAVES * R);
+    [[maybe_unused]] volatile int bad_before = 0;
     double res = 0.0;  // this lane's part of the row residual of the previous iterate
     int k = k0;
 
@@ -374,6 +383,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 if (q < ncl) to[q] = src.template load<1>(row, q * LPR + sub, J);
         };
         if constexpr (kAhead) fetch(0, nraw);
+        [[maybe_unused]] bool bad_cost = false;
         for (int st = 0; st < steps; ++st) {
             const int lr = (st * WAVES + w) * R + rg;
             const bool vrow = lr < nrows;
@@ -384,7 +394,12 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             auto arg = [&](int q, const typename Src::template Raw<1>& raw) {
                 t[q] = -pinf64();
                 const int j = q * LPR + sub;
-                if (q < ncl && j < J && vrow) t[q] = (gl[j] - src.template cost<true, 1>(row, raw, 0, i, j, stage)) * kk;
+                if (q < ncl && j < J && vrow) {
+                    const double c = src.template cost<true, 1>(row, raw, 0, i, j, stage);
+                    if constexpr (Src::kTag <= 2) bad_cost |= !isfinite(c);
+                    else if constexpr (Src::kTag <= 4) bad_cost |= !(c > 0.0 && isfinite(c));  // (R > 0 and finite)
+                    t[q] = (gl[j] - c) * kk;
+                }
                 mx = fmaxf(mx, (float)t[q]);
             };
             if constexpr (kAhead) {
@@ -431,6 +446,10 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 Sl[lr] = S;
             }
         }
+        // (the verdict is final once the value comes back, before this workgroup
+        // publishes anything)
+        if (A.validate && k == k0 + 1 && __any(bad_cost) && lane == 0)
+            bad_before = __hip_atomic_fetch_or(&ctl->input_bad, 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();  // (the fold also reuses the staged source data's LDS)
         // |rowsum_i - a_i| of the previous iterate, from the change of the log-sum-exp
         res = 0.0;
@@ -574,9 +593,61 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         }
     };
 
+    // The partials of column block o tagged kt from every workgroup, summed in
+    // a fixed order: thread t takes column t % 8 of producers t / 8 + (T / 8) u
+    // (whole lines per wave). Leaves the waves' sums in ored, behind a barrier;
+    // false (in every thread) if a wait gave up.
+    auto collect = [&](int o, int kt) -> bool {
+        constexpr int PB = T / kColBlock, NU = kMaxCoopGroups / PB;  // producers per round, rounds
+        const double* pk = part + (size_t)(kt & 1) * nb * X.Jp;
+        const int c = tid & (kColBlock - 1), pb = tid / kColBlock;
+        const int j = o * kColBlock + c;
+        const bool cv = j < J;
+        double x[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int pr = pb + PB * u;
+            x[u] = (cv && pr < nb) ? get_agent(pk + (size_t)pr * X.Jp + j) : tag_value(0.0, kt);
+        }
+        bool fail = false;
+        int spin = 0;
+        for (;;) {
+            bool pend = false;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) pend |= !has_tag(x[u], kt);
+            if (!__any(pend)) break;
+            if ((++spin & 31) == 0 && (get_agent(abort_word) != 0 || spin > A.max_spin)) {
+                put_agent(abort_word, (uint64_t)1);
+                fail = true;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+                if (!has_tag(x[u], kt)) x[u] = get_agent(pk + (size_t)(pb + PB * u) * X.Jp + j);
+        }
+        // (tag bits of the partials stay in the sum: a relative change below 2^-50)
+        double s = x[0];
+#pragma unroll
+        for (int u = 1; u < NU; ++u) s += x[u];
+        s += dpp_d<0x128>(s);  // lanes of one wave with the same column (producers
+        s = xor16_sum(s);      // pb .. pb + 7 of this wave): lane l ^ 8, l ^ 16, l ^ 32
+        s = xor32_sum(s);
+        if (lane < kColBlock) ored[w][lane] = s;
+        if (fail && lane == 0) atomicOr(&s_flag[kt & 1], 1);
+        __syncthreads();
+        return !(s_flag[kt & 1] & 1);
+    };
+    auto collected = [&](int cc) {
+        double csum = 0.0;
+#pragma unroll
+        for (int q = 0; q < WAVES; ++q) csum += ored[q][cc];
+        return csum;
+    };
+
     __syncthreads();
     int kind = kItRef;
-    bool ok = true;
+    bool ok = true, bad = false;
     for (;;) {
         ++k;
         const int P = k & 1;
@@ -655,55 +726,16 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             }
         }
 
-        // ---- 2. column update of the owned blocks of kColBlock columns: thread
-        //      t takes column t % 8 of producers t / 8 + (T / 8) u (whole lines
-        //      per wave), sums them in a fixed order, publishes v in every replica
+        // ---- 2. column update of the owned blocks of kColBlock columns, v
+        //      published in every replica
         for (int o = blk, oi = 0; nb > 1 && o * kColBlock < J; o += nb, ++oi) {
-            constexpr int PB = T / kColBlock, NU = kMaxCoopGroups / PB;  // producers per round, rounds
             if (oi > 0) __syncthreads();  // ored still holds the previous block
-            const int c = tid & (kColBlock - 1), pb = tid / kColBlock;
-            const int j = o * kColBlock + c;
-            const bool cv = j < J;
-            double x[NU];
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int pr = pb + PB * u;
-                x[u] = (cv && pr < nb) ? get_agent(part + ((size_t)P * nb + pr) * X.Jp + j) : tag_value(0.0, k);
-            }
-            int spin = 0;
-            for (;;) {
-                bool pend = false;
-#pragma unroll
-                for (int u = 0; u < NU; ++u) pend |= !has_tag(x[u], k);
-                if (!__any(pend)) break;
-                if ((++spin & 31) == 0 && (get_agent(abort_word) != 0 || spin > A.max_spin)) {
-                    put_agent(abort_word, (uint64_t)1);
-                    fail = true;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    if (!has_tag(x[u], k)) x[u] = get_agent(part + ((size_t)P * nb + pb + PB * u) * X.Jp + j);
-            }
-            // (tag bits of the partials stay in the sum: a relative change below 2^-50)
-            double s = x[0];
-#pragma unroll
-            for (int u = 1; u < NU; ++u) s += x[u];
-            s += dpp_d<0x128>(s);  // lanes of one wave with the same column (producers
-            s = xor16_sum(s);      // pb .. pb + 7 of this wave): lane l ^ 8, l ^ 16, l ^ 32
-            s = xor32_sum(s);
-            if (lane < kColBlock) ored[w][lane] = s;
-            if (fail && lane == 0) atomicOr(&s_flag[P], 1);
-            __syncthreads();
-            if (s_flag[P] & 1) { fail = true; break; }
+            if (!collect(o, k)) { fail = true; break; }
             if (tid < kColBlock * kReplicas) {
                 const int cc = tid & (kColBlock - 1), r = tid >> 3;
                 const int jj = o * kColBlock + cc;
                 if (jj < J && !hold) {
-                    double csum = 0.0;
-#pragma unroll
-                    for (int q = 0; q < WAVES; ++q) csum += ored[q][cc];
+                    const double csum = collected(cc);
                     const int e = oi * kColBlock + cc;
                     put_agent(gx + ((size_t)P * kReplicas + r) * X.Gs + jj, tag_value(col_v(e, csum), k));
                     if (kind == kItRefDelta && r == 0) cl[e] = csum;
@@ -754,35 +786,212 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         if (fl & 1) { ok = false; break; }
         has_prev = 1;
         if ((code & kDecStop) || (fl & 2)) {
-            if ((fl & 2) && blk == dblk && tid == 0) {
-                cs.numeric_bad = 1;
-                cs.done = 1;
-                cs.stop = 1;
-                cs.result_iter = cs.iter;
-            }
+            bad = (fl & 2) != 0;
             break;
         }
         if (fine) kind = ((code & kDecRefDelta) || (fl & 4)) ? kItRefDelta : kItDelta;
         else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
-    // the final iterate k: f of the rows, g (workgroup 0) and the control block
-    if (ok) {
+    if (ok && !bad) {
+        // ---- the returned iterate k: f of the rows, g (workgroup 0), and its exact
+        //      check: FP64 sums over pi_ij = exp((f_i + g_j - C_ij) / eps) from the cost
+        //      (read or regenerated once more), the plan and the RRH loads
+        //      sum_i C_ij pi_ij where they are asked for. In this launch it costs
+        //      one pass and two hops of the exchange; as launches of its own it
+        //      took five more (polish, combine, check, two folds).
+        asm volatile("" : "+v"(tid), "+v"(lane), "+v"(sub), "+v"(rg), "+s"(J), "+s"(Jp), "+s"(ncl));
+        double* stage = reinterpret_cast<double*>(red);
+        src.stage(stage, J);
         double* fo = A.f[k & 1];
-        for (int lr = tid; lr < nrows; lr += T)
-            fo[r0 + lr] = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
-        if (blk == 0) {
-            double* go = A.g[k & 1];
-            for (int j = tid; j < J; j += T) go[j] = gl[j] + eps * log(vl[j]);
+        for (int lr = tid; lr < nrows; lr += T) {
+            const double fi = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
+            ml[lr] = fi;
+            fo[r0 + lr] = fi;
+        }
+        double* go = A.g[k & 1];
+        for (int j = tid; j < J; j += T) {
+            gl[j] += eps * log(vl[j]);
+            if (blk == 0) go[j] = gl[j];
+        }
+        __syncthreads();
+        const bool with_loads = A.loads != nullptr;
+        double ac[CPL], acl[CPL];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) ac[q] = acl[q] = 0.0;
+        double rowres = 0.0, cost = 0.0, ent = 0.0, mass = 0.0, fa = 0.0;
+        for (int st = 0; st < steps; ++st) {
+            const int lr = (st * WAVES + w) * R + rg;
+            const bool vrow = lr < nrows;
+            const int64_t i = r0 + (vrow ? lr : 0);
+            auto row = src.row(i);
+            const double fk = vrow ? ml[lr] * kk : 0.0;
+            double rs = 0.0;
+            constexpr int G = CPL <= 16 ? CPL : 8;  // cells loaded at a time
+#pragma unroll
+            for (int q0 = 0; q0 < CPL; q0 += G) {
+                typename Src::template Raw<1> raw[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    if (q0 + u < CPL && q0 + u < ncl) raw[u] = src.template load<1>(row, (q0 + u) * LPR + sub, J);
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    const int q = q0 + u;
+                    const int j = q * LPR + sub;
+                    if (q < CPL && q < ncl && j < J && vrow) {
+                        const double c = src.template cost<true, 1>(row, raw[u], 0, i, j, stage);
+                        const double t = fk + fma(c, -kk, gl[j] * kk);  // log2 pi_ij (rounded as in the plan kernel)
+                        const double p = exp2_tab(fmax(t, -2000.0), e2tab);
+                        rs += p;
+                        if (p > 0.0) {  // (an infinite cost has no mass and adds nothing)
+                            cost = fma(c, p, cost);
+                            ent = fma(p, t * kLn2 - 1.0, ent);
+                            if (with_loads) acl[q] = fma(c, p, acl[q]);
+                        }
+                        ac[q] += p;
+                        if (A.plan_out) {
+                            if (A.plan_f64) reinterpret_cast<double*>(A.plan_out)[i * J + j] = p;
+                            else reinterpret_cast<float*>(A.plan_out)[i * J + j] = (float)p;
+                        }
+                    }
+                }
+                if constexpr (CPL > 16) __builtin_amdgcn_sched_barrier(0);
+            }
+            rs = group_sum<LPR>(rs);
+            if (sub == 0 && vrow) {
+                rowres += fabs(rs - al[lr]);
+                mass += rs;
+                fa += ml[lr] * al[lr];
+            }
+        }
+        {
+            const double v[5] = {wave_sum(rowres), wave_sum(cost), wave_sum(ent), wave_sum(mass), wave_sum(fa)};
+            if (lane == 0)
+                for (int q = 0; q < 5; ++q) wst[w][q] = v[q];
+        }
+        __syncthreads();  // (the fold reuses the staged source data's LDS)
+        // partials tagged k + 1 (loads: k + 2; the last reader of either parity's
+        // slots was done with them before iteration k's v arrived), scalars
+        // and column owners' results
+        const int k1 = k + 1;
+        double* slots = A.xch + X.fin;
+        constexpr int kOwnSlots = 5 * kMaxCoopGroups;
+        auto publish = [&](double (&v)[CPL], int kt) {
+            double* prow = part + ((size_t)(kt & 1) * nb + blk) * X.Jp;
+            fold(v, col_ref, [&](int c, double t) { put_agent(prow + c, tag_value(t, kt)); });
+        };
+        publish(ac, k1);
+        if (tid < 5) {
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < WAVES; ++q) t += wst[q][tid];
+            put_agent(slots + blk * 5 + tid, tag_value(t, 1));
+        }
+        if (with_loads) {
+            __syncthreads();  // the fold buffer is still read
+            publish(acl, k1 + 1);
+        }
+        for (int o = blk, oi = 0; ok && o * kColBlock < J; o += nb, ++oi) {
+            __syncthreads();
+            ok = collect(o, k1);
+            if (!ok) break;
+            if (tid < kColBlock) {
+                const int jj = o * kColBlock + tid;
+                const int e = oi * kColBlock + tid;
+                double cres = 0.0, gb = 0.0;
+                if (jj < J) {
+                    cres = fabs(collected(tid) - bl[e]);
+                    gb = gl[jj] * bl[e];
+                }
+                cres += dpp_d<0xB1>(cres);  // the 8 columns of the block
+                cres += dpp_d<0x4E>(cres);
+                cres += dpp_d<0x141>(cres);
+                gb += dpp_d<0xB1>(gb);
+                gb += dpp_d<0x4E>(gb);
+                gb += dpp_d<0x141>(gb);
+                if (tid == 0) {
+                    put_agent(slots + kOwnSlots + 2 * o, tag_value(cres, 1));
+                    put_agent(slots + kOwnSlots + 2 * o + 1, tag_value(gb, 1));
+                }
+            }
+            if (with_loads) {
+                __syncthreads();
+                ok = collect(o, k1 + 1);
+                if (!ok) break;
+                if (tid < kColBlock && o * kColBlock + tid < J) A.loads[o * kColBlock + tid] = collected(tid);
+            }
+        }
+        if (blk == dblk && ok) {
+            const int nblk = (J + kColBlock - 1) / kColBlock;
+            double x[7];
+            auto at = [&](int u, bool& live) {
+                live = u < 5 ? tid < nb : tid < nblk;
+                return u < 5 ? slots + tid * 5 + u : slots + kOwnSlots + 2 * tid + (u - 5);
+            };
+            static_assert(T >= kMaxCoopGroups, "one thread per workgroup and per column block");
+#pragma unroll
+            for (int u = 0; u < 7; ++u) {
+                bool live;
+                const double* p = at(u, live);
+                x[u] = live ? get_agent(p) : tag_value(0.0, 1);
+            }
+            int spin = 0;
+            bool fail = false;
+            for (;;) {
+                bool pend = false;
+#pragma unroll
+                for (int u = 0; u < 7; ++u) pend |= !has_tag(x[u], 1);
+                if (!__any(pend)) break;
+                if ((++spin & 31) == 0 && (get_agent(abort_word) != 0 || spin > A.max_spin)) {
+                    put_agent(abort_word, (uint64_t)1);
+                    fail = true;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+                for (int u = 0; u < 7; ++u) {
+                    bool live;
+                    const double* p = at(u, live);
+                    if (!has_tag(x[u], 1)) x[u] = get_agent(p);
+                }
+            }
+            __syncthreads();  // wst and the flags are reused
+            if (fail && lane == 0) atomicOr(&s_flag[k1 & 1], 1);
+#pragma unroll
+            for (int u = 0; u < 7; ++u) {
+                const double t = wave_sum(x[u]);
+                if (lane == 0) wst[w][u] = t;
+            }
+            __syncthreads();
+            ok = !(s_flag[k1 & 1] & 1);
+            if (ok && tid == 0) {
+                double t[7];
+                for (int u = 0; u < 7; ++u) {
+                    t[u] = 0.0;
+                    for (int q = 0; q < WAVES; ++q) t[u] += wst[q][u];
+                }
+                cs.chk_row_res = t[0];
+                cs.chk_col_res = t[5];
+                cs.chk_violation = (t[0] + t[5]) / cs.mass;
+                cs.chk_objective = t[1];
+                cs.chk_reg_objective = t[1] + eps * t[2];
+                cs.chk_mass = t[3];
+                cs.chk_dual = t[4] + t[6] - eps * t[3];
+            }
         }
     }
     if (blk == dblk && tid == 0) {
-        if (!ok) {
-            cs.sync_fail = 1;
+        if (bad || !ok) {
+            cs.numeric_bad |= bad ? 1 : 0;
+            cs.sync_fail = ok ? 0 : 1;
             cs.done = 1;
             cs.stop = 1;
             cs.result_iter = cs.iter;
         }
+        // (every workgroup's verdict on its rows of the matrix preceded its
+        // first partials)
+        cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cs.input_bad) cs.done = cs.stop = 1;
         *ctl = cs;
     }
 }
@@ -800,31 +1009,6 @@ static __global__ void k_xch_clear(double* xch, int nb, int J, Ctl* ctl) {
     for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < X.total; q += stride)
         xch[q] = q < X.dec ? empty : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctl->stop = 0;
-}
-
-// Between the FP32 phase and the FP64 polish, decided on the device: the
-// polish runs unless the solve is done, at max_iter, or the FP32 residual
-// already met a tol above the FP32 noise threshold. The iterate is then
-// moved to the buffers the host-issued launches expect: parity 0 when the
-// polish runs (it starts from there), parity np & 1 when it is skipped (where
-// the polish would have left it), so that the check reads parity np & 1
-// either way.
-static __global__ void k_polish_gate(Ctl* ctl, double* f0, double* f1, double* g0, double* g1, int64_t I, int J,
-                                     double tol, double stall_below, int np) {
-    const int it = ctl->iter;
-    const bool met = ctl->r_last < ctl->tol_fast && tol >= stall_below;
-    const bool skip = ctl->done || np <= 0 || it >= ctl->max_iter || met;
-    const int want = skip ? (np & 1) : 0;
-    if ((it & 1) != want) {
-        const double* fs = (it & 1) ? f1 : f0;
-        const double* gs = (it & 1) ? g1 : g0;
-        double* fd = want ? f1 : f0;
-        double* gd = want ? g1 : g0;
-        const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-        for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < I; q += stride) fd[q] = fs[q];
-        for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < J; q += stride) gd[q] = gs[q];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->stop = skip ? 1 : 0;
 }
 
 // ------------------------------------------------------------ solve set-up --
