@@ -5,7 +5,10 @@
 // generations of work lists that the kernels of batch_kernels.h consume and
 // rebuild. A chunk of CHUNK iterations (three persistent launches each) is
 // captured once into a HIP graph and replayed for the life of the engine:
-// which instances and parts are live is data, not graph structure. The host
+// which instances and parts are live is data, not graph structure. Most
+// instances never get there: they are solved by teams of workgroups first
+// (team_kernels.h), and only what those leave (an iteration cap reached, a
+// check that missed tol, an instance too large for LDS) goes on in chunks. The host
 // admits new instances between chunks and learns about finished ones from a
 // copy of the control blocks taken one chunk behind the device.
 //
@@ -33,8 +36,11 @@
 #include "../../include/ot_assoc.h"
 #include "batch_kernels.h"
 #include "handle.h"
+#include "team_kernels.h"
 
 using namespace otk;
+
+const void* otk_team_kernel();  // team.hip
 
 namespace {
 
@@ -42,6 +48,12 @@ constexpr int kChunk = 8;  // iterations per captured chunk (even: list generati
 constexpr int64_t kTailItems = 256;  // at most this many items left: the chunk runs on the tail grids
 constexpr double kBatchStallBelow = 1e-7;  // FP32 sweeps are not trusted below this residual
 constexpr size_t kAlign = 256;
+// Iterations of one team launch. Batches: past any but the slowest instance,
+// and short enough that the longest list of a workgroup (kTeamLaunch instances
+// over 256 workgroups, at 6 us per iteration) ends far within the waits' bound.
+// Servers: new requests wait for the launch to end.
+constexpr int kTeamCapBatch = 1024, kTeamCapServe = 256;
+constexpr size_t kTeamLaunch = 1024;  // instances of one launch
 
 double now_s() {
     using namespace std::chrono;
@@ -243,7 +255,7 @@ struct BatchEngine {
     ot_status init(int dev, hipStream_t st, int slots_cap, int items_cap, size_t budget);
     ot_status prepare_kernels();
     ot_status capture(int widx);
-    ot_status admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict);
+    ot_status admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict, bool queue);
     ot_status upload_cost(Slot& s, const ot_cost_desc* c, char* C_mem, char* stage, PadJob* pad, GeoJob* geo);
     ot_status launch_chunk();
     ot_status collect(bool wait, std::vector<int>& finished);
@@ -253,6 +265,15 @@ struct BatchEngine {
     ot_status tune(const std::vector<int>& batch_slots);
     std::string tune_key(const std::vector<int>& batch_slots) const;
     ot_status relayout(const std::vector<int>& batch_slots, int w, int64_t rpp);
+    // teams: job, item and list staging, exchange blocks, control blocks read back
+    int lds_max = 0;
+    char *team_h = nullptr, *team_d = nullptr;
+    size_t team_cap = 0;
+    double* team_xch = nullptr;
+    size_t team_xch_cap = 0;
+    Ctl* team_ctl = nullptr;
+    ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left);
+    ot_status run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished, std::vector<int>& left);
     int widx() const { return waves == 4 ? 0 : 1; }
     int gidx() const { return 2 * widx() + (items_running <= kTailItems ? 1 : 0); }
 };
@@ -280,10 +301,10 @@ BatchEngine::~BatchEngine() {
     if (stream) hipStreamSynchronize(stream);
     for (auto g : graph)
         if (g) hipGraphExecDestroy(g);
-    void* dev_bufs[] = {tab, ctl, lists_mem, blob_d[0], blob_d[1], relay_d};
+    void* dev_bufs[] = {tab, ctl, lists_mem, blob_d[0], blob_d[1], relay_d, team_d, team_xch};
     for (void* p : dev_bufs)
         if (p) hipFree(p);
-    void* host_bufs[] = {snap[0], snap[1], blob_h[0], blob_h[1], relay_h};
+    void* host_bufs[] = {snap[0], snap[1], blob_h[0], blob_h[1], relay_h, team_h, team_ctl};
     for (void* p : host_bufs)
         if (p) hipHostFree(p);
     hipEvent_t evs[] = {ev_snap[0], ev_snap[1], ev_adm[0], ev_adm[1]};
@@ -328,6 +349,10 @@ ot_status BatchEngine::init(int dev, hipStream_t st, int slots_cap, int items_ca
     ECHK(this, hipHostMalloc(&relay_h, sizeof(int) * 2 * cap_slots));
     ECHK(this, otk_host::dev_malloc((void**)&relay_d, sizeof(int) * 2 * cap_slots));
     for (auto& s : snap) ECHK(this, hipHostMalloc(&s, sizeof(Ctl) * cap_slots));
+    ECHK(this, hipHostMalloc(&team_ctl, sizeof(Ctl) * cap_slots));
+    int coop = 0;
+    if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) lds_max = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) lds_max = 0;
     for (auto& e : ev_snap) ECHK(this, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     slots.assign(cap_slots, Slot{});
     free_slots.clear();
@@ -538,7 +563,8 @@ static ot_status check_desc(BatchEngine* e, const ot_cost_desc* c) {
 // that fits and reports the admitted slots. Settings are checked here,
 // marginal values on the device, so admission never waits on the GPU beyond
 // the staging set of the admission before last.
-ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict) {
+ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict,
+                             bool queue) {
     out_slots.clear();
     if (reqs.empty()) return OT_OK;
     ECHK(this, hipSetDevice(device));
@@ -711,6 +737,7 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
         J1.slot = k;
         J1.item_base = n_items;
         J1.inst_pos = n_insts;
+        J1.queue = queue ? 1 : 0;
         n_items += parts;
         n_cap += parts_cap;
         ++n_insts;
@@ -743,7 +770,7 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
             hipLaunchKernelGGL(k_bmat_jobs, dim3(mat_blocks), dim3(512), 0, stream, geos_d, n_geos);
         hipLaunchKernelGGL(k_badmit_jobs, dim3(n_insts), dim3(256), 0, stream, (const AdmJob*)blob_d[set], tab, ctl,
                            L[0]);
-        hipLaunchKernelGGL(k_bcount, dim3(1), dim3(64), 0, stream, L[0], n_items, n_insts);
+        if (queue) hipLaunchKernelGGL(k_bcount, dim3(1), dim3(64), 0, stream, L[0], n_items, n_insts);
         ECHK(this, hipGetLastError());
         ECHK(this, hipEventRecord(ev_adm[set], stream));
         adm_pending[set] = true;
@@ -752,6 +779,184 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
         items_running += n_cap;
     }
     for (char* x : stages) pool.release(x);
+    return OT_OK;
+}
+
+// ------------------------------------------------------------------ teams --
+// Row split and team size of an instance, by its own size alone: as few
+// workgroups as its kernel fits (the exchange, most of an iteration, costs
+// the same however many share it), with equal shares.
+namespace {
+struct TeamShape {
+    int cls = 0, rpw = 0, nb = 0, ncl = 0;
+    size_t lds = 0;
+};
+constexpr int kTeamRows = 16;  // rows of a workgroup's step (8 waves, two rows each)
+
+bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
+    t.cls = team_class(J);
+    const int cpl = team_cpl(t.cls), width = cpl * 32;
+    t.ncl = (J + 31) / 32;
+    const int Jp = t.ncl * 32, slack = width - Jp;
+    const int groups = std::min(num_cu, kMaxCoopGroups);
+    auto lds_of = [&](int64_t rpw, int nb) { return persist_lds_bytes((int)rpw, J, Jp, 8, width, slack, nb) + 2048; };
+    const size_t fixed = lds_of(0, 1), per_row = (size_t)Jp * 4 + 32;  // (owned columns shrink with nb: bounded by nb = 1)
+    if (lds_max <= 0 || fixed + kTeamRows * per_row > (size_t)lds_max) return false;
+    const int64_t most = (int64_t)(((size_t)lds_max - fixed) / per_row) / kTeamRows * kTeamRows;
+    const int64_t nb = (I + most - 1) / most;
+    if (most < kTeamRows || nb > groups) return false;
+    t.rpw = (int)(((I + nb - 1) / nb + kTeamRows - 1) / kTeamRows * kTeamRows);
+    t.nb = (int)((I + t.rpw - 1) / t.rpw);
+    t.lds = lds_of(t.rpw, t.nb) - 2048;
+    return lds_of(t.rpw, t.nb) <= (size_t)lds_max;
+}
+}  // namespace
+
+// Solves admitted instances by teams; waits for them. Those that are done are
+// returned in `finished`, the others queued for the chunks and in `left`.
+ot_status BatchEngine::run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished,
+                                 std::vector<int>& left) {
+    finished.clear();
+    left.clear();
+    for (size_t q = 0; q < ks.size(); q += kTeamLaunch)
+        if (ot_status st = run_team_group(ks.data() + q, std::min(kTeamLaunch, ks.size() - q), cap, finished, left))
+            return st;
+    if (left.empty()) return OT_OK;
+    for (int q = 0; q < 2; ++q)  // (relay_h is idle: its last reader was waited for)
+        if (ot_status st = wait_staging(q)) return st;
+    for (size_t q = 0; q < left.size(); ++q) relay_h[q] = left[q];
+    ECHK(this, hipMemcpyAsync(relay_d, relay_h, sizeof(int) * left.size(), hipMemcpyHostToDevice, stream));
+    hipLaunchKernelGGL(k_brequeue, dim3((unsigned)left.size()), dim3(256), 0, stream, tab, (const int*)relay_d,
+                       rpp_rows, L[0]);
+    ECHK(this, hipGetLastError());
+    ECHK(this, hipStreamSynchronize(stream));
+    return OT_OK;
+}
+
+ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished,
+                                      std::vector<int>& left) {
+    const int groups = std::min(num_cu, kMaxCoopGroups);
+    struct Entry {
+        int slot;
+        TeamShape t;
+        size_t xch;
+    };
+    std::vector<Entry> jobs;
+    size_t xch = 0, n_items = 0;
+    for (size_t q = 0; q < n; ++q) {
+        const Slot& sl = slots[ks[q]];
+        Entry e{ks[q], {}, xch};
+        if (!team_shape(sl.I, sl.J, groups, lds_max, e.t)) {
+            continue;  // (too large for LDS: it stays as admitted)
+        }
+        xch += (persist_exchange_doubles(e.t.nb, sl.J) + 31) / 32 * 32;
+        n_items += (size_t)e.t.nb;
+        jobs.push_back(e);
+    }
+    if (!jobs.empty()) {
+        // the largest teams first (ties in request order)
+        std::stable_sort(jobs.begin(), jobs.end(), [](const Entry& a, const Entry& b) { return a.t.nb > b.t.nb; });
+        const size_t jobs_b = align_up(sizeof(TeamJob) * jobs.size()), items_b = align_up(sizeof(int2) * n_items);
+        const size_t need = jobs_b + items_b + align_up(sizeof(int) * (size_t)(groups + 1));
+        if (team_cap < need) {
+            if (team_h) hipHostFree(team_h);
+            if (team_d) hipFree(team_d);
+            team_h = team_d = nullptr;
+            team_cap = 0;
+            ECHK(this, hipHostMalloc(&team_h, 2 * need));
+            ECHK(this, otk_host::dev_malloc((void**)&team_d, 2 * need));
+            team_cap = 2 * need;
+        }
+        if (team_xch_cap < xch) {
+            if (team_xch) hipFree(team_xch);
+            team_xch = nullptr;
+            team_xch_cap = 0;
+            ECHK(this, otk_host::dev_malloc((void**)&team_xch, sizeof(double) * xch));
+            team_xch_cap = xch;
+        }
+        TeamJob* jh = (TeamJob*)team_h;
+        int2* ih = (int2*)(team_h + jobs_b);
+        int* sh = (int*)(team_h + jobs_b + items_b);
+        size_t lds = 0;
+        std::vector<double> load((size_t)groups, 0.0);
+        std::vector<int> order((size_t)groups);
+        for (int b = 0; b < groups; ++b) order[b] = b;
+        std::vector<std::vector<int2>> lists((size_t)groups);
+        for (size_t q = 0; q < jobs.size(); ++q) {
+            const Entry& e = jobs[q];
+            const Slot& sl = slots[e.slot];
+            TeamJob& J = jh[q];
+            J = TeamJob{};
+            PersistArgs& A = J.A;
+            A.I = sl.I;
+            A.J = sl.J;
+            A.Jp = e.t.ncl * 32;
+            A.ncl = e.t.ncl;
+            A.rpw = e.t.rpw;
+            A.max_spin = 1 << 21;
+            A.stall_below = kBatchStallBelow;
+            A.a = sl.d.a;
+            A.b = sl.d.b;
+            A.f[0] = sl.d.f[0];
+            A.f[1] = sl.d.f[1];
+            A.g[0] = sl.d.g[0];
+            A.g[1] = sl.d.g[1];
+            A.xch = team_xch + e.xch;
+            A.ctl = ctl + e.slot;
+            A.prm = sl.prm;
+            A.batch = 1;
+            A.cap = cap;
+            J.src = DenseSrc<float>{sl.d.C, sl.d.ld};
+            J.nb = e.t.nb;
+            J.cls = e.t.cls;
+            lds = std::max(lds, e.t.lds);
+            // the nb workgroups with the least work so far, the first of
+            // `order` (an instance starts when its last member is free);
+            // they then go behind all with no more work than theirs
+            const double cost = 3.0 + (double)e.t.rpw * e.t.ncl / 800.0;  // us per iteration: exchange, rows
+            const double at = load[order[e.t.nb - 1]] + cost;
+            for (int r = 0; r < e.t.nb; ++r) {
+                load[order[r]] = at;
+                lists[order[r]].push_back(int2{(int)q, r});
+            }
+            const auto rest = order.begin() + e.t.nb;
+            std::rotate(order.begin(), rest,
+                        std::upper_bound(rest, order.end(), at, [&](double x, int b) { return x < load[b]; }));
+        }
+        int pos = 0;
+        for (int b = 0; b < groups; ++b) {
+            sh[b] = pos;
+            for (const int2& it : lists[b]) ih[pos++] = it;
+        }
+        sh[groups] = pos;
+        ECHK(this, hipMemcpyAsync(team_d, team_h, need, hipMemcpyHostToDevice, stream));
+        hipLaunchKernelGGL(k_team_clear, dim3((unsigned)std::min<size_t>(2048, (xch + 255) / 256)), dim3(256), 0, stream,
+                           team_xch, xch);
+        const void* kern = otk_team_kernel();
+        ECHK(this, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        const TeamJob* jd = (const TeamJob*)team_d;
+        const int2* id = (const int2*)(team_d + jobs_b);
+        const int* sd = (const int*)(team_d + jobs_b + items_b);
+        void* args[] = {(void*)&jd, (void*)&id, (void*)&sd};
+        // (refused: the instances stay as admitted and go to the chunks)
+        if (hipLaunchCooperativeKernel(kern, dim3((unsigned)groups), dim3(512), args, (unsigned)lds, stream) != hipSuccess)
+            (void)hipGetLastError();
+    }
+    ECHK(this, hipMemcpyAsync(team_ctl, ctl, sizeof(Ctl) * std::max(hi_slot, 1), hipMemcpyDeviceToHost, stream));
+    ECHK(this, hipStreamSynchronize(stream));
+    for (size_t q = 0; q < n; ++q) {
+        Slot& s = slots[ks[q]];
+        const Ctl& c = team_ctl[ks[q]];
+        if (c.phase == kPhDone) {
+            s.fin = c;
+            s.finished = true;
+            --n_live_running;
+            items_running -= s.parts_cap;
+            finished.push_back(ks[q]);
+        } else {
+            left.push_back(ks[q]);
+        }
+    }
     return OT_OK;
 }
 
@@ -1004,6 +1209,7 @@ static void fill_result(const Slot& s, ot_assoc_result* r) {
     const Ctl& c = s.fin;
     ot_status rs = OT_OK;
     if (c.numeric_bad == 2) rs = OT_EINVAL;  // marginals rejected on the device
+    else if (c.sync_fail) rs = OT_EDEVICE;   // a wait of its team gave up
     else if (c.numeric_bad || !std::isfinite(c.chk_violation)) rs = OT_ENUMERIC;
     else if (!(c.chk_violation < c.tol)) rs = OT_WARN_MAXITER;
     r->iterations = c.result_iter;
@@ -1137,7 +1343,7 @@ ot_status ot_assoc_solve_batch(ot_assoc* h, int n, const ot_cost_desc* costs, co
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     std::vector<int> ks;
-    ot_status st = e->admit(reqs, ks, true);
+    ot_status st = e->admit(reqs, ks, true, true);
     if (!st) {
         // marginals were checked on the device: one read-back for all of them
         const int hi = *std::max_element(ks.begin(), ks.end()) + 1;
@@ -1159,7 +1365,13 @@ ot_status ot_assoc_solve_batch(ot_assoc* h, int n, const ot_cost_desc* costs, co
     if (!st && !h->opt.batch_tune) st = e->relayout(ks, 8, 128);
     if (!st) {
         hipEventRecord(e0, e->stream);
-        st = run_to_completion(e, ks, (long)max_iter / kChunk + 16);
+        std::vector<int> fin, left = ks;
+        if (h->opt.persistent) {
+            // (the items queued for the tuner's sweeps are not taken)
+            hipLaunchKernelGGL(k_bclear, dim3(1), dim3(64), 0, e->stream, e->L[0]);
+            st = e->run_teams(ks, kTeamCapBatch, fin, left);
+        }
+        if (!st && !left.empty()) st = run_to_completion(e, left, (long)max_iter / kChunk + 16);
         hipEventRecord(e1, e->stream);
         hipEventSynchronize(e1);
     }
@@ -1435,6 +1647,7 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
     // fails is retried one request at a time, so that the error completes
     // the request it belongs to.
     size_t gmax = kServeAdmitGroup;
+    std::vector<int> admitted;
     auto complete_with = [&](const Pending& p, ot_status st) {
         ot_completion c{};
         c.ticket = p.ticket;
@@ -1470,7 +1683,7 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
             gres.push_back(res);
         }
         std::vector<int> ks;
-        ot_status st = e.admit(group, ks, false);
+        ot_status st = e.admit(group, ks, false, false);
         if (st) {
             if (group.size() > 1) {
                 gmax = 1;
@@ -1500,11 +1713,15 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
             s->warm_of[ks[q]] = gres[q] ? 1 : 0;
             if (gres[q]) gres[q]->last_use = ++s->tick;
             s->running.push_back(ks[q]);
+            admitted.push_back(ks[q]);
             s->queue.pop_front();
         }
     }
-    // 2. one chunk, and the snapshot behind the previous one
-    std::vector<int> fin;
+    // 2. the admitted requests by teams; then one chunk of what those left (now
+    // or earlier), and the snapshot behind the previous chunk
+    std::vector<int> fin, done_now, left;
+    if (!admitted.empty())
+        if (ot_status st = e.run_teams(admitted, kTeamCapServe, done_now, left)) return serve_fail(s, st, e.err);
     if (e.n_live_running > 0) {
         if (ot_status st = e.launch_chunk()) return serve_fail(s, st, e.err);
         if (ot_status st = e.collect(true, fin)) return serve_fail(s, st, e.err);
@@ -1512,6 +1729,7 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
         if (ot_status st = e.drain_snapshot(&fin)) return serve_fail(s, st, e.err);
         e.snap_pending = -1;
     }
+    fin.insert(fin.end(), done_now.begin(), done_now.end());
     // 3. completions: keep the layouts' potentials, then free the slots (once
     // the resident copies that read them are queued, so that no slot memory
     // is handed out again while a pending copy still reads it)

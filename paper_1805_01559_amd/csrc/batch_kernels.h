@@ -25,7 +25,6 @@ namespace otk {
 
 constexpr int kBatchMaxJ = 512;  // RRHs per batched instance (4 column classes)
 
-enum : int { kPhFast = 0, kPhPolish = 1, kPhCheck = 2, kPhExact = 3, kPhDone = 4 };
 enum : int { kItPrev = 1, kItPar = 2, kItCheck = 4 };
 
 // One instance of the batch. The cost is a padded FP32 row-major matrix
@@ -338,7 +337,7 @@ struct AdmJob {
     int slot;
     int item_base;  // offset of its items among this admission's items
     int inst_pos;   // position among this admission's instances
-    int pad_;
+    int queue;      // 1: queues its first sweep items (0: it goes to a team)
 };
 
 // One workgroup per admitted instance: copies and checks its marginals
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(256) void k_badmit_jobs(const AdmJob* __restrict__ 
     }
     const int base = l.cnt[0] + J.item_base;
     const int flags = J.f0 ? kItPrev : 0;
-    for (int p = threadIdx.x; p < d.parts; p += blockDim.x) l.it32[base + p] = BItem{J.slot, p, flags, 0};
+    for (int p = threadIdx.x; J.queue && p < d.parts; p += blockDim.x) l.it32[base + p] = BItem{J.slot, p, flags, 0};
     __syncthreads();
     if (threadIdx.x == 0) {
         const double ta = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
@@ -401,7 +400,7 @@ __global__ __launch_bounds__(256) void k_badmit_jobs(const AdmJob* __restrict__ 
         ctls[J.slot] = c;
         tab[J.slot] = d;
         *J.prm_dst = J.sp;
-        l.inst[l.cnt[2] + J.inst_pos] = J.slot;
+        if (J.queue) l.inst[l.cnt[2] + J.inst_pos] = J.slot;
     }
 }
 
@@ -428,6 +427,28 @@ __global__ __launch_bounds__(256) void k_brelayout(BInst* tab, const int* __rest
         tab[k].parts = parts;
         l.inst[blockIdx.x] = k;
     }
+}
+
+// Queues the next sweep items of instances that a team has left to the sweeps
+// (FP32 ones that reached its iteration cap or had no team, FP64 ones whose
+// check missed tol), in rows per part rpp, behind what the list holds.
+__global__ __launch_bounds__(256) void k_brequeue(BInst* tab, const int* __restrict__ slots, int64_t rpp, BList l) {
+    __shared__ int s_base;
+    const int k = slots[blockIdx.x];
+    const Ctl* c = tab[k].ctl;
+    const bool exact = c->phase == kPhExact;
+    const int64_t I = tab[k].I;
+    const int parts = (int)((I + rpp - 1) / rpp);
+    if (threadIdx.x == 0) {
+        tab[k].rpp = rpp;
+        tab[k].parts = parts;
+        s_base = atomicAdd(&l.cnt[exact ? 1 : 0], parts);
+        l.inst[atomicAdd(&l.cnt[2], 1)] = k;
+    }
+    __syncthreads();
+    const int flags = (c->has_prev ? kItPrev : 0) | ((c->iter & 1) ? kItPar : 0);
+    BItem* dst = (exact ? l.it64 : l.it32) + s_base;
+    for (int p = threadIdx.x; p < parts; p += blockDim.x) dst[p] = BItem{k, p, flags, 0};
 }
 
 // Clears a list generation (all three counters).

@@ -21,22 +21,43 @@ constexpr double kLn2 = 0.69314718055994530942;
 // instructions of the library's exp2. For finite t only (results below the
 // smallest subnormal round through ldexp to 0, above the largest double to
 // infinity); callers select away lanes whose t is not finite.
+// The integer part comes from adding 1.5 2^52 (rounding to the nearest, ties to
+// even, in the sum's low bits): the rounding and conversion instructions run
+// at a quarter of the FP64 add's rate.
+constexpr double kRoundMagic = 0x1.8p52;
 __device__ __forceinline__ double exp2_tab(double t, const double* tab) {
-    const double k = __builtin_rint(t * 64.0);
-    const double r = fma(k, -1.0 / 64.0, t);  // exact for |t| < 2^46
-    // (the conversion is clamped to keep it defined: beyond |t| = 2^14 the
-    // result is 0 or infinity either way, and a NaN t stays NaN through q)
-    const int ki = (int)fmin(fmax(k, -1048576.0), 1048576.0);
-    const int j = ki & 63, n = ki >> 6;
-    const double x = r * kLn2;
+    // (beyond |t| = 1100 the result is 0 or infinity either way)
+    const double tc = fmin(fmax(t, -1100.0), 1100.0);
+    const double s = fma(tc, 64.0, kRoundMagic);
+    const int ki = (int)__double_as_longlong(s);  // low word: round(64 t)
+    const double r = fma(s - kRoundMagic, -1.0 / 64.0, tc);  // exact
+    const double x = fma(r, kLn2, t - t);  // (a NaN t stays NaN)
     double q = fma(x, 1.0 / 720.0, 1.0 / 120.0);
     q = fma(x, q, 1.0 / 24.0);
     q = fma(x, q, 1.0 / 6.0);
     q = fma(x, q, 0.5);
     q = fma(x, q, 1.0);
     q *= x;
-    const double T = tab[j];
-    return ldexp(fma(T, q, T), n);
+    const double T = tab[ki & 63];
+    return ldexp(fma(T, q, T), ki >> 6);
+}
+// The same for arguments of a stored kernel: t <= 1 (entries shifted by about
+// their row's largest), results below 2^-1000 as 2^-1000 (stored in FP32 they
+// are 0). The scaling is an addition to the exponent.
+__device__ __forceinline__ double exp2_tab_neg(double t, const double* tab) {
+    const double tc = fmax(t, -1000.0);
+    const double s = fma(tc, 64.0, kRoundMagic);
+    const int ki = (int)__double_as_longlong(s);
+    const double x = fma(s - kRoundMagic, -1.0 / 64.0, tc) * kLn2;
+    double q = fma(x, 1.0 / 720.0, 1.0 / 120.0);
+    q = fma(x, q, 1.0 / 24.0);
+    q = fma(x, q, 1.0 / 6.0);
+    q = fma(x, q, 0.5);
+    q = fma(x, q, 1.0);
+    q *= x;
+    const double T = tab[ki & 63];
+    const long long y = __double_as_longlong(fma(T, q, T));
+    return __longlong_as_double(y + ((long long)(ki >> 6) << 52));
 }
 // Fills tab[j] = 2^(j/64), j < 64, by the first 64 threads of the workgroup;
 // the caller synchronises before use.
@@ -201,6 +222,9 @@ enum : int {
     kModePolish = 1,  // FP64 sweeps run unconditionally (no stop decision)
     kModeExact = 2,   // FP64 sweeps: stop when an FP64 iterate meets tol
 };
+
+// Phase of an instance of a batch.
+enum : int { kPhFast = 0, kPhPolish = 1, kPhCheck = 2, kPhExact = 3, kPhDone = 4 };
 
 struct Ctl {
     int32_t iter;          // full iterations completed (the current iterate's number)

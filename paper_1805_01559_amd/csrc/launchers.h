@@ -209,7 +209,6 @@ constexpr int check_nch() { return VEC == 4 ? 8 : VEC == 2 ? 16 : 32; }  // J <=
 // narrow instantiation (J <= 512) has the registers for a second set of
 // column accumulators; the wide one is at the register limit without them
 // (with them it spills, at eight waves and at four).
-constexpr int kFusedLoadsJ = 512;
 inline bool check_fuses_loads(const Shape& s) {
     const int wide = s.vec == 4 ? 8 : s.vec == 2 ? 16 : 32;
     return s.lpr == 64 && s.nch <= wide / 4;

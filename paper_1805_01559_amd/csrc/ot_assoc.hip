@@ -747,8 +747,9 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.prm = h->prm;
     A.tile = h->ker;
     A.validate = h->validate_pending ? 1 : 0;
+    A.cap = 1 << 30;
     // (Alg. 2's solves sum the loads; their plans are not asked for)
-    A.loads = h->want_loads && J <= kFusedLoadsJ ? h->loads : nullptr;
+    A.loads = h->want_loads && p.cpl <= kLoadsCpl ? h->loads : nullptr;
     A.plan_out = (A.loads || I * J > h->plan_cap) ? nullptr : h->plan_out;
     A.plan_f64 = h->plan_dtype == OT_F64 ? 1 : 0;
     h->loads_fresh = A.loads != nullptr;

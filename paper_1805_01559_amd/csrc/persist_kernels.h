@@ -22,8 +22,8 @@
 // only when a reference is taken (C is then read again):
 //   - at the first iteration, and again when a scaling leaves [2^-40, 2^40];
 //   - once the residual is below 1e-5 (for targets below the FP32 noise of
-//     about 4e-8 of residual). From there on the iteration adds to the FP64 sums
-//     R_i of the reference, and likewise to those of its columns, only the
+//     about 4e-8 of residual), with FP64 exponentials. From there on the iteration
+//     adds to the FP64 sums R_i of the reference, and likewise to those of its columns, only the
 //     change against it, S_i = R_i + sum_j E_ij (v_j - 1), so its FP32 rounding is 2^-24 of |v - 1| instead of
 //     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
 //     cost were needed before.
@@ -115,6 +115,14 @@ __host__ __device__ inline XchLayout persist_xch_layout(int nb, int J) {
 }
 __host__ __device__ inline size_t persist_exchange_doubles(int nb, int J) { return persist_xch_layout(nb, J).total; }
 
+// Pause between two polls: short while the other side is about to answer,
+// longer in a wait that lasts (a workgroup that an earlier instance of its
+// batch still holds), so that the polls leave the memory system alone.
+__device__ __forceinline__ void poll_pause(int spin) {
+    if (spin < 64) __builtin_amdgcn_s_sleep(1);
+    else __builtin_amdgcn_s_sleep(16);
+}
+
 // Polls U tagged slots per lane of one wave (slot u of lane l at
 // base[(u 64 + l) stride] for u 64 + l < n) until each holds tag k; absent
 // slots read 0. Returns false if the wait gave up (bound reached or abort set).
@@ -137,7 +145,7 @@ __device__ bool poll_tagged(const double* base, int64_t stride, int n, int k, do
             put_agent(abort_word, (uint64_t)1);
             return false;
         }
-        __builtin_amdgcn_s_sleep(1);
+        poll_pause(spin);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = u * kWave + lane;
@@ -170,6 +178,19 @@ struct PersistArgs {
     void* plan_out;  // I x J plan the final check writes, or null
     int plan_f64;
     double* loads;   // J: RRH loads the final check sums, or null
+    int batch;       // an instance of a batch: its control block carries a phase (kPh...)
+    int cap;         // iterations of this launch (an instance of a batch that reaches it goes on in sweeps)
+};
+
+// Static LDS of the cooperative phase.
+struct PersistShared {
+    Ctl cs;  // decision workgroup: the control block for the whole launch
+    double e2tab[64];
+    double wres[8];
+    double wst[8][7];           // the final check's scalars
+    double ored[8][kColBlock];  // per-wave column sums of an owned block
+    uint32_t dec;
+    int flag[2];  // by iteration parity: 1 a wait gave up, 2 v not finite, 4 v out of the reference's range
 };
 
 // Column blocks each workgroup owns at most (workgroup w owns w, w + nb, ...).
@@ -207,6 +228,9 @@ constexpr double kDeltaBelow = 1e-5;
 // flushed to zero in FP32 (below 2^-126 of its row's largest) then stands for
 // less than 2^-46 of any row or column sum.
 constexpr double kScaleMax = 0x1p40;
+// The final check sums RRH loads up to this many cells per lane (416 columns):
+// the second set of FP64 column sums takes wider rows past the registers.
+constexpr int kLoadsCpl = 13;
 // The delta sums keep |v - 1| below this (else the reference is renewed).
 constexpr double kDeltaMax = 0.125;
 
@@ -217,8 +241,8 @@ constexpr double kDeltaMax = 0.125;
 // 1e-6 of the residual r_ref at which the reference was taken and are therefore
 // compared with tol itself. Long delta phases (a slowly converging instance
 // whose scalings drift far from the reference) renew the reference.
-__device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, double& r_ref,
-                                             int& k_ref) {
+__device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, bool batch,
+                                             double& r_ref, int& k_ref) {
     const int k = c->iter + 1;
     const double r = c->has_prev ? rsum / c->mass : pinf64();
     const bool bad = c->numeric_bad || (c->has_prev && !isfinite(r));
@@ -239,7 +263,10 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
     const bool met = r < target && (fine || target >= stall_below);
     const bool at_check = c->check_every <= 1 || k % c->check_every == 0;
     int code = 0;
-    if (kind == kItRefDelta) k_ref = k;
+    if (kind == kItRefDelta) {
+        k_ref = k;
+        if (batch) c->fp64_iters += 1;  // (a sweep of FP64 exponentials; a single solve counts those after the phase)
+    }
     if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kDeltaBelow)) {
         r_ref = r;
         code = kDecRefDelta;
@@ -265,20 +292,24 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
 // GM: the streamed form, for instances whose kernel does not fit in LDS. The
 // tile is in device memory and every iteration reads it once, PD row steps
 // ahead (64 - 128 KB in flight per CU). Bound by that read.
-template <class Src, int CPL, int LPR, int WAVES, bool GM>
-__global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
+//
+// One workgroup's part of the phase: workgroup blk of the nb that solve the
+// instance together.
+template <class Src, int CPL, int LPR, int WAVES, bool GM, bool LEAN = false>
+__device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src, const int nb, const int blk,
+                                            PersistShared& ps) {
     extern __shared__ __align__(16) float4 sm4[];  // (its 16-byte reads have to be aligned)
     double* sm = reinterpret_cast<double*>(sm4);
     constexpr int R = kWave / LPR;
     constexpr int T = WAVES * kWave;
-    constexpr int U = CPL <= 4 ? 8 : CPL <= 16 ? 5 : 1;  // row steps at a time (their sums' chains overlap)
+    constexpr int U = CPL <= 4 ? 8 : CPL <= 16 ? (LEAN && CPL > 8 ? 4 : 5) : 1;  // row steps at a time (their sums' chains overlap)
     static_assert(WAVES >= 4 && WAVES <= 8, "at least one wave per publishing column block, wres and ored sized for 8");
     int J = A.J, Jp = A.Jp, ncl = A.ncl;
     const int rpw = A.rpw;
     int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (nothing derived from it is kept across a batch's instances)
     int lane = tid & (kWave - 1), w = tid / kWave;
     int sub = lane % LPR, rg = lane / LPR;
-    const int nb = (int)gridDim.x, blk = (int)blockIdx.x;
     const int64_t r0 = (int64_t)blk * rpw;
     const int nrows = (int)max((int64_t)0, min((int64_t)rpw, A.I - r0));
     constexpr int WD = CPL * LPR;  // width of x and of the fold buffer
@@ -296,13 +327,13 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the reference (delta sums)
     float* xl = reinterpret_cast<float*>(cl + (size_t)kColBlock * nown);  // v_j, or v_j - 1 for delta sums, in FP32
     float* red = xl + WD;
-    __shared__ Ctl cs;  // decision workgroup: the control block for the whole launch
-    __shared__ double e2tab[64];
-    __shared__ double wres[WAVES];
-    __shared__ double wst[WAVES][7];  // the final check's scalars
-    __shared__ double ored[WAVES][kColBlock];  // per-wave column sums of an owned block
-    __shared__ uint32_t s_dec;
-    __shared__ int s_flag[2];  // by iteration parity: 1 a wait gave up, 2 v not finite, 4 v out of the reference's range
+    Ctl& cs = ps.cs;
+    auto& e2tab = ps.e2tab;
+    auto& wres = ps.wres;
+    auto& wst = ps.wst;
+    auto& ored = ps.ored;
+    auto& s_dec = ps.dec;
+    auto& s_flag = ps.flag;
 
     const XchLayout X = persist_xch_layout(nb, J);
     double* part = A.xch + X.part;
@@ -324,7 +355,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         ml[lr] = 0.0;
         Rl[lr] = Sl[lr] = 1.0;
     }
-    const double* g_in = A.g[k0 & 1];
+    const double* g_in = (k0 & 1) ? A.g[1] : A.g[0];
     for (int j = tid; j < J; j += T) {
         gl[j] = g_in[j];
         vl[j] = 1.0;
@@ -352,12 +383,13 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     const int steps = rpw / (WAVES * R);
     [[maybe_unused]] volatile int bad_before = 0;
     double res = 0.0;  // this lane's part of the row residual of the previous iterate
-    int k = k0;
+    int k = k0, kind = kItRef;
 
     // Row update of an iteration that takes a new reference G = g: the kernel
     // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i about the row maximum,
-    // in FP64 (the table-driven exponential), stored in FP32; S_i = R_i and the
-    // column partials sum_i E_ij a_i / S_i are sums of the FP64 entries.
+    // from FP64 arguments, stored in FP32; S_i = R_i and the column partials
+    // sum_i E_ij a_i / S_i are FP64 sums. For delta sums the exponentials are
+    // FP64, too (table-driven), and the sums those of the FP64 entries.
     auto take_reference = [&](double (&ac)[CPL]) {
         constexpr bool kAhead = Src::kCheap && CPL <= 16;  // a row's loads one step ahead, where the registers allow it
         double* stage = reinterpret_cast<double*>(red);
@@ -369,7 +401,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         // the previous row sums as logarithms (log2 sum_j exp((g_j - C_ij) / eps)),
         // at the launch's start from f
         for (int lr = tid; lr < nrows; lr += T)
-            Rl[lr] = k == k0 + 1 ? (has_prev ? (log(al[lr]) - A.f[k0 & 1][r0 + lr] * inv_eps) * kLog2e : 0.0)
+            Rl[lr] = k == k0 + 1 ? (has_prev ? (log(al[lr]) - ((k0 & 1) ? A.f[1] : A.f[0])[r0 + lr] * inv_eps) * kLog2e : 0.0)
                                  : ml[lr] + log2(Sl[lr]);
         __syncthreads();
 #pragma unroll
@@ -424,14 +456,22 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 }
             }
             const double m = fmax((double)group_max<LPR>(mx), -1e300);
+            if (kind == kItRefDelta) {
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) {
+                    t[q] = exp2_tab_neg(t[q] - m, e2tab);
+                    if constexpr (!kAhead)
+                        if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) t[q] = (double)exp2_f32((float)(t[q] - m));
+            }
             double s = 0, s2 = 0;  // even and odd cells: two shorter add chains
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
-                t[q] = exp2_tab(fmax(t[q] - m, -2000.0), e2tab);  // (2^-2000 is 0)
                 if (q & 1) s2 += t[q];
                 else s += t[q];
-                if constexpr (!kAhead)
-                    if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
             const double S = group_sum<LPR>(s + s2);
             const double wq = vrow ? al[lr] / S : 0.0;
@@ -621,7 +661,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 fail = true;
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
+            poll_pause(spin);
 #pragma unroll
             for (int u = 0; u < NU; ++u)
                 if (!has_tag(x[u], kt)) x[u] = get_agent(pk + (size_t)(pb + PB * u) * X.Jp + j);
@@ -646,7 +686,6 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     };
 
     __syncthreads();
-    int kind = kItRef;
     bool ok = true, bad = false;
     for (;;) {
         ++k;
@@ -716,7 +755,8 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
                 for (int u = 0; u < 4; ++u) r += x[u];
                 r = wave_sum(r);
                 int code = 0;
-                if (lane == 0) code = bookkeep_coop(&cs, r, kind, A.stall_below, r_ref, k_ref);
+                if (lane == 0) code = bookkeep_coop(&cs, r, kind, A.stall_below, A.batch != 0, r_ref, k_ref);
+                if (lane == 0 && k - k0 >= A.cap) code = kDecStop;
                 code = __shfl(code, 0, kWave);
                 if (nb == 1) {
                     if (lane == 0) s_dec = (uint32_t)code;
@@ -778,8 +818,8 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             if (lane == 0) atomicOr(&s_flag[P], f);
         }
         __syncthreads();
-        const int fl = s_flag[P];
-        const uint32_t code = s_dec;
+        const int fl = __builtin_amdgcn_readfirstlane(s_flag[P]);
+        const uint32_t code = __builtin_amdgcn_readfirstlane(s_dec);
         // (the other parity's flags were last read before this iteration's
         // barriers, and are next set after the next iteration's first)
         if (tid == 0) s_flag[P ^ 1] = 0;
@@ -800,26 +840,42 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         //      sum_i C_ij pi_ij where they are asked for. In this launch it costs
         //      one pass and two hops of the exchange; as launches of its own it
         //      took five more (polish, combine, check, two folds).
+        J = __builtin_amdgcn_readfirstlane(J);
+        Jp = __builtin_amdgcn_readfirstlane(Jp);
+        ncl = __builtin_amdgcn_readfirstlane(ncl);
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(sub), "+v"(rg), "+s"(J), "+s"(Jp), "+s"(ncl));
         double* stage = reinterpret_cast<double*>(red);
         src.stage(stage, J);
-        double* fo = A.f[k & 1];
+        double* fo = (k & 1) ? A.f[1] : A.f[0];
         for (int lr = tid; lr < nrows; lr += T) {
             const double fi = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
             ml[lr] = fi;
             fo[r0 + lr] = fi;
         }
-        double* go = A.g[k & 1];
+        double* go = (k & 1) ? A.g[1] : A.g[0];
         for (int j = tid; j < J; j += T) {
             gl[j] += eps * log(vl[j]);
             if (blk == 0) go[j] = gl[j];
         }
         __syncthreads();
-        const bool with_loads = A.loads != nullptr;
-        double ac[CPL], acl[CPL];
+        constexpr bool kLoads = !LEAN && CPL <= kLoadsCpl;
+        const bool with_loads = kLoads && A.loads != nullptr;
+        double ac[CPL], acl[kLoads ? CPL : 1];
 #pragma unroll
-        for (int q = 0; q < CPL; ++q) ac[q] = acl[q] = 0.0;
+        for (int q = 0; q < CPL; ++q) ac[q] = acl[kLoads ? q : 0] = 0.0;
         double rowres = 0.0, cost = 0.0, ent = 0.0, mass = 0.0, fa = 0.0;
+        // (a row's loads one step ahead, as the references take them)
+        constexpr bool kAhead = Src::kCheap && CPL * sizeof(typename Src::template Raw<1>) <= (LEAN ? 32 : 104);
+        constexpr int G = Src::kTag == 5 ? 1 : LEAN && CPL > 8 ? 2 : LEAN || CPL > 13 ? (CPL < 4 ? CPL : 4) : CPL;  // cells at a time (their plan values held until stored)
+        typename Src::template Raw<1> nraw[kAhead ? CPL : 1];
+        [[maybe_unused]] auto fetch = [&](int st) {
+            const int lr = (st * WAVES + w) * R + rg;
+            auto row = src.row(r0 + (lr < nrows ? lr : 0));
+#pragma unroll
+            for (int q = 0; q < CPL; ++q)
+                if (q < ncl) nraw[kAhead ? q : 0] = src.template load<1>(row, q * LPR + sub, J);
+        };
+        if constexpr (kAhead) fetch(0);
         for (int st = 0; st < steps; ++st) {
             const int lr = (st * WAVES + w) * R + rg;
             const bool vrow = lr < nrows;
@@ -827,35 +883,56 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             auto row = src.row(i);
             const double fk = vrow ? ml[lr] * kk : 0.0;
             double rs = 0.0;
-            constexpr int G = CPL <= 16 ? CPL : 8;  // cells loaded at a time
-#pragma unroll
-            for (int q0 = 0; q0 < CPL; q0 += G) {
-                typename Src::template Raw<1> raw[G];
-#pragma unroll
-                for (int u = 0; u < G; ++u)
-                    if (q0 + u < CPL && q0 + u < ncl) raw[u] = src.template load<1>(row, (q0 + u) * LPR + sub, J);
+            // without a branch, so that the cells' exponentials overlap; a cell
+            // outside the instance, or of infinite cost, adds zeros
+            double pl[G];
+            auto cell = [&](int q, const typename Src::template Raw<1>& raw) {
+                const int j = q * LPR + sub;
+                const bool in = q < ncl && j < J && vrow;
+                pl[q % G] = 0.0;
+                if (Src::kTag == 5 && !in) return;  // (the geometry functor has no registers for several cells)
+                double c = 0.0;
+                if (in) c = src.template cost<true, 1>(row, raw, 0, i, j, stage);
+                // log2 pi_ij (rounded as in the plan kernel)
+                const double t = in ? fmax(fk + fma(c, -kk, gl[j] * kk), -2000.0) : -2000.0;
+                const double p = exp2_tab(t, e2tab);
+                c = p > 0.0 ? c : 0.0;
+                rs += p;
+                cost = fma(c, p, cost);
+                ent = fma(p, t * kLn2 - 1.0, ent);
+                if constexpr (kLoads) acl[q] = fma(c, p, acl[q]);
+                ac[q] += p;
+                pl[q % G] = p;
+            };
+            auto store = [&](int q0) {
+                if (!A.plan_out) return;
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
-                    const int q = q0 + u;
-                    const int j = q * LPR + sub;
+                    const int q = q0 + u, j = q * LPR + sub;
                     if (q < CPL && q < ncl && j < J && vrow) {
-                        const double c = src.template cost<true, 1>(row, raw[u], 0, i, j, stage);
-                        const double t = fk + fma(c, -kk, gl[j] * kk);  // log2 pi_ij (rounded as in the plan kernel)
-                        const double p = exp2_tab(fmax(t, -2000.0), e2tab);
-                        rs += p;
-                        if (p > 0.0) {  // (an infinite cost has no mass and adds nothing)
-                            cost = fma(c, p, cost);
-                            ent = fma(p, t * kLn2 - 1.0, ent);
-                            if (with_loads) acl[q] = fma(c, p, acl[q]);
-                        }
-                        ac[q] += p;
-                        if (A.plan_out) {
-                            if (A.plan_f64) reinterpret_cast<double*>(A.plan_out)[i * J + j] = p;
-                            else reinterpret_cast<float*>(A.plan_out)[i * J + j] = (float)p;
-                        }
+                        if (A.plan_f64) reinterpret_cast<double*>(A.plan_out)[i * J + j] = pl[u];
+                        else reinterpret_cast<float*>(A.plan_out)[i * J + j] = (float)pl[u];
                     }
                 }
-                if constexpr (CPL > 16) __builtin_amdgcn_sched_barrier(0);
+            };
+            typename Src::template Raw<1> raw[kAhead ? CPL : G];
+            if constexpr (kAhead) {
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) raw[q] = nraw[q];
+                if (st + 1 < steps) fetch(st + 1);
+            }
+#pragma unroll
+            for (int q0 = 0; q0 < CPL; q0 += G) {
+                if constexpr (!kAhead) {
+#pragma unroll
+                    for (int u = 0; u < G; ++u)
+                        if (q0 + u < CPL && q0 + u < ncl) raw[u] = src.template load<1>(row, (q0 + u) * LPR + sub, J);
+                }
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    if (q0 + u < CPL) cell(q0 + u, raw[kAhead ? (q0 + u < CPL ? q0 + u : 0) : u]);
+                store(q0);
+                if constexpr (G < CPL) __builtin_amdgcn_sched_barrier(0);
             }
             rs = group_sum<LPR>(rs);
             if (sub == 0 && vrow) {
@@ -887,9 +964,11 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
             for (int q = 0; q < WAVES; ++q) t += wst[q][tid];
             put_agent(slots + blk * 5 + tid, tag_value(t, 1));
         }
-        if (with_loads) {
-            __syncthreads();  // the fold buffer is still read
-            publish(acl, k1 + 1);
+        if constexpr (kLoads) {
+            if (with_loads) {
+                __syncthreads();  // the fold buffer is still read
+                publish(acl, k1 + 1);
+            }
         }
         for (int o = blk, oi = 0; ok && o * kColBlock < J; o += nb, ++oi) {
             __syncthreads();
@@ -992,8 +1071,24 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
         // first partials)
         cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (cs.input_bad) cs.done = cs.stop = 1;
+        if (A.batch) {
+            // done, or further FP64 sweeps until an iterate meets tol; at the
+            // launch's cap further sweeps of the phase
+            const bool fin = cs.done || cs.chk_violation < cs.tol || cs.iter >= cs.max_iter ||
+                             !isfinite(cs.chk_violation);
+            cs.phase = fin ? kPhDone : k - k0 >= A.cap ? kPhFast : kPhExact;
+            cs.done = fin ? 1 : 0;
+            cs.stop = 0;
+            cs.result_iter = cs.check_iter = cs.iter;
+        }
         *ctl = cs;
     }
+}
+
+template <class Src, int CPL, int LPR, int WAVES, bool GM>
+__global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
+    __shared__ PersistShared ps;
+    persist_run<Src, CPL, LPR, WAVES, GM>(A, src, (int)gridDim.x, (int)blockIdx.x, ps);
 }
 
 // Prepares the exchange block and clears the stop flag before a persistent
