@@ -24,8 +24,8 @@ FLAGS = [
 
 def sources():
     return [os.path.join(CSRC, f) for f in ("ot_assoc.hip", "launch_dense.hip", "launch_rates.hip", "launch_geo.hip",
-                                            "coop_dense.hip", "coop_rates.hip", "coop_geo.hip", "batch.hip", "team.hip",
-                                            "snapshots.hip")]
+                                            "coop_dense.hip", "coop_dense64.hip", "coop_rates.hip", "coop_geo.hip",
+                                            "batch.hip", "team.hip", "snapshots.hip")]
 
 
 def _compile(src: str, obj: str, inc: str):

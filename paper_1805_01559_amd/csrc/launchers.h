@@ -324,6 +324,28 @@ const void* persist_kernel(int lpr, int cpl, bool gm) {
     return nullptr;
 }
 
+// The cooperative phase in FP64, for dense costs (and what is held as one): up
+// to 1024 columns, whose cells a wave has registers for.
+template <class Src>
+constexpr bool persist64_source() { return Src::kTag <= 2; }
+constexpr int kMaxCoopJ64 = 1024;
+
+template <class Src>
+const void* persist_kernel64(int lpr, int cpl) {
+    constexpr int W = 8;
+    if constexpr (persist64_source<Src>()) {
+        if (lpr == 64) return (const void*)k_persist<Src, 16, 64, W, false, true>;
+        switch (cpl) {
+            case 2: return (const void*)k_persist<Src, 2, 32, W, false, true>;
+            case 4: return (const void*)k_persist<Src, 4, 32, W, false, true>;
+            case 8: return (const void*)k_persist<Src, 8, 32, W, false, true>;
+            case 13: return (const void*)k_persist<Src, 13, 32, W, false, true>;
+            default: return (const void*)k_persist<Src, 16, 32, W, false, true>;
+        }
+    }
+    return nullptr;
+}
+
 }  // namespace otk_launch
 
 // Explicit instantiation (EXT empty) or its declaration (EXT = extern) of
@@ -344,3 +366,4 @@ const void* persist_kernel(int lpr, int cpl, bool gm) {
 
 // The cooperative kernels of cost source S (coop_*.hip).
 #define OT_COOP(EXT, S) EXT template const void* otk_launch::persist_kernel<S>(int, int, bool);
+#define OT_COOP64(EXT, S) EXT template const void* otk_launch::persist_kernel64<S>(int, int);

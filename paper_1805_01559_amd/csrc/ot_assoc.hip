@@ -50,6 +50,8 @@ OT_COOP(extern, RatesSrc<float>)
 OT_COOP(extern, RatesSrc<double>)
 OT_COOP(extern, GeoSrc)
 OT_COOP(extern, EuclidSrc)
+OT_COOP64(extern, DenseSrc<float>)
+OT_COOP64(extern, DenseSrc<double>)
 
 using otk_launch::kMaxNb;
 
@@ -655,15 +657,21 @@ struct Solver {
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 
 constexpr int64_t kSoloSteps = 8;
+// Smallest tol of the cooperative phase in FP64.
+constexpr double kMinCoopTol64 = 1e-13;
 
 struct PersistPlan {
     int lpr = 0, cpl = 0, ncl = 0, rpw = 0, nb = 0, Jp = 0, waves = 8;
     size_t lds = 0;
     bool gm = false;  // the streamed form: the stored kernel in device memory
+    bool f64 = false;
 };
 
 template <class Src>
-bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
+bool persist_plan(ot_assoc* h, int64_t I, int J, bool f64, PersistPlan& p) {
+    p.f64 = f64;
+    if (f64 && (!persist64_source<Src>() || J > kMaxCoopJ64)) return false;
+    const int elem = f64 ? 8 : 4;
     if (!persist_source<Src>() || h->num_cu < 1 || h->lds_max < 1 || I < 1 || !h->xch) return false;
     // cells per lane: the smallest instantiated width that covers the row
     if (J <= 512) {
@@ -686,17 +694,17 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, PersistPlan& p) {
     // 0.1 us per iteration, the two hops of the exchange that it saves 2 us
     const int64_t solo = (I + slots - 1) / slots;
     if (solo <= kSoloSteps && persist_lds_bytes((int)(solo * slots), J, p.Jp, p.waves, p.cpl * p.lpr,
-                                                (p.cpl - p.ncl) * p.lpr, 1) + 2048 <= (size_t)h->lds_max)
+                                                (p.cpl - p.ncl) * p.lpr, 1, elem) + 2048 <= (size_t)h->lds_max)
         steps = solo;
     p.rpw = (int)(steps * slots);
     p.nb = (int)((I + p.rpw - 1) / p.rpw);
-    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, p.cpl * p.lpr, (p.cpl - p.ncl) * p.lpr, p.nb);
+    p.lds = persist_lds_bytes(p.rpw, J, p.Jp, p.waves, p.cpl * p.lpr, (p.cpl - p.ncl) * p.lpr, p.nb, elem);
     // (a little LDS stays for the kernel's static arrays)
     if (p.nb > h->num_cu || p.nb > kMaxCoopGroups) return false;
     if (p.lds + 2048 <= (size_t)h->lds_max) return true;
     // too large for LDS: the kernel in device memory, 16 bytes per lane (up to
     // 128, 256 and 512 columns for 32 lanes, 1024 and 2048 for 64)
-    if (!stream_source<Src>()) return false;
+    if (!stream_source<Src>() || f64) return false;
     p.gm = true;
     p.cpl = J <= 128 ? 4 : J <= 256 ? 8 : J <= 1024 ? 16 : 32;
     p.Jp = (J + 3) & ~3;
@@ -711,7 +719,7 @@ template <class Src>
 ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const PersistPlan& p, double stall_below,
                       bool& launched) {
     launched = false;
-    const void* kern = persist_kernel<Src>(p.lpr, p.cpl, p.gm);
+    const void* kern = p.f64 ? persist_kernel64<Src>(p.lpr, p.cpl) : persist_kernel<Src>(p.lpr, p.cpl, p.gm);
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) != hipSuccess) {
         (void)hipGetLastError();
         return OT_OK;
@@ -827,17 +835,26 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     bool checked = false;
     PersistPlan pp;
     bool persisted = false;
-    if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && (Src::kTag != 2 || h->mat_held) &&
-        persist_plan<Src>(h, I, J, pp))
+    const bool f64 = h->opt.precision == OT_PREC_FP64;
+    // an FP64 solve first looks whether a warm start is within tol already, and
+    // stays with the sweeps for a tol that the tags of the exchanged sums
+    // (2^-51 of a value) could keep it from
+    const bool coop = h->opt.persistent && (f64 ? tol >= kMinCoopTol64 : Src::kTag != 2 || h->mat_held) &&
+                      persist_plan<Src>(h, I, J, f64, pp);
+    if (coop && f64 && c.has_prev) {
+        if ((st = validate_matrix(h)) || (st = S.run_check<Src>(src, c.iter, c))) return st;
+        checked = true;
+    }
+    if (coop && !(checked && (c.done || c.chk_violation < tol || c.iter >= max_iter)))
         if ((st = run_persist<Src>(h, src, I, J, pp, stall_below, persisted))) return st;
-    h->last_persistent = persisted && !pp.gm;
+    h->last_persistent = persisted && !pp.gm && !f64;
     if (persisted) {  // the launch has checked its iterate (one host wait)
         h->validate_pending = false;
         if ((st = S.snapshot(0)) || (st = S.wait(0))) return st;
         c = h->ctl_h[0];
         checked = true;
         h->last_fast_iters = c.iter;  // (the solve starts at iteration 0)
-    } else if ((st = validate_matrix(h))) {
+    } else if (!checked && (st = validate_matrix(h))) {
         return st;
     } else if (h->opt.precision == OT_PREC_FP32) {
         hipLaunchKernelGGL(k_log_a, dim3((unsigned)std::min<int64_t>(1024, (I + 255) / 256)), dim3(256), 0, h->stream,
@@ -1173,7 +1190,7 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
     unsigned init_groups = 1;
     h->xch_zeroed = false;
     h->stop_recorded = false;
-    if (h->opt.precision == OT_PREC_FP32 && h->opt.persistent && h->xch && h->num_cu > 0) {
+    if (h->opt.persistent && h->xch && h->num_cu > 0) {
         ia.xch = h->xch;
         ia.nx = (int64_t)persist_exchange_doubles(std::min(h->num_cu, kMaxCoopGroups), (int)J);
         init_groups = 1 + (unsigned)std::min<int64_t>(32, (ia.nx + 4095) / 4096);

@@ -204,11 +204,13 @@ __host__ __device__ inline int persist_owned_blocks(int nb, int J) {
 // (G, v), the row vectors (a, m, R, S), b and the reference column sums of
 // the owned columns, x and the fold buffer of the column partials (FP32 partials of all waves at
 // once up to 512 columns, of half of them for wider rows), both of width
-// CPL LPR, so that a lane handles all its cells alike.
-__host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int waves, int width, int slack, int nb) {
+// CPL LPR, so that a lane handles all its cells alike. An FP64 kernel (elem 8)
+// has the tile and x in FP64 and keeps the v of the iterate before.
+__host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int waves, int width, int slack, int nb,
+                                                   int elem = 4) {
     const size_t Jr2 = (size_t)((J + 1) & ~1);
-    return ((size_t)rpw * Jp + (size_t)slack) * 4 + 2 * Jr2 * 8 + 4 * (size_t)rpw * 8 +
-           2 * (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + (size_t)width * 4 +
+    return ((size_t)rpw * Jp + (size_t)slack) * elem + (elem == 8 ? 3 : 2) * Jr2 * 8 + 4 * (size_t)rpw * 8 +
+           2 * (size_t)kColBlock * persist_owned_blocks(nb, J) * 8 + (size_t)width * elem +
            (size_t)(J > 512 ? waves / 2 : waves) * width * 4;
 }
 
@@ -217,7 +219,8 @@ __host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int 
 // delta sums.
 enum : int { kItRef = 0, kItPlain = 1, kItRefDelta = 2, kItDelta = 3 };
 // Decision codes: bit 0 stop, bit 1 take a reference for delta sums next.
-constexpr int kDecStop = 1, kDecRefDelta = 2;
+// (in FP64: the iterate before is the returned one)
+constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2;
 // Delta sums begin once the residual is below this: the scalings
 // then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
 // residuals down to about 1e-12, far below the FP32 noise (4e-8) of the plain
@@ -295,14 +298,23 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
 //
 // One workgroup's part of the phase: workgroup blk of the nb that solve the
 // instance together.
-template <class Src, int CPL, int LPR, int WAVES, bool GM, bool LEAN = false>
+//
+// F64: the phase of a solve in FP64. The kernel, v and every product are FP64, the
+// references take FP64 exponentials, and the stop rule is that of the
+// FP64 sweeps: the iterate before the one just computed is returned once its
+// residual is below tol. Bound by the exchange, too: a solve of 2999 x 197 with
+// 72 iterations takes 324 us, with a sweep and a fold launch per iteration
+// (7.2 + 4.3 us) it took 969.
+template <class Src, int CPL, int LPR, int WAVES, bool GM, bool LEAN = false, bool F64 = false>
 __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src, const int nb, const int blk,
                                             PersistShared& ps) {
     extern __shared__ __align__(16) float4 sm4[];  // (its 16-byte reads have to be aligned)
     double* sm = reinterpret_cast<double*>(sm4);
     constexpr int R = kWave / LPR;
     constexpr int T = WAVES * kWave;
-    constexpr int U = CPL <= 4 ? 8 : CPL <= 16 ? (LEAN && CPL > 8 ? 4 : 5) : 1;  // row steps at a time (their sums' chains overlap)
+    using Real = std::conditional_t<F64, double, float>;
+    static_assert(!F64 || (!GM && !LEAN), "the FP64 kernel is held in LDS, by a solve of its own");
+    constexpr int U = F64 ? (CPL <= 4 ? 5 : CPL <= 8 ? 3 : 2) : CPL <= 4 ? 8 : CPL <= 16 ? (LEAN && CPL > 8 ? 4 : 5) : 1;  // row steps at a time (their sums' chains overlap)
     static_assert(WAVES >= 4 && WAVES <= 8, "at least one wave per publishing column block, wres and ored sized for 8");
     int J = A.J, Jp = A.Jp, ncl = A.ncl;
     const int rpw = A.rpw;
@@ -315,7 +327,8 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     constexpr int WD = CPL * LPR;  // width of x and of the fold buffer
     const int Jr2 = (J + 1) & ~1;
     const int slack = GM ? 0 : (CPL - ncl) * LPR;  // (a multiple of 32 floats: what follows stays 8-byte aligned)
-    float* tile = GM ? A.tile + r0 * Jp : reinterpret_cast<float*>(sm);
+    Real* tile = reinterpret_cast<Real*>(sm);
+    if constexpr (GM) tile = A.tile + r0 * Jp;
     double* gl = GM ? sm : reinterpret_cast<double*>(tile + (size_t)rpw * Jp + slack);  // G_j of the reference
     double* vl = gl + Jr2;    // v_j = exp((g_j - G_j) / eps)
     double* al = vl + Jr2;    // a_i
@@ -325,8 +338,9 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     const int nown = persist_owned_blocks(nb, J);
     double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block)
     double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the reference (delta sums)
-    float* xl = reinterpret_cast<float*>(cl + (size_t)kColBlock * nown);  // v_j, or v_j - 1 for delta sums, in FP32
-    float* red = xl + WD;
+    double* vp = cl + (size_t)kColBlock * nown;  // FP64: v_j of the iterate before
+    Real* xl = reinterpret_cast<Real*>(vp + (F64 ? Jr2 : 0));  // v_j, or v_j - 1 for delta sums
+    float* red = reinterpret_cast<float*>(xl + WD);
     Ctl& cs = ps.cs;
     auto& e2tab = ps.e2tab;
     auto& wres = ps.wres;
@@ -365,13 +379,13 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         bl[e] = j < J ? A.b[j] : 1.0;
         cl[e] = 0.0;
     }
-    for (int e = tid; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0.0f;
+    for (int e = tid; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0;
     // column of cell q of this lane: as the references are taken, and as the
     // iterations read the tile
     auto col_ref = [&](int q) { return q * LPR + sub; };
-    constexpr int NV = CPL / 4;  // 16-byte loads of a lane and row step
+    constexpr int NV = F64 ? 0 : CPL / 4;  // 16-byte loads of a lane and row step
     auto col_it = [&](int q) { return q < 4 * NV ? ((q / 4) * LPR + sub) * 4 + q % 4 : q * LPR + sub; };
-    for (int j = tid; j < WD; j += T) xl[j] = 0.0f;
+    for (int j = tid; j < WD; j += T) xl[j] = 0;
     if (tid < 2) s_flag[tid] = 0;
     // the decision workgroup (the last one: with fewer column blocks than
     // workgroups it owns none) sums the residuals and takes the stop decision
@@ -403,6 +417,10 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         for (int lr = tid; lr < nrows; lr += T)
             Rl[lr] = k == k0 + 1 ? (has_prev ? (log(al[lr]) - ((k0 & 1) ? A.f[1] : A.f[0])[r0 + lr] * inv_eps) * kLog2e : 0.0)
                                  : ml[lr] + log2(Sl[lr]);
+        if constexpr (F64) {  // (kept in case iterate k - 1 is the returned one)
+            double* fo = ((k - 1) & 1) ? A.f[1] : A.f[0];
+            for (int lr = tid; lr < nrows && k > k0 + 1; lr += T) fo[r0 + lr] = eps * (log(al[lr]) - kLn2 * Rl[lr]);
+        }
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < CPL; ++q) ac[q] = 0;
@@ -456,7 +474,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 }
             }
             const double m = fmax((double)group_max<LPR>(mx), -1e300);
-            if (kind == kItRefDelta) {
+            if (F64 || kind == kItRefDelta) {
 #pragma unroll
                 for (int q = 0; q < CPL; ++q) {
                     t[q] = exp2_tab_neg(t[q] - m, e2tab);
@@ -475,11 +493,11 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             }
             const double S = group_sum<LPR>(s + s2);
             const double wq = vrow ? al[lr] / S : 0.0;
-            float* trow = tile + (size_t)lr * Jp + sub;
+            Real* trow = tile + (size_t)lr * Jp + sub;
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
                 ac[q] = fma(t[q], wq, ac[q]);
-                if (GM ? (vrow && q * LPR + sub < Jp) : q < ncl) trow[q * LPR] = (float)t[q];
+                if (GM ? (vrow && q * LPR + sub < Jp) : q < ncl) trow[q * LPR] = (Real)t[q];
             }
             if (sub == 0 && vrow) {
                 ml[lr] = m;
@@ -503,23 +521,23 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     // reference's FP64 sums S_i = R_i + sum_j E_ij (v_j - 1), whose FP32 rounding scales
     // with |v - 1|; the column partials sum_i E_ij a_i / S_i, or their change
     // against the reference, sum_i E_ij (a_i / S_i - a_i / R_i).
-    auto rows = [&](auto delta, float (&acc)[CPL]) {
+    auto rows = [&](auto delta, Real (&acc)[CPL]) {
         constexpr bool D = decltype(delta)::value;
-        float x[CPL];
+        Real x[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) x[q] = xl[col_it(q)];  // (0 past J)
         res = 0.0;
-        auto row_sum = [&](const float (&ev)[CPL]) {
-            float s0 = 0.0f, s1 = 0.0f;
+        auto row_sum = [&](const Real (&ev)[CPL]) {
+            Real s0 = 0, s1 = 0;
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
-                if (q & 1) s1 = fmaf(ev[q], x[q], s1);
-                else s0 = fmaf(ev[q], x[q], s0);
+                if (q & 1) s1 = fma(ev[q], x[q], s1);
+                else s0 = fma(ev[q], x[q], s0);
             }
             return s0 + s1;
         };
         // the cells of one row step of this lane: 16 bytes at a time, then word by word
-        auto load_row = [&](const float* trow, float (&ev)[CPL], bool whole) {
+        auto load_row = [&](const Real* trow, Real (&ev)[CPL], bool whole) {
 #pragma unroll
             for (int c = 0; c < NV; ++c) {
                 float4 y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -535,6 +553,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         auto finish = [&](int st, const auto& ev) {
             constexpr int N = std::extent<std::remove_reference_t<decltype(ev)>>::value;
             double d[N], Sn[N];
+            [[maybe_unused]] double Sp[N];
 #pragma unroll
             for (int u = 0; u < N; ++u) d[u] = (double)row_sum(ev[u]);
             group_sums<LPR>(d);
@@ -543,16 +562,26 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 const int lr = ((st + u) * WAVES + w) * R + rg;
                 const double ai = al[lr], Rr = D ? Rl[lr] : 0.0, So = Sl[lr];
                 const double S = D ? Rr + d[u] : (lr < nrows ? d[u] : 1.0);
-                float wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
-                if constexpr (D) wq *= -(float)d[u] * __builtin_amdgcn_rcpf((float)Rr);
+                Real wq;
+                if constexpr (F64) {
+                    wq = ai / S;
+                    res += ai * (fabs(S - So) / So);
+                    Sp[u] = So;
+                } else {
+                    wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+                    if constexpr (D) wq *= -(float)d[u] * __builtin_amdgcn_rcpf((float)Rr);
+                    res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
+                }
 #pragma unroll
-                for (int q = 0; q < CPL; ++q) acc[q] = fmaf(ev[u][q], wq, acc[q]);
-                res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
+                for (int q = 0; q < CPL; ++q) acc[q] = fma(ev[u][q], wq, acc[q]);
                 Sn[u] = S;
             }
             if (sub == 0) {
 #pragma unroll
-                for (int u = 0; u < N; ++u) Sl[((st + u) * WAVES + w) * R + rg] = Sn[u];
+                for (int u = 0; u < N; ++u) {
+                    Sl[((st + u) * WAVES + w) * R + rg] = Sn[u];
+                    if constexpr (F64) Rl[((st + u) * WAVES + w) * R + rg] = Sp[u];  // (of iterate k - 1)
+                }
             }
         };
         if constexpr (GM) {
@@ -576,7 +605,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         } else {
             auto step = [&](int st, auto nu) {
                 constexpr int N = decltype(nu)::value;
-                float ev[N][CPL];
+                Real ev[N][CPL];
 #pragma unroll
                 for (int u = 0; u < N; ++u)
                     load_row(tile + (size_t)(((st + u) * WAVES + w) * R + rg) * Jp, ev[u], true);
@@ -687,6 +716,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
 
     __syncthreads();
     bool ok = true, bad = false;
+    [[maybe_unused]] bool prev = false;  // FP64: iterate k - 1 is the returned one
     for (;;) {
         ++k;
         const int P = k & 1;
@@ -700,8 +730,9 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         // sums), with the flags that choose the next iteration's kind
         int flag = 0;
         auto take_v = [&](int j, double v) {
+            if constexpr (F64) vp[j] = vl[j];
             vl[j] = v;
-            xl[j] = (float)(fine ? v - 1.0 : v);
+            xl[j] = (Real)(fine ? v - 1.0 : v);
             if (!(v > 0.0) || !isfinite(v)) flag |= 2;
             if (fine ? !(fabs(v - 1.0) <= kDeltaMax) : !(v >= 1.0 / kScaleMax && v <= kScaleMax)) flag |= 4;
         };
@@ -726,11 +757,15 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             take_reference(ac);
             fold(ac, col_ref, out);
         } else {
-            float ac[CPL];
+            Real ac[CPL];
 #pragma unroll
-            for (int q = 0; q < CPL; ++q) ac[q] = 0.0f;
-            if (kind == kItDelta) rows(std::true_type{}, ac);
-            else rows(std::false_type{}, ac);
+            for (int q = 0; q < CPL; ++q) ac[q] = 0;
+            if constexpr (F64) {
+                rows(std::false_type{}, ac);
+            } else {
+                if (kind == kItDelta) rows(std::true_type{}, ac);
+                else rows(std::false_type{}, ac);
+            }
             fold(ac, col_it, out);
         }
         if (tid == T - 1 && nb > 1) {
@@ -755,7 +790,15 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 for (int u = 0; u < 4; ++u) r += x[u];
                 r = wave_sum(r);
                 int code = 0;
-                if (lane == 0) code = bookkeep_coop(&cs, r, kind, A.stall_below, A.batch != 0, r_ref, k_ref);
+                if constexpr (F64) {
+                    if (lane == 0) {
+                        bookkeep(&cs, r, kModeExact, 0.0);
+                        code = cs.stop | cs.done ? kDecStop : 0;
+                        if (cs.done && !cs.numeric_bad) code |= kDecPrev;
+                    }
+                } else if (lane == 0) {
+                    code = bookkeep_coop(&cs, r, kind, A.stall_below, A.batch != 0, r_ref, k_ref);
+                }
                 if (lane == 0 && k - k0 >= A.cap) code = kDecStop;
                 code = __shfl(code, 0, kWave);
                 if (nb == 1) {
@@ -827,9 +870,11 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         has_prev = 1;
         if ((code & kDecStop) || (fl & 2)) {
             bad = (fl & 2) != 0;
+            prev = F64 && !bad && (code & kDecPrev);
             break;
         }
-        if (fine) kind = ((code & kDecRefDelta) || (fl & 4)) ? kItRefDelta : kItDelta;
+        if constexpr (F64) kind = (fl & 4) ? kItRef : kItPlain;
+        else if (fine) kind = ((code & kDecRefDelta) || (fl & 4)) ? kItRefDelta : kItDelta;
         else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
@@ -846,15 +891,18 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(sub), "+v"(rg), "+s"(J), "+s"(Jp), "+s"(ncl));
         double* stage = reinterpret_cast<double*>(red);
         src.stage(stage, J);
-        double* fo = (k & 1) ? A.f[1] : A.f[0];
+        const int kr = F64 && prev ? k - 1 : k;  // the returned iterate
+        double* fo = (kr & 1) ? A.f[1] : A.f[0];
         for (int lr = tid; lr < nrows; lr += T) {
-            const double fi = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(Sl[lr])));
+            double fi;
+            if (F64 && prev && kind == kItRef) fi = fo[r0 + lr];  // (kept when the reference was taken)
+            else fi = eps * (log(al[lr]) - kLn2 * (ml[lr] + log2(F64 && prev ? Rl[lr] : Sl[lr])));
             ml[lr] = fi;
             fo[r0 + lr] = fi;
         }
-        double* go = (k & 1) ? A.g[1] : A.g[0];
+        double* go = (kr & 1) ? A.g[1] : A.g[0];
         for (int j = tid; j < J; j += T) {
-            gl[j] += eps * log(vl[j]);
+            gl[j] += eps * log(F64 && prev ? vp[j] : vl[j]);
             if (blk == 0) go[j] = gl[j];
         }
         __syncthreads();
@@ -1067,6 +1115,10 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             cs.stop = 1;
             cs.result_iter = cs.iter;
         }
+        if (F64 && prev && ok) {
+            cs.iter = k - 1;
+            cs.done = 0;
+        }
         // (every workgroup's verdict on its rows of the matrix preceded its
         // first partials)
         cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1085,10 +1137,10 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     }
 }
 
-template <class Src, int CPL, int LPR, int WAVES, bool GM>
+template <class Src, int CPL, int LPR, int WAVES, bool GM, bool F64 = false>
 __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src src) {
     __shared__ PersistShared ps;
-    persist_run<Src, CPL, LPR, WAVES, GM>(A, src, (int)gridDim.x, (int)blockIdx.x, ps);
+    persist_run<Src, CPL, LPR, WAVES, GM, false, F64>(A, src, (int)gridDim.x, (int)blockIdx.x, ps);
 }
 
 // Prepares the exchange block and clears the stop flag before a persistent
