@@ -561,59 +561,199 @@ __global__ void k_snap_all_potentials(SnapArgs S, const double* fbar, const doub
         G[(int64_t)s * S.J + j] = gbar[j] + eps * log((double)S.V[(int64_t)s * S.Jp + j]);
 }
 
-// Exact FP64 check of every snapshot in one launch: workgroup (chunk, s)
-// takes rows [chunk rpc, (chunk + 1) rpc) of snapshot s and writes its column
-// partials and five row statistics (check_rows).
-template <int NCH>
-__global__ __launch_bounds__(512) void k_snap_check(const float* C, int64_t ldc, int64_t I, int J, int64_t rpc,
-                                                    const double* A, const double* F, const double* G, double kk,
-                                                    double* col_part, double* stat_part) {
-    const int s = blockIdx.y, chunk = blockIdx.x, nchunk = gridDim.x;
-    CheckJob cj;
-    cj.r0 = (int64_t)chunk * rpc;
-    cj.r1 = min(I, cj.r0 + rpc);
-    cj.J = J;
-    cj.nch = (J + 63) / 64;
-    cj.kk = kk;
-    cj.a = A + (int64_t)s * I;
-    cj.f = F + (int64_t)s * I;
-    cj.g = G + (int64_t)s * J;
-    cj.col_out = col_part + ((int64_t)s * nchunk + chunk) * J;
-    cj.stat_out = stat_part + ((int64_t)s * nchunk + chunk) * 5;
-    check_rows<DenseSrc<float>, 1, NCH, 8>(cj, DenseSrc<float>{C, ldc});
+// ------------------------------------------------------------ exact check --
+// FP64 check of every snapshot's plan pi_ij = exp((f_i + g_j - C_ij) / eps). The
+// potentials are those of the reference plus eps ln u_i and eps ln v_j, so
+// pi_ij = Kbar_ij u_i v_j with ONE FP64 kernel Kbar for all snapshots: an exponential per
+// cell of the cost instead of one per cell and snapshot, and the sums of all
+// snapshots as FP64 matrix products (Kbar V and (C Kbar) V for the rows, Kbar^T U
+// for the columns). 20000 x 400, 64 snapshots: a check that took the 512 M
+// exponentials ran 870 us; this one takes 91 (rows) + 64 (columns), bound by the FP64
+// matrix rate (3 GFLOP) and the FP64 exponentials of 8 M cells, taken once per pass.
+//
+// Tiles of 16 x 16 cells; one matrix instruction multiplies 16 x 4 by 4 x 16.
+// Which four of the inner indices an instruction takes is free as long as both
+// operands agree: lane group k = lane / 16 holds the indices 4 k + q of a
+// group of 16 in instruction q, so that a lane's U or V values of four
+// instructions are one 16-byte load.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// A lane's four cells (i, j) of the stabilised kernel in FP64, with C Kbar:
+// step moves from one to the next (di, dj); outside the instance both are 0,
+// and so is the product of a cell whose kernel entry is 0 (an infinite cost).
+__device__ __forceinline__ void snap_cells(const float* C, int64_t ldc, int64_t I, int J, int64_t i, int j, int di,
+                                           int dj, const double* fbar, const double* gbar, double kk,
+                                           const double* tab, double (&p)[4], double (&cp)[4]) {
+    double c[4], t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t iq = i + q * di;
+        const int jq = j + q * dj;
+        const bool in = iq < I && jq < J;
+        c[q] = in ? (double)C[iq * ldc + jq] : 0.0;
+        t[q] = in ? fma(fbar[iq], kk, fma(c[q], -kk, gbar[jq] * kk)) : -2000.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        p[q] = exp2_tab(t[q], tab);
+        cp[q] = p[q] > 0.0 ? c[q] * p[q] : 0.0;
+    }
+}
+
+// Rows: a workgroup takes tiles of 16 rows, its four waves every fourth group
+// of 16 columns, all 64 snapshots at once. Per tile and snapshot five sums
+// over the rows go to stat_part[s][workgroup]: |row sum - a|, <C, pi>, the mass,
+// <f, row sums> and <f, a>.
+__global__ __launch_bounds__(256) void k_snap_check_rows(SnapArgs S, const float* C, int64_t ldc, const double* fbar,
+                                                         const double* gbar, const double* F, double kk,
+                                                         double* stat_part) {
+    __shared__ double red[4][2][16][64];
+    __shared__ double tab[64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n = lane & 15, k = lane >> 4;
+    const int s = lane;  // (snapshot of the row sums)
+    exp2_tab_fill(tab);
+    __syncthreads();
+    double st[5] = {0, 0, 0, 0, 0};
+    const int64_t tiles = (S.I + 15) / 16;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        f64x4 r[4], x[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r[t] = x[t] = f64x4{0, 0, 0, 0};
+        for (int j0 = w * 16; j0 < S.J; j0 += 64) {
+            const int j = j0 + 4 * k;
+            double p[4], cp[4];
+            snap_cells(C, ldc, S.I, S.J, tile * 16 + n, j, 0, 1, fbar, gbar, kk, tab, p, cp);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // (Jp is a multiple of 32: the load stays in the row)
+                const float4 v4 = *reinterpret_cast<const float4*>(S.V + (int64_t)(16 * t + n) * S.Jp + j);
+                const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double b = (j + q < S.J && 16 * t + n < S.B) ? (double)v[q] : 0.0;
+                    r[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[q], b, r[t], 0, 0, 0);
+                    x[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(cp[q], b, x[t], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();  // (the previous tile's sums are taken)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {  // (register q of a result: row 4 q + lane / 16, column lane % 16)
+                red[w][0][4 * q + k][16 * t + n] = r[t][q];
+                red[w][1][4 * q + k][16 * t + n] = x[t][q];
+            }
+        __syncthreads();
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = tile * 16 + w * 4 + q;
+            if (i < S.I && s < S.B) {
+                const double u = (double)S.U[(int64_t)s * S.Ip + i], a = S.A[(int64_t)s * S.I + i];
+                const double f = F[(int64_t)s * S.I + i];
+                double y[2];
+                for (int e = 0; e < 2; ++e)
+                    y[e] = u * ((red[0][e][w * 4 + q][s] + red[1][e][w * 4 + q][s]) +
+                                (red[2][e][w * 4 + q][s] + red[3][e][w * 4 + q][s]));
+                st[0] += fabs(y[0] - a);
+                st[1] += y[1];
+                st[2] += y[0];
+                st[3] += f * y[0];
+                st[4] += f * a;
+            }
+        }
+    }
+    __syncthreads();
+    double* rs = &red[0][0][0][0];
+    for (int u = 0; u < 5; ++u) rs[(u * 4 + w) * 64 + s] = st[u];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 5 * S.B; e += 256) {
+        const int u = e % 5, q = e / 5;
+        stat_part[((int64_t)q * gridDim.x + blockIdx.x) * 5 + u] =
+            (rs[(u * 4 + 0) * 64 + q] + rs[(u * 4 + 1) * 64 + q]) + (rs[(u * 4 + 2) * 64 + q] + rs[(u * 4 + 3) * 64 + q]);
+    }
+}
+
+// Columns: workgroup (column tile, row chunk) of 16 columns and rpc rows (a
+// multiple of 64); its waves take every fourth group of 16 rows.
+__global__ __launch_bounds__(256) void k_snap_check_cols(SnapArgs S, const float* C, int64_t ldc, int64_t rpc,
+                                                         const double* fbar, const double* gbar, double kk,
+                                                         double* col_part) {
+    __shared__ double red[4][16][64];
+    __shared__ double tab[64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n = lane & 15, k = lane >> 4;
+    exp2_tab_fill(tab);
+    __syncthreads();
+    const int j0 = blockIdx.x * 16;
+    const int64_t r0 = (int64_t)blockIdx.y * rpc, r1 = min(S.I, r0 + rpc);
+    f64x4 y[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) y[t] = f64x4{0, 0, 0, 0};
+    for (int64_t i0 = r0 + w * 16; i0 < r1; i0 += 64) {
+        const int64_t i = i0 + 4 * k;
+        double p[4], cp[4];
+        snap_cells(C, ldc, S.I, S.J, i, j0 + n, 1, 0, fbar, gbar, kk, tab, p, cp);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // (Ip is a multiple of 32: the load stays in the row)
+            const float4 u4 = *reinterpret_cast<const float4*>(S.U + (int64_t)(16 * t + n) * S.Ip + i);
+            const float u[4] = {u4.x, u4.y, u4.z, u4.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double b = (i + q < S.I && 16 * t + n < S.B) ? (double)u[q] : 0.0;
+                y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[q], b, y[t], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[w][4 * q + k][16 * t + n] = y[t][q];
+    __syncthreads();
+    const int j = threadIdx.x & 15;
+    for (int s = threadIdx.x >> 4; s < S.B; s += 16)
+        if (j0 + j < S.J)
+            col_part[((int64_t)s * gridDim.y + blockIdx.y) * S.J + j0 + j] =
+                (double)S.V[(int64_t)s * S.Jp + j0 + j] *
+                ((red[0][j][s] + red[1][j][s]) + (red[2][j][s] + red[3][j][s]));
 }
 
 // Per snapshot: column sums of the check, the statistics, into out[s * 8]:
 // violation, <C, pi>, reg. objective, dual, mass, row residual, col residual.
-__global__ __launch_bounds__(256) void k_snap_check_finish(int nchunk, int J, const double* b, const double* G,
-                                                           const double* col_part, const double* stat_part,
-                                                           const double* mass, double eps, double* out) {
+// The entropy needs no sum of its own: sum pi ln pi = (<f, row sums> + <g, column
+// sums> - <C, pi>) / eps.
+__global__ __launch_bounds__(256) void k_snap_check_finish(int nchunk, int nstat, int J, const double* b,
+                                                           const double* G, const double* col_part,
+                                                           const double* stat_part, const double* mass, double eps,
+                                                           double* out) {
     const int s = blockIdx.x;
-    __shared__ double red[4][7];
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
+    __shared__ double red[4][8];
+    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int j = threadIdx.x; j < J; j += blockDim.x) {
         double cs = 0.0;
+#pragma unroll 8
         for (int c = 0; c < nchunk; ++c) cs += col_part[((int64_t)s * nchunk + c) * J + j];
+        const double g = G[(int64_t)s * J + j];
         v[5] += fabs(cs - b[j]);
-        v[6] += G[(int64_t)s * J + j] * b[j];
+        v[6] += g * b[j];
+        v[7] += g * cs;
     }
-    for (int c = threadIdx.x; c < nchunk; c += blockDim.x)
-        for (int u = 0; u < 5; ++u) v[u] += stat_part[((int64_t)s * nchunk + c) * 5 + u];
+    for (int c = threadIdx.x; c < nstat; c += blockDim.x)
+        for (int u = 0; u < 5; ++u) v[u] += stat_part[((int64_t)s * nstat + c) * 5 + u];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int u = 0; u < 7; ++u) {
+    for (int u = 0; u < 8; ++u) {
         const double t = wave_sum(v[u]);
         if (lane == 0) red[w][u] = t;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double t[7];
-        for (int u = 0; u < 7; ++u) t[u] = (red[0][u] + red[1][u]) + (red[2][u] + red[3][u]);
+        double t[8];
+        for (int u = 0; u < 8; ++u) t[u] = (red[0][u] + red[1][u]) + (red[2][u] + red[3][u]);
         double* o = out + (int64_t)s * 8;
         o[0] = (t[0] + t[5]) / mass[s];
         o[1] = t[1];
-        o[2] = t[1] + eps * t[2];
-        o[3] = t[4] + t[6] - eps * t[3];
-        o[4] = t[3];
+        o[2] = t[3] + t[7] - eps * t[2];
+        o[3] = t[4] + t[6] - eps * t[2];
+        o[4] = t[2];
         o[5] = t[0];
         o[6] = t[5];
     }

@@ -28,7 +28,8 @@ using namespace otk;
 namespace {
 
 constexpr int kSnapChunk = 8;
-constexpr int kMaxChunks = 64;  // row chunks per snapshot in the exact check
+constexpr int kMaxChunks = 64;      // row chunks of the exact check's column sums
+constexpr int kCheckGroups = 2048;  // workgroups of its row sums
 constexpr int kSnapCUs = 256;   // workgroups that fill the GPU once (one per CU)
 
 template <bool KLO>
@@ -77,7 +78,7 @@ struct SnapState {
     double* F = nullptr;      // kSnapB x I potentials f_s
     double* G = nullptr;      // kSnapB x J potentials g_s
     double* ccol = nullptr;   // check: kSnapB x kMaxChunks x J column partials
-    double* cstat = nullptr;  // check: kSnapB x kMaxChunks x 5 row statistics
+    double* cstat = nullptr;  // check: kSnapB x kCheckGroups x 5 row statistics
     double* cout = nullptr;   // check: kSnapB x 8 results
     int* ctl_h = nullptr;     // pinned mirror of S.ctl
     hipGraphExec_t graph = nullptr;
@@ -181,7 +182,7 @@ ot_status snap_reserve(ot_assoc* h, SnapState* s, int64_t I, int J) {
     add((void**)&s->F, 8 * (size_t)kSnapB * I);
     add((void**)&s->G, 8 * (size_t)kSnapB * J);
     add((void**)&s->ccol, 8 * (size_t)kSnapB * kMaxChunks * J);
-    add((void**)&s->cstat, 8 * (size_t)kSnapB * kMaxChunks * 5);
+    add((void**)&s->cstat, 8 * (size_t)kSnapB * (size_t)std::min<int64_t>(kCheckGroups, (Ip + 15) / 16) * 5);
     add((void**)&s->cout, 8 * (size_t)kSnapB * 8);
     for (auto& p : parts) off += up(p.second, 256);
     SCHK(otk_host::dev_malloc((void**)&s->mem, off));
@@ -377,25 +378,22 @@ ot_status ot_assoc_solve_snapshots(ot_assoc* h, const ot_cost_desc* cost, int B,
     const int iters = s->ctl_h[1] ? s->ctl_h[3] : s->ctl_h[0];
     std::vector<double> resid(kSnapB);
     SCHK(hipMemcpy(resid.data(), S.res, sizeof(double) * kSnapB, hipMemcpyDeviceToHost));
-    // 5. potentials of every snapshot and their exact FP64 check, in three
+    // 5. potentials of every snapshot and their exact FP64 check, in four
     //    launches and one read-back
     const dim3 pg(64, (unsigned)B);
     hipLaunchKernelGGL(k_snap_all_potentials, pg, dim3(256), 0, h->stream, S, (const double*)s->fbar,
                        (const double*)s->gbar, eps, s->F, s->G);
-    const int nchunk = (int)std::min<int64_t>({(int64_t)kMaxChunks, (int64_t)std::max(1, 512 / B), (I + 7) / 8});
-    const int64_t rpc = (I + nchunk - 1) / nchunk;
-    const int nch = (J + 63) / 64;
-    const dim3 cg((unsigned)nchunk, (unsigned)B);
-    if (nch <= 2)
-        hipLaunchKernelGGL(k_snap_check<2>, cg, dim3(512), sizeof(double) * 4 * 2 * 64, h->stream, C, ldc, I, J, rpc,
-                           (const double*)S.A, (const double*)s->F, (const double*)s->G, kk, s->ccol, s->cstat);
-    else if (nch <= 8)
-        hipLaunchKernelGGL(k_snap_check<8>, cg, dim3(512), sizeof(double) * 4 * 8 * 64, h->stream, C, ldc, I, J, rpc,
-                           (const double*)S.A, (const double*)s->F, (const double*)s->G, kk, s->ccol, s->cstat);
-    else
-        hipLaunchKernelGGL(k_snap_check<32>, cg, dim3(512), sizeof(double) * 4 * 32 * 64, h->stream, C, ldc, I, J,
-                           rpc, (const double*)S.A, (const double*)s->F, (const double*)s->G, kk, s->ccol, s->cstat);
-    hipLaunchKernelGGL(k_snap_check_finish, dim3((unsigned)B), dim3(256), 0, h->stream, nchunk, J,
+    // (about two workgroups of the column sums per CU fill the matrix units)
+    const int jt = (J + 15) / 16;
+    const int64_t want = std::min<int64_t>({(int64_t)kMaxChunks, (int64_t)std::max(1, 512 / jt), (I + 63) / 64});
+    const int64_t rpc = (int64_t)up((size_t)((I + want - 1) / want), 64);
+    const int nchunk = (int)((I + rpc - 1) / rpc);
+    const int nstat = (int)std::min<int64_t>(kCheckGroups, (I + 15) / 16);
+    hipLaunchKernelGGL(k_snap_check_rows, dim3((unsigned)nstat), dim3(256), 0, h->stream, S, C, ldc,
+                       (const double*)s->fbar, (const double*)s->gbar, (const double*)s->F, kk, s->cstat);
+    hipLaunchKernelGGL(k_snap_check_cols, dim3((unsigned)jt, (unsigned)nchunk), dim3(256), 0, h->stream, S, C, ldc, rpc,
+                       (const double*)s->fbar, (const double*)s->gbar, kk, s->ccol);
+    hipLaunchKernelGGL(k_snap_check_finish, dim3((unsigned)B), dim3(256), 0, h->stream, nchunk, nstat, J,
                        (const double*)S.b, (const double*)s->G, (const double*)s->ccol, (const double*)s->cstat,
                        (const double*)S.mass, eps, s->cout);
     SCHK(hipGetLastError());
