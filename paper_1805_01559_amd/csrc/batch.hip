@@ -481,9 +481,8 @@ ot_status BatchEngine::upload_cost(Slot& s, const ot_cost_desc* c, char* C_mem, 
             ot_status st = ot_assoc_cost_median(helper, c, &scale);
             if (st) return fail(st, "cost median: %s", ot_assoc_last_error(helper));
         }
-        // a job of the admission's two set-up launches: per-device
-        // interference sums (geometry, into the staging block), then the
-        // padded FP32 matrix; non-finite positions surface as a numeric
+        // a job of the admission's set-up launch: the padded FP32 matrix;
+        // non-finite positions surface as a numeric
         // failure of the solve
         *geo = GeoJob{};
         geo->dst = dst;
@@ -501,12 +500,6 @@ ot_status BatchEngine::upload_cost(Slot& s, const ot_cost_desc* c, char* C_mem, 
         GeoSrc& g = geo->geo;
         g.dev_xy = (const float*)c->geom.dev_xy;
         g.rrh_xy = (const float*)c->geom.rrh_xy;
-        geo->s_all = (double*)stage;
-        geo->s_ex = geo->s_all + I;
-        geo->j1 = (int*)(geo->s_ex + I);
-        g.s_all = geo->s_all;
-        g.s_ex = geo->s_ex;
-        g.j1 = geo->j1;
         g.k = geo_const(c->geom, scale);
         return OT_OK;
     }
@@ -626,12 +619,10 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
             }
             break;
         }
-        // staging for host cost matrices and for the geometry set-up pass;
-        // released once the work reading it is queued (stream order)
+        // staging for host cost matrices; released once the work reading it is queued (stream order)
         const size_t esz = c->dtype == OT_F64 ? 8 : 4;
         size_t stage_b = 0;
         if (!ref && !from_positions(c) && c->mem == OT_MEM_HOST) stage_b = esz * (size_t)(I * lds);
-        if (c->kind == OT_COST_GEOMETRY) stage_b = (2 * sizeof(double) + sizeof(int)) * (size_t)I;
         char* stage = stage_b ? pool.alloc(stage_b) : nullptr;
         char* mem = (stage_b && !stage) ? nullptr : pool.alloc(slot_bytes(I, J, ld, parts_cap, !ref));
         if (!mem) {
@@ -744,16 +735,13 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
         sl.t_admit = now_s();
         sl.adm_seq = seq;
     }
-    // block ranges of the set-up launches
-    int pre_blocks = 0, mat_blocks = 0;
+    // block ranges of the set-up launch
+    int geo_blocks = 0;
     for (int q = 0; q < n_geos; ++q) {
         GeoJob& g = geos_h[q];
-        g.pre_blk0 = pre_blocks;
-        g.pre_nblk = g.kind == 0 ? (int)((g.I + kGeoJobRowsPre - 1) / kGeoJobRowsPre) : 0;
-        g.mat_blk0 = mat_blocks;
-        g.mat_nblk = (int)((g.I + kGeoJobRowsMat - 1) / kGeoJobRowsMat);
-        pre_blocks += g.pre_nblk;
-        mat_blocks += g.mat_nblk;
+        g.blk0 = geo_blocks;
+        g.nblk = (int)((g.I + kGeoJobRows - 1) / kGeoJobRows);
+        geo_blocks += g.nblk;
     }
     if (n_insts) {
         const size_t used = (size_t)(marg_h - blob_h[set]);
@@ -764,10 +752,7 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
                                     n_pads),
                                dim3(256), 0, stream, (const PadJob*)(blob_d[set] + jobs_b));
         const GeoJob* geos_d = (const GeoJob*)(blob_d[set] + jobs_b + pads_b);
-        if (pre_blocks)
-            hipLaunchKernelGGL(k_bgeo_prepass_jobs, dim3(pre_blocks), dim3(256), 0, stream, geos_d, n_geos);
-        if (mat_blocks)
-            hipLaunchKernelGGL(k_bmat_jobs, dim3(mat_blocks), dim3(512), 0, stream, geos_d, n_geos);
+        if (geo_blocks) hipLaunchKernelGGL(k_bgeo_jobs, dim3(geo_blocks), dim3(512), 0, stream, geos_d, n_geos);
         hipLaunchKernelGGL(k_badmit_jobs, dim3(n_insts), dim3(256), 0, stream, (const AdmJob*)blob_d[set], tab, ctl,
                            L[0]);
         if (queue) hipLaunchKernelGGL(k_bcount, dim3(1), dim3(64), 0, stream, L[0], n_items, n_insts);
@@ -791,24 +776,25 @@ struct TeamShape {
     int cls = 0, rpw = 0, nb = 0, ncl = 0;
     size_t lds = 0;
 };
-constexpr int kTeamRows = 16;  // rows of a workgroup's step (8 waves, two rows each)
 
 bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
     t.cls = team_class(J);
-    const int cpl = team_cpl(t.cls), width = cpl * 32;
-    t.ncl = (J + 31) / 32;
-    const int Jp = t.ncl * 32, slack = width - Jp;
+    const int lpr = team_lpr(t.cls), rows = team_rows(t.cls), width = team_cpl(t.cls) * lpr;
+    t.ncl = (J + lpr - 1) / lpr;
+    const int Jp = t.ncl * lpr, slack = width - Jp;
     const int groups = std::min(num_cu, kMaxCoopGroups);
     auto lds_of = [&](int64_t rpw, int nb) { return persist_lds_bytes((int)rpw, J, Jp, 8, width, slack, nb) + 2048; };
-    const size_t fixed = lds_of(0, 1), per_row = (size_t)Jp * 4 + 32;  // (owned columns shrink with nb: bounded by nb = 1)
-    if (lds_max <= 0 || fixed + kTeamRows * per_row > (size_t)lds_max) return false;
-    const int64_t most = (int64_t)(((size_t)lds_max - fixed) / per_row) / kTeamRows * kTeamRows;
-    const int64_t nb = (I + most - 1) / most;
-    if (most < kTeamRows || nb > groups) return false;
-    t.rpw = (int)(((I + nb - 1) / nb + kTeamRows - 1) / kTeamRows * kTeamRows);
-    t.nb = (int)((I + t.rpw - 1) / t.rpw);
-    t.lds = lds_of(t.rpw, t.nb) - 2048;
-    return lds_of(t.rpw, t.nb) <= (size_t)lds_max;
+    // the smallest team that fits (the LDS of the owned columns shrinks as it grows)
+    const size_t fixed = lds_of(0, groups), per_row = (size_t)Jp * 4 + 32;
+    if (lds_max <= 0 || fixed + rows * per_row > (size_t)lds_max) return false;
+    const int64_t most = (int64_t)(((size_t)lds_max - fixed) / per_row) / rows * rows;
+    for (int64_t nb = (I + most - 1) / most; nb <= groups; ++nb) {
+        t.rpw = (int)(((I + nb - 1) / nb + rows - 1) / rows * rows);
+        t.nb = (int)((I + t.rpw - 1) / t.rpw);
+        t.lds = lds_of(t.rpw, t.nb) - 2048;
+        if (lds_of(t.rpw, t.nb) <= (size_t)lds_max) return true;
+    }
+    return false;
 }
 }  // namespace
 
@@ -890,7 +876,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             PersistArgs& A = J.A;
             A.I = sl.I;
             A.J = sl.J;
-            A.Jp = e.t.ncl * 32;
+            A.Jp = e.t.ncl * team_lpr(e.t.cls);
             A.ncl = e.t.ncl;
             A.rpw = e.t.rpw;
             A.max_spin = 1 << 21;

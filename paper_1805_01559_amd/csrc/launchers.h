@@ -309,9 +309,9 @@ const void* persist_kernel(int lpr, int cpl, bool gm) {
     }
     if constexpr (persist_source<Src>()) {
         if (gm) return nullptr;
+        if (lpr == 16) return (const void*)k_persist<Src, 4, 16, W, false>;
         if (lpr == 32) {
             switch (cpl) {
-                case 2: return (const void*)k_persist<Src, 2, 32, W, false>;
                 case 4: return (const void*)k_persist<Src, 4, 32, W, false>;
                 case 8: return (const void*)k_persist<Src, 8, 32, W, false>;
                 case 13: return (const void*)k_persist<Src, 13, 32, W, false>;
@@ -334,9 +334,9 @@ template <class Src>
 const void* persist_kernel64(int lpr, int cpl) {
     constexpr int W = 8;
     if constexpr (persist64_source<Src>()) {
+        if (lpr == 16) return (const void*)k_persist<Src, 4, 16, W, false, true>;
         if (lpr == 64) return (const void*)k_persist<Src, 16, 64, W, false, true>;
         switch (cpl) {
-            case 2: return (const void*)k_persist<Src, 2, 32, W, false, true>;
             case 4: return (const void*)k_persist<Src, 4, 32, W, false, true>;
             case 8: return (const void*)k_persist<Src, 8, 32, W, false, true>;
             case 13: return (const void*)k_persist<Src, 13, 32, W, false, true>;

@@ -674,10 +674,13 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, bool f64, PersistPlan& p) {
     const int elem = f64 ? 8 : 4;
     if (!persist_source<Src>() || h->num_cu < 1 || h->lds_max < 1 || I < 1 || !h->xch) return false;
     // cells per lane: the smallest instantiated width that covers the row
-    if (J <= 512) {
+    if (J <= 64) {
+        p.lpr = 16;
+        p.cpl = 4;
+    } else if (J <= 512) {
         p.lpr = 32;
         const int n = (J + 31) / 32;
-        p.cpl = n <= 2 ? 2 : n <= 4 ? 4 : n <= 8 ? 8 : n <= 13 ? 13 : 16;
+        p.cpl = n <= 4 ? 4 : n <= 8 ? 8 : n <= 13 ? 13 : 16;
     } else if (J <= kMaxJ) {
         p.lpr = 64;
         p.cpl = J <= 1024 ? 16 : 32;
@@ -706,6 +709,7 @@ bool persist_plan(ot_assoc* h, int64_t I, int J, bool f64, PersistPlan& p) {
     // 128, 256 and 512 columns for 32 lanes, 1024 and 2048 for 64)
     if (!stream_source<Src>() || f64) return false;
     p.gm = true;
+    p.lpr = std::max(p.lpr, 32);
     p.cpl = J <= 128 ? 4 : J <= 256 ? 8 : J <= 1024 ? 16 : 32;
     p.Jp = (J + 3) & ~3;
     p.lds = persist_lds_bytes(p.rpw, J, 0, p.waves, p.cpl * p.lpr, 0, p.nb);

@@ -22,11 +22,13 @@
 
 namespace otk {
 
-// Cells per lane (32 lanes per row) by class: up to 128, 256 and 512 columns.
-// More classes (2 and 13 cells for up to 64 and 416 columns) saved less in the
-// row sums, a quarter of an iteration, than they cost in registers.
-__host__ __device__ constexpr int team_class(int J) { return J <= 128 ? 0 : J <= 256 ? 1 : 2; }
-__host__ __device__ constexpr int team_cpl(int cls) { return cls == 0 ? 4 : cls == 1 ? 8 : 16; }
+// Lanes per row and cells per lane by class: up to 64, 128, 256 and 512 columns.
+// One more (13 cells for up to 416 columns) saved less in the row sums, a quarter
+// of an iteration, than it cost in registers.
+__host__ __device__ constexpr int team_class(int J) { return J <= 64 ? 0 : J <= 128 ? 1 : J <= 256 ? 2 : 3; }
+__host__ __device__ constexpr int team_lpr(int cls) { return cls == 0 ? 16 : 32; }
+__host__ __device__ constexpr int team_cpl(int cls) { return cls <= 1 ? 4 : cls == 2 ? 8 : 16; }
+__host__ __device__ constexpr int team_rows(int cls) { return 8 * kWave / team_lpr(cls); }  // of a workgroup's step
 
 struct TeamJob {
     PersistArgs A;
@@ -62,9 +64,10 @@ static __global__ __launch_bounds__(512) void k_team(const TeamJob* __restrict__
         }
         using S = DenseSrc<float>;
         switch (J.cls) {
-            case 0: persist_run<S, team_cpl(0), 32, 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
-            case 1: persist_run<S, team_cpl(1), 32, 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
-            default: persist_run<S, team_cpl(2), 32, 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
+            case 0: persist_run<S, team_cpl(0), team_lpr(0), 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
+            case 1: persist_run<S, team_cpl(1), team_lpr(1), 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
+            case 2: persist_run<S, team_cpl(2), team_lpr(2), 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
+            default: persist_run<S, team_cpl(3), team_lpr(3), 8, false, true>(J.A, J.src, J.nb, it.y, ps); break;
         }
         __syncthreads();  // LDS is the next instance's
     }
