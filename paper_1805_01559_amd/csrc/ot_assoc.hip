@@ -1366,6 +1366,9 @@ ot_status ot_assoc_set_plan_output(ot_assoc* h, void* pi, ot_dtype dtype, int64_
     return OT_OK;
 }
 
+// Largest block of a plan that is staged for the host at once.
+static constexpr size_t kPlanStage = (size_t)64 << 20;
+
 ot_status ot_assoc_plan(ot_assoc* h, void* pi, ot_mem mem, ot_dtype dtype) {
     if (!h) return OT_EINVAL;
     h->err.clear();
@@ -1379,12 +1382,23 @@ ot_status ot_assoc_plan(ot_assoc* h, void* pi, ot_mem mem, ot_dtype dtype) {
     const int64_t I = h->I, J = h->J;
     const size_t esz = dtype == OT_F32 ? 4 : 8;
     // device memory: the whole plan in one launch. Host memory: blocks of
-    // rows through the handle's work region (nothing is allocated).
-    const int64_t block = mem == OT_MEM_DEVICE ? I : std::max<int64_t>(1, (int64_t)(ws_work_bytes(h->I_max, h->J_max) / (esz * (size_t)J)));
+    // rows, as large as the room beyond the fixed buffers takes (up to
+    // kPlanStage; a block costs a launch, a copy and two waits, and through the work
+    // region alone 1000 x 50 took 12 of them, 250 us of the whole call's 590),
+    // else through the handle's work region.
+    const size_t row_b = esz * (size_t)J;
+    void* stage = h->work;
+    size_t stage_b = ws_work_bytes(h->I_max, h->J_max);
+    const size_t want_b = std::min(row_b * (size_t)I, std::max(kPlanStage, row_b));
+    if (mem == OT_MEM_HOST && stage_b < want_b && ensure_ker(h, want_b)) {
+        stage = h->ker;
+        stage_b = want_b;
+    }
+    const int64_t block = mem == OT_MEM_DEVICE ? I : std::max<int64_t>(1, (int64_t)(stage_b / row_b));
     ot_status st = OT_OK;
     for (int64_t r0 = 0; r0 < I && !st; r0 += block) {
         const int64_t r1 = std::min(I, r0 + block);
-        void* dst = mem == OT_MEM_DEVICE ? pi : h->work;
+        void* dst = mem == OT_MEM_DEVICE ? pi : stage;
         st = with_retained(h, [&](const auto& src, const void* data) -> ot_status {
             using S = std::decay_t<decltype(src)>;
             const Shape s = row64(make_shape<S>(h, I, J, vec_for<S>(J, ld_of(h->last), data)), J);
@@ -1397,9 +1411,9 @@ ot_status ot_assoc_plan(ot_assoc* h, void* pi, ot_mem mem, ot_dtype dtype) {
         });
         if (!st && mem == OT_MEM_HOST) {
             const size_t bytes = (size_t)((r1 - r0) * J) * esz;
-            hipError_t e = hipMemcpyAsync((char*)pi + (size_t)(r0 * J) * esz, h->work, bytes, hipMemcpyDeviceToHost,
+            hipError_t e = hipMemcpyAsync((char*)pi + (size_t)(r0 * J) * esz, stage, bytes, hipMemcpyDeviceToHost,
                                           h->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // the work region is reused by the next block
+            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // the staging is reused by the next block
             if (e != hipSuccess) st = fail(h, OT_EDEVICE, "plan copy failed: %s", hipGetErrorString(e));
         }
     }
