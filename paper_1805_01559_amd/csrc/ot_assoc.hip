@@ -1191,16 +1191,19 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
     ia.ctl = c;
     // a solve that may take the cooperative FP32 phase has its exchange
     // block zeroed by this launch (nb <= num_cu bounds the launch's layout)
-    unsigned init_groups = 1;
+    ia.groups = I <= kInitSingle ? 1 : (int)std::min<int64_t>(kInitGroups, (I + 4095) / 4096);
+    ia.part = h->stat_part;  // (written by checks only, behind this launch)
+    unsigned init_groups = (unsigned)ia.groups;
     h->xch_zeroed = false;
     h->stop_recorded = false;
     if (h->opt.persistent && h->xch && h->num_cu > 0) {
         ia.xch = h->xch;
         ia.nx = (int64_t)persist_exchange_doubles(std::min(h->num_cu, kMaxCoopGroups), (int)J);
-        init_groups = 1 + (unsigned)std::min<int64_t>(32, (ia.nx + 4095) / 4096);
+        init_groups += (unsigned)std::min<int64_t>(32, (ia.nx + 4095) / 4096);
         h->xch_zeroed = true;
     }
     hipLaunchKernelGGL(k_solve_init, dim3(init_groups), dim3(1024), 0, h->stream, ia);
+    if (ia.groups > 1) hipLaunchKernelGGL(k_solve_init_fin, dim3(1), dim3(256), 0, h->stream, ia);
     HIPCHK(h, hipGetLastError());
 
     Ctl fin = c;

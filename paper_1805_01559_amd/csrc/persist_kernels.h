@@ -1166,12 +1166,18 @@ static __global__ void k_xch_clear(double* xch, int nb, int J, Ctl* ctl) {
 }
 
 // ------------------------------------------------------------ solve set-up --
-// One workgroup: checks the marginals (positive and finite, equal masses),
-// copies them into the solver's buffers, zeroes g for a cold start and
-// writes the solve constants and the initial control block, so that a solve
-// needs no host round trip before its first sweep. The masses are
-// compensated sums (per-thread Neumaier sums in a fixed strided order, then a
-// fixed pairwise tree of two-sum merges).
+// Checks the marginals (positive and finite, equal masses), copies them into
+// the solver's buffers, zeroes g for a cold start and writes the solve
+// constants and the initial control block, so that a solve needs no host
+// round trip before its first sweep. The masses are compensated sums
+// (per-thread Neumaier sums in a fixed strided order, then two-sum merges in
+// a fixed order across lanes, waves and workgroups). One workgroup does it all
+// for up to kInitSingle devices; above, the devices are split over workgroups
+// whose sums k_solve_init_fin merges: the compensated sums of one CU take
+// 11 us at I = 5000, 17 at 20000 and 76 at 200000, split 17, 19 and 25 (both
+// launches start cold).
+constexpr int64_t kInitSingle = 32768;
+constexpr int kInitGroups = 64;  // workgroups of the device sums at most
 struct InitArgs {
     int64_t I;
     int J;
@@ -1187,6 +1193,8 @@ struct InitArgs {
     Ctl ctl;
     double* xch;  // exchange block zeroed by the workgroups past the first (nx doubles), or nullptr
     int64_t nx;
+    int groups;    // workgroups of the device sums (1: no second launch)
+    double* part;  // 3 per such workgroup: sum, its error, invalid entries
 };
 
 __device__ __forceinline__ void two_sum_add(double& s, double& c, double x) {
@@ -1195,81 +1203,146 @@ __device__ __forceinline__ void two_sum_add(double& s, double& c, double x) {
     s = t;
 }
 
-// Workgroup 0 checks and sums the marginals and writes the constants and
-// the control block. The workgroups past it zero the cooperative exchange
-// block, for a cooperative launch that starts from iteration 0: a zero slot
-// carries tag 0, which neither of the launch's first two iterations (1 and
-// 2, one per buffer parity) waits for, and zero decision and abort words;
-// so the launch needs no clearing pass of its own.
-static __global__ __launch_bounds__(1024) void k_solve_init(InitArgs A) {
-    if (blockIdx.x > 0) {
-        const size_t stride = (size_t)(gridDim.x - 1) * blockDim.x;
-        for (size_t q = (size_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x; q < (size_t)A.nx; q += stride)
-            A.xch[q] = 0.0;
-        return;
+// A lane's compensated sum merged with its partner's, by DPP lane moves within
+// 16 lanes and row swaps beyond (as a tree through LDS with ten
+// barriers: 10.4 us at I = 100, now 8.2).
+template <int CTRL>
+__device__ __forceinline__ void two_sum_dpp(double& s, double& c) {
+    const double s2 = dpp_d<CTRL>(s), c2 = dpp_d<CTRL>(c);
+    two_sum_add(s, c, s2);
+    c += c2;
+}
+__device__ __forceinline__ void two_sum_row16(double& s, double& c) {
+    two_sum_dpp<0xB1>(s, c);
+    two_sum_dpp<0x4E>(s, c);
+    two_sum_dpp<0x141>(s, c);
+    two_sum_dpp<0x140>(s, c);
+}
+// lanes 0, 16, 32, 48 hold their rows' sums; the same in every lane
+__device__ __forceinline__ void two_sum_rows(double& s, double& c) {
+    const double s0 = readlane_d(s, 0), c0 = readlane_d(c, 0);
+    double t = s0, e = c0;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        two_sum_add(t, e, readlane_d(s, 16 * q));
+        e += readlane_d(c, 16 * q);
     }
-    __shared__ double ss[2][1024], sc[2][1024];
+    s = t;
+    c = e;
+}
+
+// Thread 0 of the workgroup gets the merged sum of all its threads (sums of b
+// and flags likewise); ends behind a barrier.
+__device__ __forceinline__ void init_merge(double (&sum)[2], double (&err)[2], int& bad) {
+    __shared__ double ws[2][16], wc[2][16];  // per-wave sums and their errors
     __shared__ int s_bad;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (threadIdx.x == 0) s_bad = 0;
     __syncthreads();
-    double sa = 0.0, ca = 0.0, sb = 0.0, cb = 0.0;
-    int bad = 0;
-    // (eight loads in flight per thread, then their terms in index order)
-    const int64_t n8 = (int64_t)blockDim.x * 8;
-    for (int64_t i0 = threadIdx.x; i0 < A.I; i0 += n8) {
-        double v[8];
+    if (bad) atomicOr(&s_bad, bad);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t i = i0 + (int64_t)u * blockDim.x;
-            v[u] = i < A.I ? A.a_src[i] : 1.0;
-        }
+    for (int u = 0; u < 2; ++u) {
+        two_sum_row16(sum[u], err[u]);
+        two_sum_rows(sum[u], err[u]);
+    }
+    if (lane == 0)
+        for (int u = 0; u < 2; ++u) { ws[u][w] = sum[u]; wc[u][w] = err[u]; }
+    __syncthreads();
+    bad = s_bad;
+    if (w == 0) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t i = i0 + (int64_t)u * blockDim.x;
-            if (i < A.I) {
-                if (!(v[u] > 0.0) || !isfinite(v[u])) bad |= 1;
-                if (A.a != A.a_src) A.a[i] = v[u];
-                two_sum_add(sa, ca, v[u]);
-            }
+        for (int u = 0; u < 2; ++u) {
+            const bool in = lane < (int)(blockDim.x / kWave);
+            sum[u] = in ? ws[u][lane & 15] : 0.0;
+            err[u] = in ? wc[u][lane & 15] : 0.0;
+            two_sum_row16(sum[u], err[u]);
         }
     }
+}
+
+// The RRHs' marginal (one workgroup).
+__device__ __forceinline__ void init_rrhs(const InitArgs& A, double& sum, double& err, int& bad) {
     for (int j = threadIdx.x; j < A.J; j += blockDim.x) {
         const double v = A.b_src[j];
         if (!(v > 0.0) || !isfinite(v)) bad |= 2;
         if (A.b != A.b_src) A.b[j] = v;
-        two_sum_add(sb, cb, v);
+        two_sum_add(sum, err, v);
         if (A.cold) A.g0[j] = 0.0;
     }
-    if (bad) atomicOr(&s_bad, bad);
-    ss[0][threadIdx.x] = sa; sc[0][threadIdx.x] = ca;
-    ss[1][threadIdx.x] = sb; sc[1][threadIdx.x] = cb;
-    __syncthreads();
-    for (int h = blockDim.x / 2; h >= 1; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            for (int u = 0; u < 2; ++u) {
-                double s = ss[u][threadIdx.x], c = sc[u][threadIdx.x] + sc[u][threadIdx.x + h];
-                two_sum_add(s, c, ss[u][threadIdx.x + h]);
-                ss[u][threadIdx.x] = s;
-                sc[u][threadIdx.x] = c;
+}
+
+// Thread 0: the solve constants and the control block.
+__device__ __forceinline__ void init_ctl(const InitArgs& A, double ma, double mb, int flags) {
+    if (fabs(ma - mb) > 1e-12 * ma) flags |= 4;
+    *A.prm_out = A.prm;
+    Ctl c = A.ctl;
+    c.mass = ma;
+    c.mass_b = mb;
+    c.input_bad = flags;
+    if (flags) {
+        c.done = 1;
+        c.stop = 1;
+    }
+    *A.ctl_out = c;
+}
+
+// Workgroups below A.groups sum the devices' marginal. Those past them zero the
+// cooperative exchange block, for a cooperative launch that starts from
+// iteration 0: a zero slot carries tag 0, which neither of the launch's first
+// two iterations (1 and 2, one per buffer parity) waits for, and zero decision
+// and abort words; so the launch needs no clearing pass of its own.
+static __global__ __launch_bounds__(1024) void k_solve_init(InitArgs A) {
+    if ((int)blockIdx.x >= A.groups) {
+        const size_t stride = (size_t)(gridDim.x - A.groups) * blockDim.x;
+        for (size_t q = (size_t)(blockIdx.x - A.groups) * blockDim.x + threadIdx.x; q < (size_t)A.nx; q += stride)
+            A.xch[q] = 0.0;
+        return;
+    }
+    double sum[2] = {0.0, 0.0}, err[2] = {0.0, 0.0};
+    int bad = 0;
+    constexpr int N = 8;  // loads in flight per thread, then their terms in index order
+    const int64_t step = (int64_t)A.groups * blockDim.x;
+    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < A.I; i0 += N * step) {
+        double v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = i0 + u * step < A.I ? A.a_src[i0 + u * step] : 1.0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int64_t i = i0 + u * step;
+            if (i < A.I) {
+                if (!(v[u] > 0.0) || !isfinite(v[u])) bad |= 1;
+                if (A.a != A.a_src) A.a[i] = v[u];
+                two_sum_add(sum[0], err[0], v[u]);
             }
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const double ma = ss[0][0] + sc[0][0], mb = ss[1][0] + sc[1][0];
-        int flags = s_bad;
-        if (fabs(ma - mb) > 1e-12 * ma) flags |= 4;
-        *A.prm_out = A.prm;
-        Ctl c = A.ctl;
-        c.mass = ma;
-        c.mass_b = mb;
-        c.input_bad = flags;
-        if (flags) {
-            c.done = 1;
-            c.stop = 1;
-        }
-        *A.ctl_out = c;
+    if (A.groups == 1) init_rrhs(A, sum[1], err[1], bad);
+    init_merge(sum, err, bad);
+    if (threadIdx.x != 0) return;
+    if (A.groups == 1) {
+        init_ctl(A, sum[0] + err[0], sum[1] + err[1], bad);
+    } else {
+        double* p = A.part + 3 * blockIdx.x;
+        p[0] = sum[0];
+        p[1] = err[0];
+        p[2] = (double)bad;
     }
+}
+
+// The second launch for more than kInitSingle devices: merges the workgroups'
+// sums, sums the RRHs' marginal and writes the control block.
+static __global__ __launch_bounds__(256) void k_solve_init_fin(InitArgs A) {
+    double sum[2] = {0.0, 0.0}, err[2] = {0.0, 0.0};
+    int bad = 0;
+    if ((int)threadIdx.x < A.groups) {
+        const double* p = A.part + 3 * threadIdx.x;
+        sum[0] = p[0];
+        err[0] = p[1];
+        bad = (int)p[2];
+    }
+    init_rrhs(A, sum[1], err[1], bad);
+    init_merge(sum, err, bad);
+    if (threadIdx.x == 0) init_ctl(A, sum[0] + err[0], sum[1] + err[1], bad);
 }
 
 }  // namespace otk
