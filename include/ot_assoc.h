@@ -117,7 +117,8 @@ typedef struct {
     int device;         /* HIP device ordinal */
     void *stream;       /* hipStream_t to issue work on; NULL = a stream owned by the handle */
     ot_precision precision;
-    int polish_iters;   /* FP64 iterations run before the first exact check (default 1) */
+    int polish_iters;   /* chunked FP32 solves: FP64 iterations run before the first exact check
+                           (default 1); the cooperative launch needs none */
     int chunk;          /* iterations per graph launch between host checks (default 8) */
     int use_graphs;     /* capture iteration chunks in HIP graphs (default 1) */
     int sweep_blocks;   /* 0 = choose automatically; else workgroups per sweep */
@@ -131,10 +132,14 @@ typedef struct {
                            the environment variable OT_ASSOC_TUNE_CACHE names a file, read from
                            and appended to it, so a later process takes it without timing (a
                            batch's results are bitwise reproducible for one choice); 0 uses 8, 128 */
-    int persistent;     /* ot_assoc_solve, FP32 precision: 1 (default) runs the FP32 phase as one
-                           cooperative launch that keeps the cost in LDS when the instance fits
-                           (about I * J <= 9.8e6 cells on 256 CUs; dense FP32, FP32 rates or
-                           geometry costs); 0 always uses graph-captured chunks of launches */
+    int persistent;     /* ot_assoc_solve: 1 (default) runs iterations, exact check and plan as one
+                           cooperative launch whose stabilised kernel is held in LDS when it fits
+                           (FP32: about I * J <= 9.8e6 cells on 256 CUs; every cost but FP64
+                           rates; FP64 precision: dense costs of half as many cells, J <= 1024,
+                           tol >= 1e-13), in FP32 above that in device memory when there is room
+                           (half of the free memory, or what a caller's workspace has left).
+                           Batches then run on teams of workgroups in the same way. 0 always
+                           uses graph-captured chunks of launches */
     int check_every;    /* ot_assoc_solve: the stop rule (residual below tol, or the FP32 residual
                            stalled) is evaluated only after iterations k that are multiples of
                            check_every (default 1: after every iteration); max_iter always stops.
@@ -173,7 +178,7 @@ typedef struct {
 } ot_assoc_result;
 
 /* ot_assoc_result.flags: the FP32 phase ran as one cooperative launch with the
-   cost held in LDS (ot_assoc_options.persistent). */
+   kernel held in LDS (ot_assoc_options.persistent; FP32 precision). */
 #define OT_RESULT_PERSISTENT 1
 /* ot_assoc_result.flags of a snapshot (ot_assoc_solve_snapshots): its status
    refers to tol on the BF16 problem, and the exact FP64 check of its
@@ -294,7 +299,7 @@ ot_status ot_assoc_materialize_cost(ot_assoc *h, const ot_cost_desc *cost, float
 
 /* Per-RRH load of the last successful solve's plan: load_j = sum_i C_ij x_ij
  * in FP64 (the FP64 cost, x = exp((f + g - C)/eps)). loads: J doubles in
- * `mem`. After ot_assoc_adaptive (J <= 512) the loads were summed by the
+ * `mem`. After ot_assoc_adaptive (J <= 416, or 512 without the cooperative launch) the loads were summed by the
  * solves' final exact checks and are copied out; otherwise they take one
  * pass over the cost. Errors: OT_ESTATE before a successful solve (or after
  * a call that replaced the handle's cost). */
@@ -385,8 +390,8 @@ ot_status ot_assoc_test_hold_exchange(int32_t iteration);
 
 /* (instrumentation) Device duration, in milliseconds, of the cooperative
  * launch that ran the FP32 phase of the last successful solve (HIP events on
- * the handle's stream right around that one launch: the LDS fill and every
- * FP32 iteration), and the number of FP32 iterations it ran.
+ * the handle's stream right around that one launch: references, every
+ * iteration, the exact check and the plan), and the number of iterations it ran.
  * Errors: OT_ESTATE if the last solve did not use the cooperative launch
  * (see ot_assoc_result.flags). */
 ot_status ot_assoc_fast_phase_time(ot_assoc *h, double *ms, int32_t *iterations);
@@ -411,10 +416,13 @@ const char *ot_assoc_last_error(const ot_assoc *h);
  * each is the problem of eq. (5) with its own cost, marginals and eps, solved
  * by the same Sinkhorn iterations (Sec. III-B) and the same phases as
  * ot_assoc_solve with OT_PREC_FP32 (FP32 sweeps, FP64 polish, exact FP64
- * check, FP64 sweeps if the check misses tol). Instances advance together,
- * three persistent launches per iteration, captured in HIP graphs; an
- * instance leaves the work lists as soon as it is done, so uneven sizes and
- * iteration counts cost only their own work.
+ * check, FP64 sweeps if the check misses tol). With the option persistent
+ * they run as teams: one cooperative launch that solves each instance on as
+ * many workgroups as its kernel needs LDS for. Those that do not fit, or
+ * need more than 1024 iterations, advance together, three persistent launches
+ * per iteration, captured in HIP graphs; an instance leaves the work lists as
+ * soon as it is done, so uneven sizes and iteration counts cost only their
+ * own work.
  *
  * Every cost is held as a padded FP32 row-major matrix: a DENSE FP32 matrix in
  * device memory whose J and row stride (ld, else J) are multiples of 4 and whose

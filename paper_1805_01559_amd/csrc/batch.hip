@@ -273,6 +273,7 @@ struct BatchEngine {
     size_t team_xch_cap = 0;
     Ctl* team_ctl = nullptr;
     ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left);
+    bool team_reserve(size_t bytes, size_t xch);
     ot_status run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished, std::vector<int>& left);
     int widx() const { return waves == 4 ? 0 : 1; }
     int gidx() const { return 2 * widx() + (items_running <= kTailItems ? 1 : 0); }
@@ -819,6 +820,30 @@ ot_status BatchEngine::run_teams(const std::vector<int>& ks, int cap, std::vecto
     return OT_OK;
 }
 
+// Room for a team launch: job and workgroup lists of `bytes`, exchange blocks of
+// `xch` doubles. False when there is none.
+bool BatchEngine::team_reserve(size_t bytes, size_t xch) {
+    bool ok = true;
+    if (team_cap < bytes) {
+        if (team_h) hipHostFree(team_h);
+        if (team_d) hipFree(team_d);
+        team_h = team_d = nullptr;
+        team_cap = 0;
+        ok = hipHostMalloc(&team_h, 2 * bytes) == hipSuccess &&
+             otk_host::dev_malloc((void**)&team_d, 2 * bytes) == hipSuccess;
+        if (ok) team_cap = 2 * bytes;
+    }
+    if (ok && team_xch_cap < xch) {
+        if (team_xch) hipFree(team_xch);
+        team_xch = nullptr;
+        team_xch_cap = 0;
+        ok = otk_host::dev_malloc((void**)&team_xch, sizeof(double) * xch) == hipSuccess;
+        if (ok) team_xch_cap = xch;
+    }
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
 ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished,
                                       std::vector<int>& left) {
     const int groups = std::min(num_cu, kMaxCoopGroups);
@@ -839,27 +864,13 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
         n_items += (size_t)e.t.nb;
         jobs.push_back(e);
     }
+    const size_t jobs_b = align_up(sizeof(TeamJob) * jobs.size()), items_b = align_up(sizeof(int2) * n_items);
+    const size_t need = jobs_b + items_b + align_up(sizeof(int) * (size_t)(groups + 1));
+    // (no memory for the launch: the instances stay as admitted and go to the chunks)
+    if (!jobs.empty() && !team_reserve(need, xch)) jobs.clear();
     if (!jobs.empty()) {
         // the largest teams first (ties in request order)
         std::stable_sort(jobs.begin(), jobs.end(), [](const Entry& a, const Entry& b) { return a.t.nb > b.t.nb; });
-        const size_t jobs_b = align_up(sizeof(TeamJob) * jobs.size()), items_b = align_up(sizeof(int2) * n_items);
-        const size_t need = jobs_b + items_b + align_up(sizeof(int) * (size_t)(groups + 1));
-        if (team_cap < need) {
-            if (team_h) hipHostFree(team_h);
-            if (team_d) hipFree(team_d);
-            team_h = team_d = nullptr;
-            team_cap = 0;
-            ECHK(this, hipHostMalloc(&team_h, 2 * need));
-            ECHK(this, otk_host::dev_malloc((void**)&team_d, 2 * need));
-            team_cap = 2 * need;
-        }
-        if (team_xch_cap < xch) {
-            if (team_xch) hipFree(team_xch);
-            team_xch = nullptr;
-            team_xch_cap = 0;
-            ECHK(this, otk_host::dev_malloc((void**)&team_xch, sizeof(double) * xch));
-            team_xch_cap = xch;
-        }
         TeamJob* jh = (TeamJob*)team_h;
         int2* ih = (int2*)(team_h + jobs_b);
         int* sh = (int*)(team_h + jobs_b + items_b);

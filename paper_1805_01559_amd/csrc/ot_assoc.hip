@@ -1,19 +1,19 @@
 // Host runtime and C ABI of the association solver (include/ot_assoc.h).
 //
-// A solve runs three phases on one HIP stream:
+// A solve runs on one HIP stream, as ONE cooperative launch where it can
+// (persist_kernels.h: iterations on a stabilised kernel in LDS or streamed from
+// device memory, exact FP64 check, plan), else in phases of launches captured
+// in HIP graphs CHUNK iterations at a time, which the combine kernel stops on
+// the device:
 //   fast    FP32-exponential sweeps until the residual meets tol or stalls at
-//           the FP32 noise floor. When the instance's FP32 cost fits in the
-//           LDS of the GPU this is ONE cooperative launch (persist_kernels.h)
-//           that keeps the cost on chip; otherwise the sweeps are captured in
-//           HIP graphs CHUNK iterations at a time, and the combine kernel
-//           stops the chunk on the device;
-//   polish  a few FP64 sweeps, then an exact FP64 check of the iterate;
-//   exact   (only if the check misses tol) FP64 sweeps until an FP64 iterate
-//           meets tol, then the check again.
+//           the FP32 noise floor;
+//   polish  a few FP64 sweeps, then an exact FP64 check of the iterate.
+// If the check misses tol, of either form:
+//   exact   FP64 sweeps until an FP64 iterate meets tol, then the check again.
 // Inputs are checked on the device (the verdict travels in the control
-// block). With the cooperative launch a solve has a single host wait before
-// the exact phase; the chunked form reads the control block once per chunk,
-// one chunk behind the device, so there is no host round trip per iteration.
+// block). The cooperative form has a single host wait; the chunked form reads
+// the control block once per chunk, one chunk behind the device, so there is
+// no host round trip per iteration.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -652,7 +652,7 @@ struct Solver {
 };
 
 // ------------------------------------------------------ cooperative phase --
-// Shape of the LDS-resident FP32 phase: one workgroup of p.waves waves
+// Shape of the cooperative phase: one workgroup of p.waves waves
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 

@@ -1,6 +1,6 @@
-// The FP32 phase of a single solve as ONE cooperative launch, for instances
-// whose FP32 kernel fits in the LDS of the whole GPU (about 40 MB on 256 CUs:
-// 20000 x 400 needs 32 MB). Each workgroup (one per CU) owns a contiguous
+// A solve as ONE cooperative launch, for instances whose kernel fits in the
+// LDS of the whole GPU (about 40 MB on 256 CUs: 20000 x 400 needs 32 MB in FP32)
+// or in device memory (the streamed form below). Each workgroup (one per CU) owns a contiguous
 // block of rows and holds their stabilised Gibbs kernel in LDS: with reference
 // potentials G, E_ij = exp((G_j - C_ij) / eps - m_i) in FP32 (arguments in FP64,
 // from the matrix or regenerated from positions; m_i the row's largest). It
@@ -28,11 +28,11 @@
 //     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
 //     cost were needed before.
 //
-// What bounds it: the exchange. With the exponentials in every iteration the
-// row update alone took 4.8 us of the 9.6 us per iteration at 20000 x 400;
-// the whole solve with its plan went 555 -> 463 us, and the distance cost at
-// that size (over 1200 iterations, 200 of them FP64 sweeps before) 15.7 -> 8.0
-// ms.
+// What bounds it: the exchange. With the cost in LDS and an exponential per cell
+// the row update alone took 4.8 us of the 9.6 us per iteration at 20000 x 400;
+// now an iteration takes 5.8 us, 1.7 of them the row update. The whole solve
+// with its plan went 577 -> 400 us, and the distance cost at that size (about
+// 1250 iterations, 200 of them FP64 sweeps before) 15.7 -> 6.5 ms.
 //
 // Only O(I + J) scalings and O(nb J) partials move per iteration; the I x J cost
 // is read two or three times per launch instead of once per iteration.
