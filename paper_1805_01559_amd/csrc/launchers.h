@@ -283,7 +283,7 @@ bool launch_plan(const Shape& s, int64_t r0, int64_t r1, int J, const double* f,
 }
 
 
-// Shape of the LDS-resident FP32 phase: one workgroup of persist_waves waves
+// Shape of the cooperative phase: one workgroup of persist_waves waves
 // per CU, rows per workgroup a whole number of wave steps; lanes per row and
 // cells per lane by J (column q LPR + sub of a row belongs to lane sub).
 // Dense FP32, FP32 rates, distances, and geometry (as the FP64 matrix of a
