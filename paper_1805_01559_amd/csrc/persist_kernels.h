@@ -508,9 +508,10 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             }
         }
         // (the verdict is final once the value comes back, before this workgroup
-        // publishes anything)
-        if (A.validate && k == k0 + 1 && __any(bad_cost) && lane == 0)
-            bad_before = __hip_atomic_fetch_or(&ctl->input_bad, 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // publishes anything; in a batch a bad cost is a numeric failure)
+        if ((A.validate || A.batch) && k == k0 + 1 && __any(bad_cost) && lane == 0)
+            bad_before = __hip_atomic_fetch_or(A.batch ? &ctl->numeric_bad : &ctl->input_bad, A.batch ? 1 : 8,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();  // (the fold also reuses the staged source data's LDS)
         // |rowsum_i - a_i| of the previous iterate, from the change of the log-sum-exp
         res = 0.0;
@@ -1131,6 +1132,8 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (cs.input_bad) cs.done = cs.stop = 1;
         if (A.batch) {
+            cs.numeric_bad |= __hip_atomic_load(&ctl->numeric_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (cs.numeric_bad) cs.done = 1;
             // done, or further FP64 sweeps until an iterate meets tol; at the
             // launch's cap further sweeps of the phase
             const bool fin = cs.done || cs.chk_violation < cs.tol || cs.iter >= cs.max_iter ||
