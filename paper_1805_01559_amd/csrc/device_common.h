@@ -41,11 +41,12 @@ __device__ __forceinline__ double exp2_tab(double t, const double* tab) {
     const double T = tab[ki & 63];
     return ldexp(fma(T, q, T), ki >> 6);
 }
-// The same for arguments of a stored kernel: t <= 1 (entries shifted by about
-// their row's largest), results below 2^-1000 as 2^-1000 (stored in FP32 they
-// are 0). The scaling is an addition to the exponent.
+// The same for arguments of a stored kernel: about t <= 1 (entries shifted by
+// their row's largest, rounded to FP32), results below 2^-1000 as 2^-1000
+// (stored in FP32 they are 0); a NaN stays one. The scaling is an addition to
+// the exponent.
 __device__ __forceinline__ double exp2_tab_neg(double t, const double* tab) {
-    const double tc = fmax(t, -1000.0);
+    const double tc = t < -1000.0 ? -1000.0 : t;
     const double s = fma(tc, 64.0, kRoundMagic);
     const int ki = (int)__double_as_longlong(s);
     const double x = fma(s - kRoundMagic, -1.0 / 64.0, tc) * kLn2;

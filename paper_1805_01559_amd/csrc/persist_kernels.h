@@ -21,12 +21,18 @@
 // A cell costs two multiply-adds per iteration and no exponential; those run
 // only when a reference is taken (C is then read again):
 //   - at the first iteration, and again when a scaling leaves [2^-40, 2^40];
-//   - once the residual is below 1e-5 (for targets below the FP32 noise of
-//     about 4e-8 of residual), with FP64 exponentials. From there on the iteration
-//     adds to the FP64 sums R_i of the reference, and likewise to those of its columns, only the
-//     change against it, S_i = R_i + sum_j E_ij (v_j - 1), so its FP32 rounding is 2^-24 of |v - 1| instead of
+//   - once the residual is below 1e-5, for targets below the FP32 noise. From
+//     there on the iteration adds to the FP64 sums R_i of the reference, and
+//     likewise to those of its columns, only the change against it, S_i = R_i +
+//     sum_j E_ij (v_j - 1), so its FP32 rounding is 2^-24 of |v - 1| instead of
 //     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
 //     cost were needed before.
+//
+// The noise: marginal violation at the fixed point of the plain sums, emulated
+// on the CPU, against that of sweeps that form every exponential anew in FP32
+// from its FP64 argument: 1.3 - 2.1e-8 and 2.5 - 3.0e-8 on C-RAN layouts, 0.9 -
+// 1.2e-8 and 2.1 - 2.4e-8 with column offsets of 20 - 27 eps. (References in FP32
+// exponentials: 1.3 - 2.1e-8, but 2.7 - 9.2e-8 with the offsets.)
 //
 // What bounds it: the exchange. With the cost in LDS and an exponential per cell
 // the row update alone took 4.8 us of the 9.6 us per iteration at 20000 x 400;
@@ -404,9 +410,10 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
 
     // Row update of an iteration that takes a new reference G = g: the kernel
     // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i about the row maximum,
-    // from FP64 arguments, stored in FP32; S_i = R_i and the column partials
-    // sum_i E_ij a_i / S_i are FP64 sums. For delta sums the exponentials are
-    // FP64, too (table-driven), and the sums those of the FP64 entries.
+    // as FP64 exponentials (table-driven), stored in FP32; S_i = R_i and the
+    // column partials sum_i E_ij a_i / S_i are sums of the FP64 entries. (As FP32
+    // exponentials an entry that a scaling later raises to a column's largest
+    // carried the rounding of an argument of up to 126.)
     auto take_reference = [&](double (&ac)[CPL]) {
         constexpr bool kAhead = Src::kCheap && CPL <= 16;  // a row's loads one step ahead, where the registers allow it
         double* stage = reinterpret_cast<double*>(red);
@@ -477,16 +484,11 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 }
             }
             const double m = fmax((double)group_max<LPR>(mx), -1e300);
-            if (F64 || kind == kItRefDelta) {
 #pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    t[q] = exp2_tab_neg(t[q] - m, e2tab);
-                    if constexpr (!kAhead)
-                        if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) t[q] = (double)exp2_f32((float)(t[q] - m));
+            for (int q = 0; q < CPL; ++q) {
+                t[q] = exp2_tab_neg(t[q] - m, e2tab);
+                if constexpr (!kAhead)
+                    if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
             double s = 0, s2 = 0;  // even and odd cells: two shorter add chains
 #pragma unroll

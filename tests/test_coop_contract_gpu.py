@@ -48,3 +48,21 @@ def test_non_finite_cost_ends_a_batched_instance(A, I, J, bad):
             for k, y in enumerate((good, x)):
                 srv.submit(*y, 0.05, tol, 500, user_tag=k)
             assert [c.result.status for c in serve(srv, 2)] == [A.OT_OK, A.OT_ENUMERIC]
+
+
+@pytest.mark.parametrize("I,J,off", [(700, 33, 25), (1500, 200, 27), (3000, 400, 20), (2000, 700, 25)])
+def test_fp32_noise_of_plain_sums_with_column_offsets(A, oracle_lib, I, J, off):
+    """check_every holds the phase at its fixed point for dozens of iterations
+    of FP32 sums. Their noise is three roundings of a row (entry, scaling, sum)
+    of 2^-24 at most and 2.1e-8 in the mean, 3.6e-8 together, the first two
+    averaged over the row; columns average over hundreds of rows: bar 4e-8."""
+    print(f"\n[case] FP32 noise {I} x {J}, column offsets of {off} eps", flush=True)
+    rng, eps = np.random.default_rng(I), 0.01
+    C = (rng.uniform(0.0, 0.05, (I, J)) + np.linspace(0.0, off * eps, J)).astype(np.float32)
+    _, a, b = instance(I, J, J)
+    with A.Solver(I, J, check_every=48) as s:
+        st, res = s.solve_dense(C, a, b, eps, 4e-7, 400)
+        f, g = s.potentials()
+    assert st == A.OT_OK and (res.iterations, res.fp64_iterations) == (48, 0)
+    chk = oracle_lib.plan_stats(C.astype(np.float64), a, b, f, g, eps)
+    assert res.marginal_violation < 4e-8 and chk["marginal_violation"] < 4e-8
