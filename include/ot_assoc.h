@@ -117,8 +117,8 @@ typedef struct {
     int device;         /* HIP device ordinal */
     void *stream;       /* hipStream_t to issue work on; NULL = a stream owned by the handle */
     ot_precision precision;
-    int polish_iters;   /* chunked FP32 solves: FP64 iterations run before the first exact check
-                           (default 1); the cooperative launch needs none */
+    int polish_iters;   /* FP32 solves and batches: FP64 iterations run before the first exact
+                           check, unless the residual met a tol of 1e-7 or more (default 1) */
     int chunk;          /* iterations per graph launch between host checks (default 8) */
     int use_graphs;     /* capture iteration chunks in HIP graphs (default 1) */
     int sweep_blocks;   /* 0 = choose automatically; else workgroups per sweep */
@@ -512,7 +512,7 @@ typedef struct {
                               (0 = 90% of free memory, at most 256 GiB) */
     int max_slots;         /* requests in flight (0 = 1024) */
     int max_items;         /* row parts in flight (0 = 2^19) */
-    int polish_iters;      /* FP64 sweeps before the exact check (default 1) */
+    int polish_iters;      /* FP64 iterations before the exact check (default 1) */
     int sweep_waves;       /* 4 or 8 waves per sweep workgroup (default 8) */
     int rows_per_part;     /* 64, 128 or 256 rows per work item (default 128) */
     int keep_layouts;      /* resident potential sets kept (0 = 4096) */

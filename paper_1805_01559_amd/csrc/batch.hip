@@ -902,6 +902,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             A.ctl = ctl + e.slot;
             A.prm = sl.prm;
             A.batch = 1;
+            A.polish = polish_iters;
             A.cap = cap;
             J.src = DenseSrc<float>{sl.d.C, sl.d.ld};
             J.nb = e.t.nb;

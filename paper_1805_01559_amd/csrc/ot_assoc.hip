@@ -759,6 +759,7 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.prm = h->prm;
     A.tile = h->ker;
     A.validate = h->validate_pending ? 1 : 0;
+    A.polish = std::max(0, h->opt.polish_iters);
     A.cap = 1 << 30;
     // (Alg. 2's solves sum the loads; their plans are not asked for)
     A.loads = h->want_loads && p.cpl <= kLoadsCpl ? h->loads : nullptr;

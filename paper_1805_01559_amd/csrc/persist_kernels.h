@@ -26,7 +26,8 @@
 //     likewise to those of its columns, only the change against it, S_i = R_i +
 //     sum_j E_ij (v_j - 1), so its FP32 rounding is 2^-24 of |v - 1| instead of
 //     2^-24 of 1, and the phase runs on to tol where FP64 sweeps of the whole
-//     cost were needed before.
+//     cost were needed before;
+//   - in the FP64 iterations (polish_iters) that end such a solve.
 //
 // The noise: marginal violation at the fixed point of the plain sums, emulated
 // on the CPU, against that of sweeps that form every exponential anew in FP32
@@ -185,6 +186,7 @@ struct PersistArgs {
     int plan_f64;
     double* loads;   // J: RRH loads the final check sums, or null
     int batch;       // an instance of a batch: its control block carries a phase (kPh...)
+    int polish;      // FP64 iterations after the stop rule
     int cap;         // iterations of this launch (an instance of a batch that reaches it goes on in sweeps)
 };
 
@@ -250,44 +252,56 @@ constexpr double kDeltaMax = 0.125;
 // 1e-6 of the residual r_ref at which the reference was taken and are therefore
 // compared with tol itself. Long delta phases (a slowly converging instance
 // whose scalings drift far from the reference) renew the reference.
-__device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, bool batch,
-                                             double& r_ref, int& k_ref) {
+//
+// The solve then ends, as one in sweeps does, with `polish` FP64 iterations,
+// unless its residual met a target above the noise: iterations that take a
+// reference, whose exponentials and sums are FP64 throughout. (One costs 5 % of a
+// solve of 20000 x 400.) `polishing` counts those still to come.
+__device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, int polish,
+                                             int& polishing, double& r_ref, int& k_ref) {
     const int k = c->iter + 1;
     const double r = c->has_prev ? rsum / c->mass : pinf64();
     const bool bad = c->numeric_bad || (c->has_prev && !isfinite(r));
     c->r_last = r;
     c->iter = k;
     c->has_prev = 1;
-    c->last_fp64 = 0;
-    const double target = c->tol_fast > 0.0 ? c->tol_fast : c->tol;
-    const bool fine = kind == kItRefDelta || kind == kItDelta;  // residuals of delta sums
-    double mn = pinf64();
-    int nfin = 0;
-    for (int q = 0; q < 4; ++q)
-        if (isfinite(c->r_hist[q])) { mn = fmin(mn, c->r_hist[q]); ++nfin; }
-    const double noise = fine ? 1e-6 * r_ref : target >= stall_below ? stall_below : 0.0;
-    const bool stall = (nfin >= 1) && isfinite(r) && (r < noise) && (r > 0.95 * mn);
-    for (int q = 3; q > 0; --q) c->r_hist[q] = c->r_hist[q - 1];
-    c->r_hist[0] = r;
-    const bool met = r < target && (fine || target >= stall_below);
-    const bool at_check = c->check_every <= 1 || k % c->check_every == 0;
+    c->last_fp64 = polishing > 0 ? 1 : 0;
     int code = 0;
-    if (kind == kItRefDelta) {
-        k_ref = k;
-        if (batch) c->fp64_iters += 1;  // (a sweep of FP64 exponentials; a single solve counts those after the phase)
+    if (polishing > 0) {
+        c->fp64_iters += 1;
+        code = --polishing > 0 ? kDecRefDelta : kDecStop;
+    } else {
+        const double target = c->tol_fast > 0.0 ? c->tol_fast : c->tol;
+        const bool fine = kind == kItRefDelta || kind == kItDelta;  // residuals of delta sums
+        double mn = pinf64();
+        int nfin = 0;
+        for (int q = 0; q < 4; ++q)
+            if (isfinite(c->r_hist[q])) { mn = fmin(mn, c->r_hist[q]); ++nfin; }
+        const double noise = fine ? 1e-6 * r_ref : target >= stall_below ? stall_below : 0.0;
+        const bool stall = (nfin >= 1) && isfinite(r) && (r < noise) && (r > 0.95 * mn);
+        for (int q = 3; q > 0; --q) c->r_hist[q] = c->r_hist[q - 1];
+        c->r_hist[0] = r;
+        const bool met = r < target && (fine || target >= stall_below);
+        const bool at_check = c->check_every <= 1 || k % c->check_every == 0;
+        if (kind == kItRefDelta) k_ref = k;
+        if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kDeltaBelow)) {
+            r_ref = r;
+            code = kDecRefDelta;
+        }
+        if (at_check && (met || stall)) {
+            polishing = r < target && target >= stall_below ? 0 : polish;
+            code = polishing > 0 ? kDecRefDelta : kDecStop;
+        }
     }
-    if (fine ? (k - k_ref >= 64 && r < 0.03 * r_ref && !met) : (target < stall_below && r < kDeltaBelow)) {
-        r_ref = r;
-        code = kDecRefDelta;
-    }
-    if ((at_check && (met || stall)) || k >= c->max_iter) c->stop = 1;
+    if (k >= c->max_iter) code = kDecStop;
     if (bad) {
         c->numeric_bad = 1;
         c->done = 1;
-        c->stop = 1;
         c->result_iter = k;
+        code = kDecStop;
     }
-    return (c->stop | c->done) ? kDecStop : code;
+    if (code == kDecStop) c->stop = 1;
+    return code;
 }
 
 // Lane layout: a row is handled by LPR lanes (16, 32 or 64) of CPL cells each: 16
@@ -401,7 +415,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     const int dblk = nb - 1;
     if (blk == dblk && tid == 0) cs = *ctl;
     double r_ref = 0.0;  // (the deciding lane's)
-    int k_ref = 0;
+    int k_ref = 0, polishing = 0;
 
     const int steps = rpw / (WAVES * R);
     [[maybe_unused]] volatile int bad_before = 0;
@@ -807,7 +821,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                         if (cs.done && !cs.numeric_bad) code |= kDecPrev;
                     }
                 } else if (lane == 0) {
-                    code = bookkeep_coop(&cs, r, kind, A.stall_below, A.batch != 0, r_ref, k_ref);
+                    code = bookkeep_coop(&cs, r, kind, A.stall_below, A.polish, polishing, r_ref, k_ref);
                 }
                 if (lane == 0 && k - k0 >= A.cap) code = kDecStop;
                 code = __shfl(code, 0, kWave);

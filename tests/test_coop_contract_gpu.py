@@ -66,3 +66,42 @@ def test_fp32_noise_of_plain_sums_with_column_offsets(A, oracle_lib, I, J, off):
     assert st == A.OT_OK and (res.iterations, res.fp64_iterations) == (48, 0)
     chk = oracle_lib.plan_stats(C.astype(np.float64), a, b, f, g, eps)
     assert res.marginal_violation < 4e-8 and chk["marginal_violation"] < 4e-8
+
+
+@pytest.mark.parametrize("I,J", [(150, 20), (2000, 60), (3000, 400), (1200, 1100)])
+def test_polish_iters_act(A, I, J):
+    """polish_iters FP64 iterations end a solve below the FP32 noise, and none
+    one that met a tol above it. They are the FP64 iteration applied to the
+    unpolished potentials: exponents of up to 30 carry 4e-15 of rounding, the
+    exchanged sums 2^-51; bar 1e-12 per iteration in units of eps."""
+    print(f"\n[case] polish_iters {I} x {J}", flush=True)
+    C, a, b = instance(I, J, 3)
+    C64, eps, tol = C.astype(np.float64), 0.05, 1e-9
+    got = []
+    for n in (0, 1, 3):
+        with A.Solver(I, J, polish_iters=n) as s:
+            assert s.solve_dense(C, a, b, eps, 1e-6)[1].fp64_iterations == 0
+            st, res = s.solve_dense(C, a, b, eps, tol)
+            f, g = s.potentials()
+            assert st == A.OT_OK and res.flags & A.OT_RESULT_PERSISTENT
+            assert res.fp64_iterations == n
+            got.append((res.iterations, f, g))
+            if n:
+                st, res = s.solve_dense(C, a, b, eps, tol, max_iter=got[0][0] + 1)
+                assert st == A.OT_OK and (res.iterations, res.fp64_iterations) == (got[0][0] + 1, 1)
+    assert [x[0] - got[0][0] for x in got] == [0, 1, 3]
+    lse = lambda x, axis: x.max(axis) + np.log(np.exp(x - np.expand_dims(x.max(axis), axis)).sum(axis))
+    g = got[0][2]
+    for k in range(1, 4):
+        f = eps * (np.log(a) - lse((g - C64) / eps, 1))
+        g = eps * (np.log(b) - lse((f[:, None] - C64) / eps, 0))
+        for n, fn, gn in got[1:]:
+            if n == got[0][0] + k:
+                assert np.abs(fn - f).max() <= 1e-12 * k * eps and np.abs(gn - g).max() <= 1e-12 * k * eps
+    if J <= 512:
+        for n in (0, 1, 3):
+            with A.Solver(16, 16, batch_tune=0, polish_iters=n) as s, A.Server(polish_iters=n) as srv:
+                assert s.solve_batch([C], [a], [b], eps, 1e-6)[1][0].fp64_iterations == 0
+                srv.submit(C, a, b, eps, tol)
+                for res in (s.solve_batch([C], [a], [b], eps, tol)[1][0], serve(srv, 1)[0].result):
+                    assert res.fp64_iterations == n and res.marginal_violation < tol
