@@ -515,6 +515,7 @@ struct CheckArgs {
     double* col_part;   // gridDim.x x J
     double* stat_part;  // gridDim.x x 5
     const SolveParams* prm;
+    const Ctl* ctl;     // (a check of rejected inputs does nothing: its plan is not to be written)
     double* load_part;  // gridDim.x x J partial RRH loads (the instantiation with loads only)
     void* plan_out;     // I x J row-major plan, FP32 or FP64 (the instantiations with a plan only)
     int plan_f64;
@@ -837,6 +838,7 @@ __device__ __forceinline__ void check_rows_g(const CheckJob& A, const Src& src) 
 
 template <class Src, int VEC, int NCH, int WAVES, bool LOADS = false, typename PlanT = void>
 __global__ __launch_bounds__(WAVES * kWave) void k_check(CheckArgs A, Src src) {
+    if (A.ctl->input_bad) return;
     CheckJob job;
     job.r0 = (int64_t)blockIdx.x * A.rows_per_block;
     job.r1 = min(A.I, job.r0 + A.rows_per_block);

@@ -628,7 +628,7 @@ struct Solver {
         CheckArgs A{};
         A.I = I; A.J = J; A.nch = cs.nch; A.rows_per_block = cs.rpb;
         A.a = h->a; A.f = h->f[k & 1]; A.g = h->g[k & 1];
-        A.col_part = h->col_part; A.stat_part = h->stat_part; A.prm = h->prm;
+        A.col_part = h->col_part; A.stat_part = h->stat_part; A.prm = h->prm; A.ctl = h->ctl;
         A.load_part = fuse ? h->col_part + (size_t)cs.nb * (size_t)J : nullptr;
         // (Alg. 2's solves sum the loads; their plans are not asked for)
         A.plan_out = (fuse || (int64_t)I * J > h->plan_cap) ? nullptr : h->plan_out;

@@ -105,3 +105,18 @@ def test_polish_iters_act(A, I, J):
                 srv.submit(C, a, b, eps, tol)
                 for res in (s.solve_batch([C], [a], [b], eps, tol)[1][0], serve(srv, 1)[0].result):
                     assert res.fp64_iterations == n and res.marginal_violation < tol
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_refused_matrix_in_sweeps_writes_no_plan(A, dtype):
+    import torch
+    print(f"\n[case] refused matrix in sweeps, {dtype.__name__}", flush=True)
+    C, a, b = instance(900, 60, 5)
+    C[3, 4] = np.inf
+    prec = A.OT_PREC_FP32 if dtype == np.float32 else A.OT_PREC_FP64
+    with A.Solver(900, 60, persistent=0, precision=prec) as s:
+        plan = torch.full((900, 60), -7.0, device="cuda")
+        s.set_plan_output(plan)
+        with pytest.raises(A.OTError, match="non-finite"):
+            s.solve_dense(C.astype(dtype), a, b, 0.05, 1e-8)
+        assert bool((plan == -7.0).all())
