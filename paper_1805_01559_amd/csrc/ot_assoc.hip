@@ -358,12 +358,11 @@ ot_status validate_matrix(ot_assoc* h) {
 // its per-device set-up pass runs). Afterwards the handle can rebuild the source without the caller.
 // Value checks of the cost: kCheckNone, kCheckNow (the host waits for the
 // verdict) or kCheckDeferred (the verdict goes into the control block, bit 8
-// of input_bad, and ends the solve on the device).
-enum { kCheckNone = 0, kCheckNow = 1, kCheckDeferred = 2 };
-
-//
+// of input_bad, and ends the solve on the device: matrices by the solve's first
+// pass, validate_pending).
 // With `keep` (solves) a geometry cost is evaluated once, in FP64, into the
 // handle's buffer when there is room for it.
+enum { kCheckNone = 0, kCheckNow = 1, kCheckDeferred = 2 };
 ot_status upload_cost(ot_assoc* h, const ot_cost_desc* c, int check, bool keep = false) {
     const bool validate_values = check != kCheckNone;
     const bool now = check == kCheckNow;

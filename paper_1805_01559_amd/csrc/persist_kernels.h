@@ -99,7 +99,7 @@ constexpr int kMaxCoopGroups = 256; // workgroups of a cooperative launch (an ow
 //   rpart [2][nb]          row-residual partials by parity (padded to a line)
 //   gx    [2][kReplicas][Gs]  new g by parity, Gs = Jp rounded up to 512 (4 KiB
 //                          between replicas)
-//   dec   [2][kReplicas][8]   (iteration << 2) | stop, as uint64, one line per replica
+//   dec   [2][kReplicas][8]   (iteration << 3) | decision code, as uint64, one line per replica
 //   abort [8]              uint64, nonzero once a poll gave up
 //   fin   [7 x kMaxCoopGroups]  scalars of the final check: five per workgroup,
 //                          two per column block, tagged 1 once written
@@ -227,8 +227,8 @@ __host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int 
 // delta sums.
 enum : int { kItRef = 0, kItPlain = 1, kItRefDelta = 2, kItDelta = 3 };
 // Decision codes: bit 0 stop, bit 1 take a reference for delta sums next.
-// (in FP64: the iterate before is the returned one)
-constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2;
+// (in FP64: the iterate before is the returned one), bit 2 leave without the check.
+constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2, kDecSkip = 4;
 // Delta sums begin once the residual is below this: the scalings
 // then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
 // residuals down to about 1e-12, far below the FP32 noise (4e-8) of the plain
@@ -739,7 +739,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     };
 
     __syncthreads();
-    bool ok = true, bad = false;
+    bool ok = true, bad = false, skip = false;
     [[maybe_unused]] bool prev = false;  // FP64: iterate k - 1 is the returned one
     for (;;) {
         ++k;
@@ -824,11 +824,18 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                     code = bookkeep_coop(&cs, r, kind, A.stall_below, A.polish, polishing, r_ref, k_ref);
                 }
                 if (lane == 0 && k - k0 >= A.cap) code = kDecStop;
+                // (every workgroup's verdict on its rows of the matrix preceded its
+                // first partials)
+                if (lane == 0 && k == k0 + 1 && (A.validate || A.batch)) {
+                    cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cs.numeric_bad |= __hip_atomic_load(&ctl->numeric_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (cs.input_bad | cs.numeric_bad) code = kDecStop | kDecSkip;
+                }
                 code = __shfl(code, 0, kWave);
                 if (nb == 1) {
                     if (lane == 0) s_dec = (uint32_t)code;
                 } else if (lane < kReplicas) {
-                    put_agent(dec + ((size_t)P * kReplicas + lane) * 8, ((uint64_t)k << 2) | (uint64_t)code);
+                    put_agent(dec + ((size_t)P * kReplicas + lane) * 8, ((uint64_t)k << 3) | (uint64_t)code);
                 }
             }
         }
@@ -868,7 +875,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             const uint64_t* dp = dec + ((size_t)P * kReplicas + rep) * 8;
             uint64_t d = get_agent(dp);
             int spin = 0;
-            while ((d >> 2) != (uint64_t)k) {
+            while ((d >> 3) != (uint64_t)k) {
                 if ((++spin & 31) == 0 && (get_agent(abort_word) != 0 || spin > A.max_spin)) {
                     put_agent(abort_word, (uint64_t)1);
                     fail = true;
@@ -877,7 +884,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 __builtin_amdgcn_s_sleep(1);
                 d = get_agent(dp);
             }
-            s_dec = (uint32_t)(d & 3);
+            s_dec = (uint32_t)(d & 7);
         }
         if (fail) flag |= 1;
         if (__any(flag)) {  // (rare; one LDS atomic per wave, not one per lane)
@@ -893,6 +900,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         if (fl & 1) { ok = false; break; }
         has_prev = 1;
         if ((code & kDecStop) || (fl & 2)) {
+            skip = (code & kDecSkip) != 0;
             bad = (fl & 2) != 0;
             prev = F64 && !bad && (code & kDecPrev);
             break;
@@ -902,7 +910,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
-    if (ok && !bad) {
+    if (ok && !bad && !skip) {
         // ---- the returned iterate k: f of the rows, g (workgroup 0), and its exact
         //      check: FP64 sums over pi_ij = exp((f_i + g_j - C_ij) / eps) from the cost
         //      (read or regenerated once more), the plan and the RRH loads
@@ -1143,13 +1151,11 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             cs.iter = k - 1;
             cs.done = 0;
         }
-        // (every workgroup's verdict on its rows of the matrix preceded its
-        // first partials)
-        cs.input_bad |= __hip_atomic_load(&ctl->input_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cs.input_bad) cs.done = cs.stop = 1;
+        if (skip) {
+            cs.done = cs.stop = 1;
+            cs.result_iter = cs.iter;
+        }
         if (A.batch) {
-            cs.numeric_bad |= __hip_atomic_load(&ctl->numeric_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (cs.numeric_bad) cs.done = 1;
             // done, or further FP64 sweeps until an iterate meets tol; at the
             // launch's cap further sweeps of the phase
             const bool fin = cs.done || cs.chk_violation < cs.tol || cs.iter >= cs.max_iter ||

@@ -120,3 +120,30 @@ def test_refused_matrix_in_sweeps_writes_no_plan(A, dtype):
         with pytest.raises(A.OTError, match="non-finite"):
             s.solve_dense(C.astype(dtype), a, b, 0.05, 1e-8)
         assert bool((plan == -7.0).all())
+
+
+@pytest.mark.parametrize("I,J", [(100, 20), (4000, 60), (75001, 128)])
+@pytest.mark.parametrize("kind", ["rates", "dense", "dense64"])
+def test_refused_matrix_ends_the_solve_at_once(A, I, J, kind):
+    """A negative rate or an infinite cost makes no NaN: the verdict itself has
+    to end the solve, which would go on for minutes here (2e7 iterations), and
+    nothing may be written."""
+    import time
+    import torch
+    print(f"\n[case] refused {kind} matrix {I} x {J}", flush=True)
+    C, a, b = instance(I, J, 4)
+    X = (1.0 / (C + np.float32(0.1))) if kind == "rates" else C
+    X[I - 1, J // 2] = -1.0 if kind == "rates" else np.inf
+    f64 = kind == "dense64"
+    with A.Solver(I, J, precision=A.OT_PREC_FP64 if f64 else A.OT_PREC_FP32) as s:
+        solve = (lambda *x: s.solve_rates(X, 1.0, *x)) if kind == "rates" else (lambda *x: s.solve_dense(X, *x))
+        if f64:
+            X = X.astype(np.float64)
+        plan = torch.full((I, J), -7.0, device="cuda")
+        s.set_plan_output(plan)
+        n = 200_000 if f64 and I > 50000 else 20_000_000  # (the first sweeps make the check where no launch does)
+        t = time.time()
+        with pytest.raises(A.OTError, match="not finite and positive" if kind == "rates" else "non-finite"):
+            solve(a, b, 0.05, 1e-300, n)
+        assert time.time() - t < 5.0
+        assert bool((plan == -7.0).all())
