@@ -359,7 +359,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     double* Rl = ml + rpw;    // R_i = sum_j E_ij of the FP64 entries
     double* Sl = Rl + rpw;    // S_i = sum_j E_ij v_j of the last row update
     const int nown = persist_owned_blocks(nb, J);
-    double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block)
+    double* bl = Sl + rpw;    // b_j of the owned columns (8 per owned block), times asc
     double* cl = bl + (size_t)kColBlock * nown;  // their column sums at the reference (delta sums)
     double* vp = cl + (size_t)kColBlock * nown;  // FP64: v_j of the iterate before
     Real* xl = reinterpret_cast<Real*>(vp + (F64 ? Jr2 : 0));  // v_j, or v_j - 1 for delta sums
@@ -385,6 +385,11 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     const int k0 = ctl->iter;
     int has_prev = ctl->has_prev;
     const double kk = A.prm->kk, eps = A.prm->eps, inv_eps = 1.0 / A.prm->eps;
+    // The row scalings a_i / S_i are FP32 values: marginals of any total mass are
+    // brought to one of [1, 2) by a power of two, which the column update takes
+    // out again (S_i may drift over 2^40 between references; at a mass of 1e-30
+    // the scalings would be flushed to zero).
+    const double asc = F64 ? 1.0 : readlane_d(ldexp(1.0, -min(max(ilogb(ctl->mass), -1000), 1000)), 0);
 
     exp2_tab_fill(e2tab);
     for (int lr = tid; lr < rpw; lr += T) {
@@ -399,7 +404,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     }
     for (int e = tid; e < kColBlock * nown; e += T) {
         const int j = (blk + (e / kColBlock) * nb) * kColBlock + e % kColBlock;
-        bl[e] = j < J ? A.b[j] : 1.0;
+        bl[e] = j < J ? A.b[j] * asc : 1.0;
         cl[e] = 0.0;
     }
     for (int e = tid; e < slack; e += T) tile[(size_t)rpw * Jp + e] = 0;
@@ -511,7 +516,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 else s += t[q];
             }
             const double S = group_sum<LPR>(s + s2);
-            const double wq = vrow ? al[lr] / S : 0.0;
+            const double wq = vrow ? al[lr] * asc / S : 0.0;
             Real* trow = tile + (size_t)lr * Jp + sub;
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
@@ -588,7 +593,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                     res += ai * (fabs(S - So) / So);
                     Sp[u] = So;
                 } else {
-                    wq = (float)ai * __builtin_amdgcn_rcpf((float)S);
+                    wq = (float)(ai * asc) * __builtin_amdgcn_rcpf((float)S);
                     if constexpr (D) wq *= -(float)d[u] * __builtin_amdgcn_rcpf((float)Rr);
                     res += ai * (fabs(S - So) * (double)__builtin_amdgcn_rcpf((float)So));
                 }
@@ -1050,17 +1055,17 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 publish(acl, k1 + 1);
             }
         }
-        for (int o = blk, oi = 0; ok && o * kColBlock < J; o += nb, ++oi) {
+        for (int o = blk; ok && o * kColBlock < J; o += nb) {
             __syncthreads();
             ok = collect(o, k1);
             if (!ok) break;
             if (tid < kColBlock) {
                 const int jj = o * kColBlock + tid;
-                const int e = oi * kColBlock + tid;
                 double cres = 0.0, gb = 0.0;
                 if (jj < J) {
-                    cres = fabs(collected(tid) - bl[e]);
-                    gb = gl[jj] * bl[e];
+                    const double bj = A.b[jj];
+                    cres = fabs(collected(tid) - bj);
+                    gb = gl[jj] * bj;
                 }
                 cres += dpp_d<0xB1>(cres);  // the 8 columns of the block
                 cres += dpp_d<0x4E>(cres);

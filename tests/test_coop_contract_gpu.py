@@ -147,3 +147,25 @@ def test_refused_matrix_ends_the_solve_at_once(A, I, J, kind):
             solve(a, b, 0.05, 1e-300, n)
         assert time.time() - t < 5.0
         assert bool((plan == -7.0).all())
+
+
+@pytest.mark.parametrize("mass", [1e-34, 3e-30, 1e-20, 0.7, 1e20, 1e33])
+@pytest.mark.parametrize("I,J", [(150, 20), (2000, 60)])
+def test_total_mass_far_from_one(A, I, J, mass):
+    """Marginals in another unit: the same iterations (scalings by a power of
+    two are exact; by the factors here the marginals round anew, so that a
+    residual may land on the other side of tol once) and the same potentials,
+    f shifted by eps ln(mass). Column offsets of 25 eps make the row sums
+    drift over 2^30 between references."""
+    print(f"\n[case] total mass {mass:g}, {I} x {J}", flush=True)
+    rng, eps = np.random.default_rng(6), 0.01
+    C = (rng.uniform(0.0, 0.05, (I, J)) + np.linspace(0.0, 25 * eps, J)).astype(np.float32)
+    _, a, b = instance(I, J, 6)
+    for tol in (1e-5, 1e-9):
+        with A.Solver(I, J) as s, A.Solver(16, 16, batch_tune=0) as sb:
+            _, ref = s.solve_dense(C, a, b, eps, tol)
+            st, res = s.solve_dense(C, mass * a, mass * b, eps, tol)
+            stb, (rb,) = sb.solve_batch([C], [mass * a], [mass * b], eps, tol)
+        for q, r in ((st, res), (stb, rb)):
+            assert q == A.OT_OK and r.marginal_violation < tol and abs(r.iterations - ref.iterations) <= 1
+            assert abs(r.objective / mass - ref.objective) <= 4 * tol * C.max()
