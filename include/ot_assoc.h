@@ -495,8 +495,9 @@ ot_status ot_assoc_snapshot_potentials(ot_assoc *h, int s, double *f, double *g,
  * per scheduling instant) are queued on submit and admitted, oldest first, as
  * instance slots, work-list room and the device-memory budget allow, while
  * earlier requests are still iterating; every ot_serve_progress call admits
- * what fits, runs one chunk of iterations of everything in flight and returns
- * the requests that finished. A request with a nonzero layout_key starts from
+ * what fits, runs one chunk of iterations of everything in flight (up to 64 by
+ * teams of workgroups, as in a batch, or 8 in sweeps, which is about as long)
+ * and returns the requests that finished. A request with a nonzero layout_key starts from
  * the potentials that the last finished request of the same key (same I x J)
  * left resident, and leaves its own; resident sets are evicted least recently
  * used first when memory or keep_layouts runs out. A request's result does
@@ -513,8 +514,8 @@ typedef struct {
     int max_slots;         /* requests in flight (0 = 1024) */
     int max_items;         /* row parts in flight (0 = 2^19) */
     int polish_iters;      /* FP64 iterations before the exact check (default 1) */
-    int sweep_waves;       /* 4 or 8 waves per sweep workgroup (default 8) */
-    int rows_per_part;     /* 64, 128 or 256 rows per work item (default 128) */
+    int sweep_waves;       /* 4 or 8 waves per sweep workgroup (default 8; requests in sweeps only) */
+    int rows_per_part;     /* 64, 128 or 256 rows per work item (default 128; likewise) */
     int keep_layouts;      /* resident potential sets kept (0 = 4096) */
 } ot_serve_options;
 

@@ -51,8 +51,11 @@ constexpr size_t kAlign = 256;
 // Iterations of one team launch. Batches: past any but the slowest instance,
 // and short enough that the longest list of a workgroup (kTeamLaunch instances
 // over 256 workgroups, at 6 us per iteration) ends far within the waits' bound.
-// Servers: new requests wait for the launch to end.
-constexpr int kTeamCapBatch = 1024, kTeamCapServe = 256;
+// Servers: one progress call's share, about as long as the chunk of sweeps that
+// it takes the place of (8 iterations of 30 us and more), since requests that
+// arrive meanwhile wait for it; the next call goes on from its iterate.
+constexpr int kTeamCapBatch = 1024, kTeamCapServe = 64;
+static_assert(kTeamCapServe % 4 == 0, "a launch's zeroed slots carry the tag of iterations 0 modulo 4");
 constexpr size_t kTeamLaunch = 1024;  // instances of one launch
 
 double now_s() {
@@ -162,6 +165,7 @@ class DevicePool {
 struct Slot {
     bool live = false;      // admitted and not yet released
     bool finished = false;  // seen done in a control-block snapshot
+    bool teamed = false;    // in the team launch whose results are being read
     int64_t I = 0;
     int J = 0;
     int64_t ld = 0;
@@ -272,9 +276,11 @@ struct BatchEngine {
     double* team_xch = nullptr;
     size_t team_xch_cap = 0;
     Ctl* team_ctl = nullptr;
-    ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left);
+    ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left,
+                        std::vector<int>* open = nullptr);
     bool team_reserve(size_t bytes, size_t xch);
-    ot_status run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished, std::vector<int>& left);
+    ot_status run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished, std::vector<int>& left,
+                             std::vector<int>* open);
     int widx() const { return waves == 4 ? 0 : 1; }
     int gidx() const { return 2 * widx() + (items_running <= kTailItems ? 1 : 0); }
 };
@@ -799,14 +805,18 @@ bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
 }
 }  // namespace
 
-// Solves admitted instances by teams; waits for them. Those that are done are
-// returned in `finished`, the others queued for the chunks and in `left`.
+// Solves admitted instances by teams, for at most `cap` iterations; waits for
+// them. Those that are done are returned in `finished`, those that reached the
+// cap in `open` (for another call; without it they are left), the others
+// queued for the chunks and in `left`.
 ot_status BatchEngine::run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished,
-                                 std::vector<int>& left) {
+                                 std::vector<int>& left, std::vector<int>* open) {
     finished.clear();
     left.clear();
+    if (open) open->clear();
     for (size_t q = 0; q < ks.size(); q += kTeamLaunch)
-        if (ot_status st = run_team_group(ks.data() + q, std::min(kTeamLaunch, ks.size() - q), cap, finished, left))
+        if (ot_status st =
+                run_team_group(ks.data() + q, std::min(kTeamLaunch, ks.size() - q), cap, finished, left, open))
             return st;
     if (left.empty()) return OT_OK;
     for (int q = 0; q < 2; ++q)  // (relay_h is idle: its last reader was waited for)
@@ -845,7 +855,7 @@ bool BatchEngine::team_reserve(size_t bytes, size_t xch) {
 }
 
 ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished,
-                                      std::vector<int>& left) {
+                                      std::vector<int>& left, std::vector<int>* open) {
     const int groups = std::min(num_cu, kMaxCoopGroups);
     struct Entry {
         int slot;
@@ -937,20 +947,27 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
         const int* sd = (const int*)(team_d + jobs_b + items_b);
         void* args[] = {(void*)&jd, (void*)&id, (void*)&sd};
         // (refused: the instances stay as admitted and go to the chunks)
-        if (hipLaunchCooperativeKernel(kern, dim3((unsigned)groups), dim3(512), args, (unsigned)lds, stream) != hipSuccess)
+        if (hipLaunchCooperativeKernel(kern, dim3((unsigned)groups), dim3(512), args, (unsigned)lds, stream) != hipSuccess) {
             (void)hipGetLastError();
+            jobs.clear();
+        }
     }
     ECHK(this, hipMemcpyAsync(team_ctl, ctl, sizeof(Ctl) * std::max(hi_slot, 1), hipMemcpyDeviceToHost, stream));
     ECHK(this, hipStreamSynchronize(stream));
+    for (const Entry& e : jobs) slots[e.slot].teamed = true;
     for (size_t q = 0; q < n; ++q) {
         Slot& s = slots[ks[q]];
         const Ctl& c = team_ctl[ks[q]];
+        const bool teamed = s.teamed;
+        s.teamed = false;
         if (c.phase == kPhDone) {
             s.fin = c;
             s.finished = true;
             --n_live_running;
             items_running -= s.parts_cap;
             finished.push_back(ks[q]);
+        } else if (open && teamed && c.phase == kPhFast) {
+            open->push_back(ks[q]);
         } else {
             left.push_back(ks[q]);
         }
@@ -1502,6 +1519,7 @@ struct ot_serve {
     std::deque<ot_completion> done;
     int keep_layouts = 4096;
     std::vector<int> running;  // slots in flight
+    std::vector<int> teams;    // those of them that teams solve, from the next progress call on
     std::unordered_map<int, int> warm_of;  // slot -> 1 if warm started
     std::unordered_map<int, uint64_t> pinned_key;
     std::vector<PendingCopy> copies;  // resident updates not yet queued
@@ -1633,7 +1651,7 @@ ot_status ot_serve_submit(ot_serve* s, const ot_request* r, uint64_t* ticket) {
 
 // Admits from the head of the queue while slots, work-list room and the
 // byte budget allow (evicting idle resident potentials if that makes room),
-// runs one chunk when anything is in flight, and hands back completions.
+// runs a share of everything in flight, and hands back completions.
 ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n_out) {
     if (!s) return OT_EINVAL;
     s->err.clear();
@@ -1645,7 +1663,6 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
     // fails is retried one request at a time, so that the error completes
     // the request it belongs to.
     size_t gmax = kServeAdmitGroup;
-    std::vector<int> admitted;
     auto complete_with = [&](const Pending& p, ot_status st) {
         ot_completion c{};
         c.ticket = p.ticket;
@@ -1711,16 +1728,19 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
             s->warm_of[ks[q]] = gres[q] ? 1 : 0;
             if (gres[q]) gres[q]->last_use = ++s->tick;
             s->running.push_back(ks[q]);
-            admitted.push_back(ks[q]);
+            s->teams.push_back(ks[q]);
             s->queue.pop_front();
         }
     }
-    // 2. the admitted requests by teams; then one chunk of what those left (now
-    // or earlier), and the snapshot behind the previous chunk
-    std::vector<int> fin, done_now, left;
-    if (!admitted.empty())
-        if (ot_status st = e.run_teams(admitted, kTeamCapServe, done_now, left)) return serve_fail(s, st, e.err);
-    if (e.n_live_running > 0) {
+    // 2. up to kTeamCapServe iterations of those that teams solve; then one chunk
+    // of what they left (now or earlier), and the snapshot behind the previous
+    // chunk
+    std::vector<int> fin, done_now, left, open;
+    if (!s->teams.empty()) {
+        if (ot_status st = e.run_teams(s->teams, kTeamCapServe, done_now, left, &open)) return serve_fail(s, st, e.err);
+        s->teams.swap(open);
+    }
+    if (e.n_live_running > (int)s->teams.size()) {
         if (ot_status st = e.launch_chunk()) return serve_fail(s, st, e.err);
         if (ot_status st = e.collect(true, fin)) return serve_fail(s, st, e.err);
     } else if (e.snap_pending >= 0) {

@@ -187,7 +187,8 @@ struct PersistArgs {
     double* loads;   // J: RRH loads the final check sums, or null
     int batch;       // an instance of a batch: its control block carries a phase (kPh...)
     int polish;      // FP64 iterations after the stop rule
-    int cap;         // iterations of this launch (an instance of a batch that reaches it goes on in sweeps)
+    int cap;         // iterations of this launch, a multiple of 4 (an instance of a batch that reaches it
+                     // leaves with its iterate and goes on in sweeps or in another launch)
 };
 
 // Static LDS of the cooperative phase.
@@ -419,13 +420,16 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     // workgroups it owns none) sums the residuals and takes the stop decision
     const int dblk = nb - 1;
     if (blk == dblk && tid == 0) cs = *ctl;
-    double r_ref = 0.0;  // (the deciding lane's)
-    int k_ref = 0, polishing = 0;
+    double r_ref = ctl->r_last;  // (the deciding lane's)
+    int k_ref = k0, polishing = 0;
 
     const int steps = rpw / (WAVES * R);
     [[maybe_unused]] volatile int bad_before = 0;
     double res = 0.0;  // this lane's part of the row residual of the previous iterate
     int k = k0, kind = kItRef;
+    // (an instance that a launch before this one left in delta sums)
+    if constexpr (!F64)
+        if (k0 > 0 && ctl->r_last < kDeltaBelow && ctl->tol_fast < A.stall_below) kind = kItRefDelta;
 
     // Row update of an iteration that takes a new reference G = g: the kernel
     // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i about the row maximum,
@@ -828,7 +832,7 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                 } else if (lane == 0) {
                     code = bookkeep_coop(&cs, r, kind, A.stall_below, A.polish, polishing, r_ref, k_ref);
                 }
-                if (lane == 0 && k - k0 >= A.cap) code = kDecStop;
+                if (lane == 0 && k - k0 >= A.cap && !(code & kDecStop) && polishing == 0) code = kDecStop | kDecSkip;
                 // (every workgroup's verdict on its rows of the matrix preceded its
                 // first partials)
                 if (lane == 0 && k == k0 + 1 && (A.validate || A.batch)) {
@@ -915,19 +919,13 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
         else kind = (code & kDecRefDelta) ? kItRefDelta : (fl & 4) ? kItRef : kItPlain;
     }
 
-    if (ok && !bad && !skip) {
-        // ---- the returned iterate k: f of the rows, g (workgroup 0), and its exact
-        //      check: FP64 sums over pi_ij = exp((f_i + g_j - C_ij) / eps) from the cost
-        //      (read or regenerated once more), the plan and the RRH loads
-        //      sum_i C_ij pi_ij where they are asked for. In this launch it costs
-        //      one pass and two hops of the exchange; as launches of its own it
-        //      took five more (polish, combine, check, two folds).
+    if (ok && !bad) {
+        // ---- the returned iterate k: f of the rows, g (workgroup 0)
         J = __builtin_amdgcn_readfirstlane(J);
         Jp = __builtin_amdgcn_readfirstlane(Jp);
         ncl = __builtin_amdgcn_readfirstlane(ncl);
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(sub), "+v"(rg), "+s"(J), "+s"(Jp), "+s"(ncl));
-        double* stage = reinterpret_cast<double*>(red);
-        src.stage(stage, J);
+        src.stage(reinterpret_cast<double*>(red), J);
         const int kr = F64 && prev ? k - 1 : k;  // the returned iterate
         double* fo = (kr & 1) ? A.f[1] : A.f[0];
         for (int lr = tid; lr < nrows; lr += T) {
@@ -943,6 +941,14 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             if (blk == 0) go[j] = gl[j];
         }
         __syncthreads();
+    }
+    if (ok && !bad && !skip) {
+        // ---- its exact check: FP64 sums over pi_ij = exp((f_i + g_j - C_ij) / eps) from
+        //      the cost (read or regenerated once more), the plan and the RRH loads
+        //      sum_i C_ij pi_ij where they are asked for. In this launch it costs
+        //      one pass and two hops of the exchange; as launches of its own it
+        //      took four more (combine, check, two folds).
+        const double* stage = reinterpret_cast<const double*>(red);
         constexpr bool kLoads = !LEAN && CPL <= kLoadsCpl;
         const bool with_loads = kLoads && A.loads != nullptr;
         double ac[CPL], acl[kLoads ? CPL : 1];
@@ -1156,16 +1162,16 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
             cs.iter = k - 1;
             cs.done = 0;
         }
-        if (skip) {
+        if (skip && (cs.input_bad | cs.numeric_bad)) {
             cs.done = cs.stop = 1;
             cs.result_iter = cs.iter;
         }
         if (A.batch) {
             // done, or further FP64 sweeps until an iterate meets tol; at the
-            // launch's cap further sweeps of the phase
-            const bool fin = cs.done || cs.chk_violation < cs.tol || cs.iter >= cs.max_iter ||
-                             !isfinite(cs.chk_violation);
-            cs.phase = fin ? kPhDone : k - k0 >= A.cap ? kPhFast : kPhExact;
+            // launch's cap further iterations of the phase
+            const bool fin = cs.done || (!skip && (cs.chk_violation < cs.tol || cs.iter >= cs.max_iter ||
+                                                   !isfinite(cs.chk_violation)));
+            cs.phase = fin ? kPhDone : skip ? kPhFast : kPhExact;
             cs.done = fin ? 1 : 0;
             cs.stop = 0;
             cs.result_iter = cs.check_iter = cs.iter;

@@ -5,6 +5,8 @@ options, limits and memory."""
 import numpy as np
 import pytest
 
+import scenario as S
+
 pytestmark = pytest.mark.gpu
 
 
@@ -169,3 +171,40 @@ def test_total_mass_far_from_one(A, I, J, mass):
         for q, r in ((st, res), (stb, rb)):
             assert q == A.OT_OK and r.marginal_violation < tol and abs(r.iterations - ref.iterations) <= 1
             assert abs(r.objective / mass - ref.objective) <= 4 * tol * C.max()
+
+
+def test_progress_runs_a_bounded_share(A, oracle_lib):
+    """One progress call runs 64 iterations of what is in flight at most: a
+    request that needs hundreds is still running after the first call, one that
+    arrives then and needs few finishes before it, and the slow one ends as it
+    does alone, bit for bit."""
+    print("\n[case] a fast request overtakes a slow one", flush=True)
+    L = S.make_layout(700, 60, 2000.0, hot_spots=2, hot_share=0.4, seed=78)
+    d = L.dev_xy.astype(np.float64)[:, None, :] - L.rrh_xy.astype(np.float64)[None, :, :]
+    C = np.sqrt((d**2).sum(2))
+    C = (C / np.median(C)).astype(np.float32)
+    eps = 0.02
+    got = []
+    for fast in (False, True):
+        for tol in (1e-6, 1e-9):
+            order = []
+            with A.Server() as srv:
+                srv.submit(C, L.a, L.b, eps, tol, 20000, layout_key=1, user_tag=0)
+                calls = 1
+                order += srv.progress()
+                assert not order and srv.counts()[1] == 1
+                if fast:
+                    srv.submit(*instance(900, 70, 5), 0.05, 1e-6, 2000, user_tag=1)
+                while len(order) < 1 + fast:
+                    order += srv.progress()
+                    calls += 1
+                f, g = srv.potentials(1, 700, 60)
+            if fast:
+                assert order[0].user_tag == 1 and order[0].result.status == A.OT_OK
+            res = order[-1].result
+            assert res.status == A.OT_OK and res.iterations > 250 and calls >= res.iterations / 64
+            chk = oracle_lib.plan_stats(C.astype(np.float64), L.a, L.b, f, g, eps)
+            assert res.marginal_violation < tol and chk["marginal_violation"] < tol * 1.05
+            got.append((f, g, res.iterations))
+    for x, y in zip(got[:2], got[2:]):
+        assert x[2] == y[2] and np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1])
