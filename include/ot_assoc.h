@@ -509,8 +509,8 @@ typedef struct ot_serve ot_serve;
 typedef struct {
     int device;
     void *stream;          /* hipStream_t; NULL = a stream owned by the server */
-    double budget_bytes;   /* device memory for requests and resident potentials
-                              (0 = 90% of free memory, at most 256 GiB) */
+    double budget_bytes;   /* device memory for requests (with their teams' exchange blocks,
+                              where they fit) and resident potentials (0 = 90% of free memory, at most 256 GiB) */
     int max_slots;         /* requests in flight (0 = 1024) */
     int max_items;         /* row parts in flight (0 = 2^19) */
     int polish_iters;      /* FP64 iterations before the exact check (default 1) */

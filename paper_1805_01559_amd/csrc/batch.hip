@@ -165,6 +165,7 @@ class DevicePool {
 struct Slot {
     bool live = false;      // admitted and not yet released
     bool finished = false;  // seen done in a control-block snapshot
+    double* xch = nullptr;  // exchange block of its team, or null (it is solved in sweeps)
     bool teamed = false;    // in the team launch whose results are being read
     int64_t I = 0;
     int J = 0;
@@ -259,7 +260,8 @@ struct BatchEngine {
     ot_status init(int dev, hipStream_t st, int slots_cap, int items_cap, size_t budget);
     ot_status prepare_kernels();
     ot_status capture(int widx);
-    ot_status admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict, bool queue);
+    ot_status admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict, bool queue,
+                    bool teams);
     ot_status upload_cost(Slot& s, const ot_cost_desc* c, char* C_mem, char* stage, PadJob* pad, GeoJob* geo);
     ot_status launch_chunk();
     ot_status collect(bool wait, std::vector<int>& finished);
@@ -269,16 +271,14 @@ struct BatchEngine {
     ot_status tune(const std::vector<int>& batch_slots);
     std::string tune_key(const std::vector<int>& batch_slots) const;
     ot_status relayout(const std::vector<int>& batch_slots, int w, int64_t rpp);
-    // teams: job, item and list staging, exchange blocks, control blocks read back
+    // teams: job, item and list staging, control blocks read back
     int lds_max = 0;
     char *team_h = nullptr, *team_d = nullptr;
     size_t team_cap = 0;
-    double* team_xch = nullptr;
-    size_t team_xch_cap = 0;
     Ctl* team_ctl = nullptr;
     ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left,
                         std::vector<int>* open = nullptr);
-    bool team_reserve(size_t bytes, size_t xch);
+    bool team_reserve(size_t bytes);
     ot_status run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished, std::vector<int>& left,
                              std::vector<int>* open);
     int widx() const { return waves == 4 ? 0 : 1; }
@@ -308,7 +308,7 @@ BatchEngine::~BatchEngine() {
     if (stream) hipStreamSynchronize(stream);
     for (auto g : graph)
         if (g) hipGraphExecDestroy(g);
-    void* dev_bufs[] = {tab, ctl, lists_mem, blob_d[0], blob_d[1], relay_d, team_d, team_xch};
+    void* dev_bufs[] = {tab, ctl, lists_mem, blob_d[0], blob_d[1], relay_d, team_d};
     for (void* p : dev_bufs)
         if (p) hipFree(p);
     void* host_bufs[] = {snap[0], snap[1], blob_h[0], blob_h[1], relay_h, team_h, team_ctl};
@@ -444,8 +444,8 @@ ot_status BatchEngine::capture(int gi) {
 
 // Bytes of one instance's block: cost (unless referenced), marginals,
 // potentials (two parities), parts partials, solve constants.
-static size_t slot_bytes(int64_t I, int J, int64_t ld, int parts_cap, bool own_cost) {
-    size_t b = 0;
+static size_t slot_bytes(int64_t I, int J, int64_t ld, int parts_cap, bool own_cost, size_t xch) {
+    size_t b = align_up(sizeof(double) * xch);
     if (own_cost) b += align_up(sizeof(float) * (size_t)I * ld);
     b += align_up(sizeof(double) * I) + align_up(sizeof(double) * J);                      // a, b
     b += 2 * align_up(sizeof(double) * I) + 2 * align_up(sizeof(double) * J);              // f, g
@@ -453,6 +453,36 @@ static size_t slot_bytes(int64_t I, int J, int64_t ld, int parts_cap, bool own_c
     b += align_up(sizeof(double) * (size_t)parts_cap * 5) + align_up(sizeof(SolveParams));
     return b;
 }
+
+// Row split and team size of an instance, by its own size alone: as few
+// workgroups as its kernel fits (the exchange, most of an iteration, costs
+// the same however many share it), with equal shares.
+namespace {
+struct TeamShape {
+    int cls = 0, rpw = 0, nb = 0, ncl = 0;
+    size_t lds = 0;
+};
+
+bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
+    t.cls = team_class(J);
+    const int lpr = team_lpr(t.cls), rows = team_rows(t.cls), width = team_cpl(t.cls) * lpr;
+    t.ncl = (J + lpr - 1) / lpr;
+    const int Jp = t.ncl * lpr, slack = width - Jp;
+    const int groups = std::min(num_cu, kMaxCoopGroups);
+    auto lds_of = [&](int64_t rpw, int nb) { return persist_lds_bytes((int)rpw, J, Jp, 8, width, slack, nb) + 2048; };
+    // the smallest team that fits (the LDS of the owned columns shrinks as it grows)
+    const size_t fixed = lds_of(0, groups), per_row = (size_t)Jp * 4 + 32;
+    if (lds_max <= 0 || fixed + rows * per_row > (size_t)lds_max) return false;
+    const int64_t most = (int64_t)(((size_t)lds_max - fixed) / per_row) / rows * rows;
+    for (int64_t nb = (I + most - 1) / most; nb <= groups; ++nb) {
+        t.rpw = (int)(((I + nb - 1) / nb + rows - 1) / rows * rows);
+        t.nb = (int)((I + t.rpw - 1) / t.rpw);
+        t.lds = lds_of(t.rpw, t.nb) - 2048;
+        if (lds_of(t.rpw, t.nb) <= (size_t)lds_max) return true;
+    }
+    return false;
+}
+}  // namespace
 
 static int64_t parts_of(int64_t I, int64_t rpp) { return (I + rpp - 1) / rpp; }
 
@@ -562,9 +592,10 @@ static ot_status check_desc(BatchEngine* e, const ot_cost_desc* c) {
 // OT_ENOMEM and nothing is admitted); otherwise admits the longest prefix
 // that fits and reports the admitted slots. Settings are checked here,
 // marginal values on the device, so admission never waits on the GPU beyond
-// the staging set of the admission before last.
+// the staging set of the admission before last. With `teams`, slots of
+// instances that a team can solve hold their exchange block, too.
 ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>& out_slots, bool strict,
-                             bool queue) {
+                             bool queue, bool teams) {
     out_slots.clear();
     if (reqs.empty()) return OT_OK;
     ECHK(this, hipSetDevice(device));
@@ -631,7 +662,9 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
         size_t stage_b = 0;
         if (!ref && !from_positions(c) && c->mem == OT_MEM_HOST) stage_b = esz * (size_t)(I * lds);
         char* stage = stage_b ? pool.alloc(stage_b) : nullptr;
-        char* mem = (stage_b && !stage) ? nullptr : pool.alloc(slot_bytes(I, J, ld, parts_cap, !ref));
+        TeamShape ts;
+        const size_t xch = teams && team_shape(I, J, num_cu, lds_max, ts) ? persist_exchange_doubles(ts.nb, J) : 0;
+        char* mem = (stage_b && !stage) ? nullptr : pool.alloc(slot_bytes(I, J, ld, parts_cap, !ref, xch));
         if (!mem) {
             if (stage) pool.release(stage);
             if (strict) {
@@ -680,6 +713,7 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
         d.res_part = (double*)carve(sizeof(double) * parts_cap);
         d.stat_part = (double*)carve(sizeof(double) * (size_t)parts_cap * 5);
         sl.prm = (SolveParams*)carve(sizeof(SolveParams));
+        if (xch) sl.xch = (double*)carve(sizeof(double) * xch);
         d.prm = sl.prm;
         d.ctl = ctl + k;
         d.kk = std::log2(std::exp(1.0)) / r.eps;
@@ -775,36 +809,6 @@ ot_status BatchEngine::admit(const std::vector<AdmitReq>& reqs, std::vector<int>
 }
 
 // ------------------------------------------------------------------ teams --
-// Row split and team size of an instance, by its own size alone: as few
-// workgroups as its kernel fits (the exchange, most of an iteration, costs
-// the same however many share it), with equal shares.
-namespace {
-struct TeamShape {
-    int cls = 0, rpw = 0, nb = 0, ncl = 0;
-    size_t lds = 0;
-};
-
-bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
-    t.cls = team_class(J);
-    const int lpr = team_lpr(t.cls), rows = team_rows(t.cls), width = team_cpl(t.cls) * lpr;
-    t.ncl = (J + lpr - 1) / lpr;
-    const int Jp = t.ncl * lpr, slack = width - Jp;
-    const int groups = std::min(num_cu, kMaxCoopGroups);
-    auto lds_of = [&](int64_t rpw, int nb) { return persist_lds_bytes((int)rpw, J, Jp, 8, width, slack, nb) + 2048; };
-    // the smallest team that fits (the LDS of the owned columns shrinks as it grows)
-    const size_t fixed = lds_of(0, groups), per_row = (size_t)Jp * 4 + 32;
-    if (lds_max <= 0 || fixed + rows * per_row > (size_t)lds_max) return false;
-    const int64_t most = (int64_t)(((size_t)lds_max - fixed) / per_row) / rows * rows;
-    for (int64_t nb = (I + most - 1) / most; nb <= groups; ++nb) {
-        t.rpw = (int)(((I + nb - 1) / nb + rows - 1) / rows * rows);
-        t.nb = (int)((I + t.rpw - 1) / t.rpw);
-        t.lds = lds_of(t.rpw, t.nb) - 2048;
-        if (lds_of(t.rpw, t.nb) <= (size_t)lds_max) return true;
-    }
-    return false;
-}
-}  // namespace
-
 // Solves admitted instances by teams, for at most `cap` iterations; waits for
 // them. Those that are done are returned in `finished`, those that reached the
 // cap in `open` (for another call; without it they are left), the others
@@ -830,28 +834,20 @@ ot_status BatchEngine::run_teams(const std::vector<int>& ks, int cap, std::vecto
     return OT_OK;
 }
 
-// Room for a team launch: job and workgroup lists of `bytes`, exchange blocks of
-// `xch` doubles. False when there is none.
-bool BatchEngine::team_reserve(size_t bytes, size_t xch) {
-    bool ok = true;
-    if (team_cap < bytes) {
-        if (team_h) hipHostFree(team_h);
-        if (team_d) hipFree(team_d);
-        team_h = team_d = nullptr;
-        team_cap = 0;
-        ok = hipHostMalloc(&team_h, 2 * bytes) == hipSuccess &&
-             otk_host::dev_malloc((void**)&team_d, 2 * bytes) == hipSuccess;
-        if (ok) team_cap = 2 * bytes;
+// Room for the job and workgroup lists of a team launch. False when there is none.
+bool BatchEngine::team_reserve(size_t bytes) {
+    if (team_cap >= bytes) return true;
+    if (team_h) hipHostFree(team_h);
+    if (team_d) hipFree(team_d);
+    team_h = team_d = nullptr;
+    team_cap = 0;
+    if (hipHostMalloc(&team_h, 2 * bytes) != hipSuccess ||
+        otk_host::dev_malloc((void**)&team_d, 2 * bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
-    if (ok && team_xch_cap < xch) {
-        if (team_xch) hipFree(team_xch);
-        team_xch = nullptr;
-        team_xch_cap = 0;
-        ok = otk_host::dev_malloc((void**)&team_xch, sizeof(double) * xch) == hipSuccess;
-        if (ok) team_xch_cap = xch;
-    }
-    if (!ok) (void)hipGetLastError();
-    return ok;
+    team_cap = 2 * bytes;
+    return true;
 }
 
 ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vector<int>& finished,
@@ -860,24 +856,21 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
     struct Entry {
         int slot;
         TeamShape t;
-        size_t xch;
     };
     std::vector<Entry> jobs;
-    size_t xch = 0, n_items = 0;
+    size_t n_items = 0;
     for (size_t q = 0; q < n; ++q) {
         const Slot& sl = slots[ks[q]];
-        Entry e{ks[q], {}, xch};
-        if (!team_shape(sl.I, sl.J, groups, lds_max, e.t)) {
-            continue;  // (too large for LDS: it stays as admitted)
-        }
-        xch += (persist_exchange_doubles(e.t.nb, sl.J) + 31) / 32 * 32;
+        Entry e{ks[q], {}};
+        if (!sl.xch || !team_shape(sl.I, sl.J, num_cu, lds_max, e.t))
+            continue;  // (too large for LDS, or admitted without an exchange block: it stays as admitted)
         n_items += (size_t)e.t.nb;
         jobs.push_back(e);
     }
     const size_t jobs_b = align_up(sizeof(TeamJob) * jobs.size()), items_b = align_up(sizeof(int2) * n_items);
     const size_t need = jobs_b + items_b + align_up(sizeof(int) * (size_t)(groups + 1));
     // (no memory for the launch: the instances stay as admitted and go to the chunks)
-    if (!jobs.empty() && !team_reserve(need, xch)) jobs.clear();
+    if (!jobs.empty() && !team_reserve(need)) jobs.clear();
     if (!jobs.empty()) {
         // the largest teams first (ties in request order)
         std::stable_sort(jobs.begin(), jobs.end(), [](const Entry& a, const Entry& b) { return a.t.nb > b.t.nb; });
@@ -908,7 +901,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             A.f[1] = sl.d.f[1];
             A.g[0] = sl.d.g[0];
             A.g[1] = sl.d.g[1];
-            A.xch = team_xch + e.xch;
+            A.xch = sl.xch;
             A.ctl = ctl + e.slot;
             A.prm = sl.prm;
             A.batch = 1;
@@ -938,8 +931,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
         }
         sh[groups] = pos;
         ECHK(this, hipMemcpyAsync(team_d, team_h, need, hipMemcpyHostToDevice, stream));
-        hipLaunchKernelGGL(k_team_clear, dim3((unsigned)std::min<size_t>(2048, (xch + 255) / 256)), dim3(256), 0, stream,
-                           team_xch, xch);
+        hipLaunchKernelGGL(k_team_clear, dim3(16, (unsigned)jobs.size()), dim3(256), 0, stream, (const TeamJob*)team_d);
         const void* kern = otk_team_kernel();
         ECHK(this, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         const TeamJob* jd = (const TeamJob*)team_d;
@@ -1358,7 +1350,9 @@ ot_status ot_assoc_solve_batch(ot_assoc* h, int n, const ot_cost_desc* costs, co
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     std::vector<int> ks;
-    ot_status st = e->admit(reqs, ks, true, true);
+    ot_status st = e->admit(reqs, ks, true, true, h->opt.persistent != 0);
+    // (a batch that only fits without the teams' exchange blocks runs in sweeps)
+    if (st == OT_ENOMEM && h->opt.persistent) st = e->admit(reqs, ks, true, true, false);
     if (!st) {
         // marginals were checked on the device: one read-back for all of them
         const int hi = *std::max_element(ks.begin(), ks.end()) + 1;
@@ -1663,6 +1657,7 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
     // fails is retried one request at a time, so that the error completes
     // the request it belongs to.
     size_t gmax = kServeAdmitGroup;
+    bool lean = false;
     auto complete_with = [&](const Pending& p, ot_status st) {
         ot_completion c{};
         c.ticket = p.ticket;
@@ -1698,7 +1693,7 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
             gres.push_back(res);
         }
         std::vector<int> ks;
-        ot_status st = e.admit(group, ks, false, false);
+        ot_status st = e.admit(group, ks, false, false, !lean);
         if (st) {
             if (group.size() > 1) {
                 gmax = 1;
@@ -1708,16 +1703,24 @@ ot_status ot_serve_progress(ot_serve* s, ot_completion* out, int max_out, int* n
             complete_with(s->queue.front(), st);
             s->queue.pop_front();
             gmax = kServeAdmitGroup;
+            lean = false;
             continue;
         }
         gmax = kServeAdmitGroup;
         if (ks.empty()) {
             if (evict_one(s, s->queue.front().req.layout_key)) continue;  // retry with more room
             if (e.n_live_running > 0) break;                               // wait for running requests to finish
+            if (!lean) {  // alone, and without its team's exchange block (it then runs in sweeps)
+                lean = true;
+                gmax = 1;
+                continue;
+            }
+            lean = false;
             complete_with(s->queue.front(), OT_ENOMEM);  // it cannot fit even on an idle engine
             s->queue.pop_front();
             continue;
         }
+        lean = false;
         for (size_t q = 0; q < ks.size(); ++q) {
             const Pending& p = s->queue.front();
             Slot& sl = e.slots[ks[q]];

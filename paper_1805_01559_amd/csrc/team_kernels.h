@@ -39,10 +39,12 @@ struct TeamJob {
 };
 
 // Zeroes the exchange blocks of a launch (a zero slot carries the tag of no
-// first iteration; instances that start warm or resume start at iteration 0,
-// too, or are left to the sweeps).
-static __global__ void k_team_clear(double* xch, size_t n) {
-    for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) xch[q] = 0.0;
+// first iteration: every launch starts an instance at a multiple of 4).
+static __global__ __launch_bounds__(256) void k_team_clear(const TeamJob* jobs) {
+    const TeamJob& J = jobs[blockIdx.y];
+    const size_t n = persist_exchange_doubles(J.nb, J.A.J);
+    for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x)
+        J.A.xch[q] = 0.0;
 }
 
 // items[start[b]] .. items[start[b + 1] - 1]: workgroup b's instances and its rank in their teams.

@@ -208,3 +208,37 @@ def test_progress_runs_a_bounded_share(A, oracle_lib):
             got.append((f, g, res.iterations))
     for x, y in zip(got[:2], got[2:]):
         assert x[2] == y[2] and np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1])
+
+
+def slot_bytes(I, J):
+    """A server request's own device memory: padded FP32 cost, marginals, two
+    sets of potentials, sweep partials of 64 rows, each part 256-byte aligned."""
+    up = lambda x: (x + 255) // 256 * 256
+    parts = (I + 63) // 64
+    return (up(4 * I * ((J + 3) // 4 * 4)) + 3 * up(8 * I) + 3 * up(8 * J) + up(8 * parts * J) + up(8 * parts) +
+            up(40 * parts) + 256)
+
+
+def test_team_memory_counts_in_the_budget(A):
+    """The exchange block of a request's team is part of what it holds, and a
+    request whose budget has no room for one is solved all the same."""
+    print("\n[case] exchange blocks within the server's budget", flush=True)
+    I, J = 3100, 130
+    C, a, b = instance(I, J, 8)
+    stage, own = 4 * I * J, slot_bytes(I, J)
+    with A.Server() as srv:
+        srv.submit(C, a, b, 0.002, 1e-300, 100000)
+        srv.progress()
+        assert srv.counts()[1] == 1 and srv.counts()[3] >= own + 2 * 8 * 8 * 512  # (replicas of v alone)
+        n0 = A.ot_assoc_device_allocations()
+        for _ in range(3):
+            srv.progress()
+        assert A.ot_assoc_device_allocations() == n0
+    tight = float(own + (stage + 255) // 256 * 256)
+    for budget, st in ((tight, A.OT_OK), (tight - 256, A.OT_ENOMEM)):
+        with A.Server(budget_bytes=budget) as srv:
+            for k in range(2):
+                srv.submit(C, a, b, 0.05, 1e-8, user_tag=k)
+            done = serve(srv, 2)
+            assert [c.result.status for c in done] == [st, st]
+            assert srv.counts()[3] == 0
