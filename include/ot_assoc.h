@@ -379,12 +379,13 @@ ot_status ot_assoc_time_sweep(ot_assoc *h, int32_t reps, int fp64, double *ms_pe
  * figures are read. Errors: OT_EINVAL for bad arguments, OT_EDEVICE. */
 ot_status ot_assoc_time_read(ot_assoc *h, const void *buf, size_t bytes, int32_t reps, double *ms_per_launch);
 
-/* (test hook) Makes the next cooperative FP32 launch started by the calling
- * thread withhold the new g at its `iteration`-th iteration (1-based; 0
+/* (test hook) Makes the next cooperative launch started by the calling
+ * thread withhold the new scalings at its `iteration`-th iteration (1-based; 0
  * cancels) and bound every wait at a few milliseconds, so that the waits
  * after it end by giving up: every workgroup then leaves the kernel normally
  * and that solve returns OT_EDEVICE ("gave up waiting") with no solution
- * held; the next solve on the handle runs as usual. For tests of the
+ * held (in a batch every instance of the launch gets that status); the next
+ * solve on the handle runs as usual. For tests of the
  * give-up path. Errors: OT_EINVAL for a negative iteration. */
 ot_status ot_assoc_test_hold_exchange(int32_t iteration);
 

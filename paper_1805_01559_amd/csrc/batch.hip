@@ -48,15 +48,19 @@ constexpr int kChunk = 8;  // iterations per captured chunk (even: list generati
 constexpr int64_t kTailItems = 256;  // at most this many items left: the chunk runs on the tail grids
 constexpr double kBatchStallBelow = 1e-7;  // FP32 sweeps are not trusted below this residual
 constexpr size_t kAlign = 256;
-// Iterations of one team launch. Batches: past any but the slowest instance,
-// and short enough that the longest list of a workgroup (kTeamLaunch instances
-// over 256 workgroups, at 6 us per iteration) ends far within the waits' bound.
+// Iterations of one team launch. Batches: past any but the slowest instance.
 // Servers: one progress call's share, about as long as the chunk of sweeps that
 // it takes the place of (8 iterations of 30 us and more), since requests that
 // arrive meanwhile wait for it; the next call goes on from its iterate.
 constexpr int kTeamCapBatch = 1024, kTeamCapServe = 64;
 static_assert(kTeamCapServe % 4 == 0, "a launch's zeroed slots carry the tag of iterations 0 modulo 4");
 constexpr size_t kTeamLaunch = 1024;  // instances of one launch
+// Modelled time (us) of one launch in which every instance runs to the cap, its
+// mean over the workgroups: instances past it go to a launch of their own. A
+// workgroup may wait that long for a member of its team that is still at an
+// earlier instance, and a wait gives up after kTeamSpin polls of about 0.9 us.
+constexpr double kTeamTime = 5e5;
+constexpr int kTeamSpin = 1 << 21;
 
 double now_s() {
     using namespace std::chrono;
@@ -461,6 +465,7 @@ namespace {
 struct TeamShape {
     int cls = 0, rpw = 0, nb = 0, ncl = 0;
     size_t lds = 0;
+    double cost() const { return 3.0 + (double)rpw * ncl / 800.0; }  // us per iteration: exchange, rows
 };
 
 bool team_shape(int64_t I, int J, int num_cu, int lds_max, TeamShape& t) {
@@ -818,10 +823,18 @@ ot_status BatchEngine::run_teams(const std::vector<int>& ks, int cap, std::vecto
     finished.clear();
     left.clear();
     if (open) open->clear();
-    for (size_t q = 0; q < ks.size(); q += kTeamLaunch)
-        if (ot_status st =
-                run_team_group(ks.data() + q, std::min(kTeamLaunch, ks.size() - q), cap, finished, left, open))
-            return st;
+    const int groups = std::min(num_cu, kMaxCoopGroups);
+    for (size_t q = 0, end = 0; q < ks.size(); q = end) {
+        double time = 0.0;
+        for (; end < ks.size() && end - q < kTeamLaunch; ++end) {
+            TeamShape t;
+            if (!team_shape(slots[ks[end]].I, slots[ks[end]].J, num_cu, lds_max, t)) continue;
+            const double more = t.cost() * t.nb / groups * cap;
+            if (time > 0.0 && time + more > kTeamTime) break;
+            time += more;
+        }
+        if (ot_status st = run_team_group(ks.data() + q, end - q, cap, finished, left, open)) return st;
+    }
     if (left.empty()) return OT_OK;
     for (int q = 0; q < 2; ++q)  // (relay_h is idle: its last reader was waited for)
         if (ot_status st = wait_staging(q)) return st;
@@ -874,6 +887,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
     if (!jobs.empty()) {
         // the largest teams first (ties in request order)
         std::stable_sort(jobs.begin(), jobs.end(), [](const Entry& a, const Entry& b) { return a.t.nb > b.t.nb; });
+        const int hold = otk_host::take_test_hold();
         TeamJob* jh = (TeamJob*)team_h;
         int2* ih = (int2*)(team_h + jobs_b);
         int* sh = (int*)(team_h + jobs_b + items_b);
@@ -893,7 +907,8 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             A.Jp = e.t.ncl * team_lpr(e.t.cls);
             A.ncl = e.t.ncl;
             A.rpw = e.t.rpw;
-            A.max_spin = 1 << 21;
+            A.max_spin = hold ? 1 << 12 : kTeamSpin;
+            A.hold_iter = hold;
             A.stall_below = kBatchStallBelow;
             A.a = sl.d.a;
             A.b = sl.d.b;
@@ -914,8 +929,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             // the nb workgroups with the least work so far, the first of
             // `order` (an instance starts when its last member is free);
             // they then go behind all with no more work than theirs
-            const double cost = 3.0 + (double)e.t.rpw * e.t.ncl / 800.0;  // us per iteration: exchange, rows
-            const double at = load[order[e.t.nb - 1]] + cost;
+            const double at = load[order[e.t.nb - 1]] + e.t.cost();
             for (int r = 0; r < e.t.nb; ++r) {
                 load[order[r]] = at;
                 lists[order[r]].push_back(int2{(int)q, r});
@@ -1403,7 +1417,8 @@ ot_status ot_assoc_solve_batch(ot_assoc* h, int n, const ot_cost_desc* costs, co
         else if (r.status > 0 && worst == OT_OK) worst = (ot_status)r.status;
     }
     e->tab_order = ks;
-    if (worst < 0) h->err = "an instance of the batch failed numerically";
+    if (worst < 0)
+        h->err = worst == OT_EDEVICE ? "a wait of an instance's team gave up" : "an instance of the batch failed numerically";
     return worst;
 }
 

@@ -22,6 +22,8 @@ struct GraphEntry {
 // (ot_assoc_device_allocations reports the count).
 hipError_t dev_malloc(void** p, size_t bytes);
 hipError_t dev_free(void* p);
+// The calling thread's pending ot_assoc_test_hold_exchange (0: none), cleared.
+int take_test_hold();
 }  // namespace otk_host
 
 // Constants of the geometry cost functor (relative gains, log2-domain

@@ -154,6 +154,11 @@ hipError_t dev_malloc(void** p, size_t bytes) {
     return e;
 }
 hipError_t dev_free(void* p) { return hipFree(p); }
+int take_test_hold() {
+    const int k = g_test_hold;
+    g_test_hold = 0;
+    return k;
+}
 }  // namespace otk_host
 
 
@@ -740,12 +745,8 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.ncl = p.ncl;
     A.rpw = p.rpw;
     A.max_spin = 1 << 20;  // polls of at least ~1 us each: ~1 s before a wait gives up
-    if (g_test_hold > 0) {
-        // (test hook, one launch): withhold g at that iteration; waits give up after ~5 ms
-        A.hold_iter = g_test_hold;
-        A.max_spin = 1 << 12;
-        g_test_hold = 0;
-    }
+    A.hold_iter = otk_host::take_test_hold();
+    if (A.hold_iter > 0) A.max_spin = 1 << 12;  // (test hook, one launch: waits give up after ~5 ms)
     A.stall_below = stall_below;
     A.a = h->a;
     A.b = h->b;

@@ -242,3 +242,37 @@ def test_team_memory_counts_in_the_budget(A):
             done = serve(srv, 2)
             assert [c.result.status for c in done] == [st, st]
             assert srv.counts()[3] == 0
+
+
+def test_batch_wait_that_gives_up(A):
+    """Scalings withheld at the third iteration: every team ends by giving up,
+    the error says so, and the next batch on the handle runs as usual."""
+    print("\n[case] teams whose waits give up", flush=True)
+    xs = [instance(I, J, I) for I, J in ((200, 20), (3000, 60), (6000, 300))]
+    args = [[x[q] for x in xs] for q in range(3)]
+    with A.Solver(16, 16, batch_tune=0) as s:
+        assert A.ot_assoc_test_hold_exchange(3) == A.OT_OK
+        with pytest.raises(A.OTError, match="gave up") as e:
+            s.solve_batch(*args, 0.05, 1e-8)
+        assert e.value.status == A.OT_EDEVICE
+        st, res = s.solve_batch(*args, 0.05, 1e-8)
+        assert st == A.OT_OK and all(r.marginal_violation < 1e-8 for r in res)
+
+
+def test_batch_of_several_launches(A):
+    """More instances than one launch takes (1024), and instances whose teams
+    would keep one launch too long: the same results as alone, bit for bit."""
+    import torch
+    print("\n[case] batches of several team launches", flush=True)
+    for n, I, J, picks in ((1100, 120, 20, (0, 1023, 1024, 1099)), (400, 8000, 400, (0, 170, 399))):
+        C, a, b = (torch.from_numpy(x).cuda() for x in instance(I, J, 11))
+        eps = np.linspace(0.05, 0.08, n)
+        with A.Solver(16, 16, batch_tune=0) as s:
+            st, res = s.solve_batch([C] * n, [a] * n, [b] * n, eps, 1e-6)
+            assert st == A.OT_OK and all(r.marginal_violation < 1e-6 for r in res)
+            got = [s.batch_potentials(k) for k in picks]
+        with A.Solver(16, 16, batch_tune=0) as s:
+            for k, (f, g) in zip(picks, got):
+                s.solve_batch([C], [a], [b], [eps[k]], 1e-6)
+                f1, g1 = s.batch_potentials(0)
+                assert np.array_equal(f, f1) and np.array_equal(g, g1)
