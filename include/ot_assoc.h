@@ -397,6 +397,16 @@ ot_status ot_assoc_test_hold_exchange(int32_t iteration);
  * (see ot_assoc_result.flags). */
 ot_status ot_assoc_fast_phase_time(ot_assoc *h, double *ms, int32_t *iterations);
 
+/* (instrumentation) How the iterations of the last successful solve ran: in
+ * sweeps, or as one cooperative launch with the stabilised kernel in LDS
+ * (OT_RESULT_PERSISTENT), streamed from device memory, or in FP64.
+ * Errors: OT_ESTATE before a successful solve. */
+#define OT_FORM_SWEEPS 0
+#define OT_FORM_LDS 1
+#define OT_FORM_STREAMED 2
+#define OT_FORM_FP64 3
+ot_status ot_assoc_solve_form(ot_assoc *h, int32_t *form);
+
 /* (instrumentation) Number of device allocations (hipMalloc) the library has
  * made in this process so far, over all handles and engines: a caller that
  * passes a workspace can check that its solves allocate nothing. */
@@ -451,6 +461,10 @@ ot_status ot_assoc_solve_batch(ot_assoc *h, int n, const ot_cost_desc *costs, co
  * batch_tune is set): waves per FP32 sweep workgroup and rows per work item.
  * OT_ESTATE before any batch. */
 ot_status ot_assoc_batch_config(ot_assoc *h, int *waves, int *rows_per_part);
+
+/* (instrumentation) Instances of the last batch that teams solved to the end
+ * (the others took sweeps). OT_ESTATE before any batch. */
+ot_status ot_assoc_batch_teams(ot_assoc *h, int32_t *instances);
 
 /* Potentials (f: I, g: J, FP64) of instance k of the last batch, into host or
  * device memory. OT_ESTATE before a batch, OT_EINVAL for a bad k. */
@@ -550,6 +564,8 @@ ot_status ot_serve_submit(ot_serve *s, const ot_request *req, uint64_t *ticket);
 ot_status ot_serve_progress(ot_serve *s, ot_completion *out, int max_out, int *n_out);
 /* Requests queued / in flight, resident potential sets, device bytes held. */
 ot_status ot_serve_counts(const ot_serve *s, int *queued, int *running, int *resident, double *bytes_in_use);
+/* (instrumentation) Requests that teams have solved to the end so far. */
+ot_status ot_serve_teams(const ot_serve *s, int64_t *requests);
 /* Resident potentials of a layout (f: I, g: J), into host or device memory. */
 ot_status ot_serve_potentials(ot_serve *s, uint64_t layout_key, double *f, double *g, ot_mem mem);
 /* The clock of the completion timestamps. */

@@ -280,6 +280,7 @@ struct BatchEngine {
     char *team_h = nullptr, *team_d = nullptr;
     size_t team_cap = 0;
     Ctl* team_ctl = nullptr;
+    int64_t teams_done = 0;  // instances that teams solved to the end
     ot_status run_teams(const std::vector<int>& ks, int cap, std::vector<int>& finished, std::vector<int>& left,
                         std::vector<int>* open = nullptr);
     bool team_reserve(size_t bytes);
@@ -972,6 +973,7 @@ ot_status BatchEngine::run_team_group(const int* ks, size_t n, int cap, std::vec
             --n_live_running;
             items_running -= s.parts_cap;
             finished.push_back(ks[q]);
+            if (teamed) ++teams_done;
         } else if (open && teamed && c.phase == kPhFast) {
             open->push_back(ks[q]);
         } else {
@@ -1340,6 +1342,7 @@ ot_status ot_assoc_solve_batch(ot_assoc* h, int n, const ot_cost_desc* costs, co
     BatchEngine* e = h->batch;
     e->err.clear();
     e->polish_iters = std::max(0, h->opt.polish_iters);
+    e->teams_done = 0;
     // the previous batch's instances are released first
     if (e->n_live_running > 0) {
         h->err = "a batch is still running on this handle";
@@ -1431,6 +1434,17 @@ ot_status ot_assoc_batch_config(ot_assoc* h, int* waves, int* rows_per_part) {
     }
     if (waves) *waves = h->batch->waves;
     if (rows_per_part) *rows_per_part = (int)h->batch->rpp_rows;
+    return OT_OK;
+}
+
+ot_status ot_assoc_batch_teams(ot_assoc* h, int32_t* instances) {
+    if (!h || !instances) return OT_EINVAL;
+    h->err.clear();
+    if (!h->batch) {
+        h->err = "no batch has run on this handle";
+        return OT_ESTATE;
+    }
+    *instances = (int32_t)h->batch->teams_done;
     return OT_OK;
 }
 
@@ -1806,6 +1820,12 @@ ot_status ot_serve_counts(const ot_serve* s, int* queued, int* running, int* res
     if (running) *running = (int)s->running.size();
     if (resident) *resident = (int)s->resident.size();
     if (bytes_in_use) *bytes_in_use = (double)s->eng.pool.in_use;
+    return OT_OK;
+}
+
+ot_status ot_serve_teams(const ot_serve* s, int64_t* requests) {
+    if (!s || !requests) return OT_EINVAL;
+    *requests = s->eng.teams_done;
     return OT_OK;
 }
 

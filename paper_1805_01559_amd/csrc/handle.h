@@ -66,7 +66,7 @@ struct ot_assoc {
     int lds_max = 0;           // LDS bytes a workgroup may allocate
     bool xch_zeroed = false;       // this solve's init launch zeroed the exchange block
     bool stop_recorded = false;    // ev_stop was recorded with the last control-block copy
-    bool last_persistent = false;  // the last solve's FP32 phase was one cooperative launch
+    int last_form = OT_FORM_SWEEPS;  // how the last solve's iterations ran
     int last_fast_iters = 0;       // ... and the FP32 iterations it ran
     hipEvent_t ev_coop[2] = {nullptr, nullptr};  // around that launch
     float* xy_dev = nullptr;  // I_max x 2

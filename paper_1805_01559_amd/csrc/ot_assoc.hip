@@ -852,7 +852,7 @@ ot_status solve_with(ot_assoc* h, const Src& src, const void* data, int64_t I, i
     }
     if (coop && !(checked && (c.done || c.chk_violation < tol || c.iter >= max_iter)))
         if ((st = run_persist<Src>(h, src, I, J, pp, stall_below, persisted))) return st;
-    h->last_persistent = persisted && !pp.gm && !f64;
+    h->last_form = !persisted ? OT_FORM_SWEEPS : f64 ? OT_FORM_FP64 : pp.gm ? OT_FORM_STREAMED : OT_FORM_LDS;
     if (persisted) {  // the launch has checked its iterate (one host wait)
         h->validate_pending = false;
         if ((st = S.snapshot(0)) || (st = S.wait(0))) return st;
@@ -1265,7 +1265,7 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
         out->iterations = result_iter;
         out->fp64_iterations = fin.fp64_iters;
         out->status = rs;
-        out->flags = h->last_persistent ? OT_RESULT_PERSISTENT : 0;
+        out->flags = h->last_form == OT_FORM_LDS ? OT_RESULT_PERSISTENT : 0;
         out->marginal_violation = fin.chk_violation;
         out->objective = fin.chk_objective;
         out->reg_objective = fin.chk_reg_objective;
@@ -1532,13 +1532,22 @@ ot_status ot_assoc_fast_phase_time(ot_assoc* h, double* ms, int32_t* iterations)
     if (!h) return OT_EINVAL;
     h->err.clear();
     if (!ms || !iterations) return fail(h, OT_EINVAL, "output pointer is NULL");
-    if (!h->solved || !h->last_persistent)
+    if (!h->solved || h->last_form != OT_FORM_LDS)
         return fail(h, OT_ESTATE, "the last solve did not run the cooperative FP32 phase");
     float t = 0.0f;
     HIPCHK(h, hipEventSynchronize(h->ev_coop[1]));
     HIPCHK(h, hipEventElapsedTime(&t, h->ev_coop[0], h->ev_coop[1]));
     *ms = (double)t;
     *iterations = h->last_fast_iters;
+    return OT_OK;
+}
+
+ot_status ot_assoc_solve_form(ot_assoc* h, int32_t* form) {
+    if (!h) return OT_EINVAL;
+    h->err.clear();
+    if (!form) return fail(h, OT_EINVAL, "output pointer is NULL");
+    if (!h->solved) return fail(h, OT_ESTATE, "no successful solve");
+    *form = h->last_form;
     return OT_OK;
 }
 

@@ -28,6 +28,7 @@ OT_F32, OT_F64 = 0, 1
 OT_PREC_FP32, OT_PREC_FP64 = 0, 1
 OT_RESULT_PERSISTENT = 1
 OT_RESULT_CHECK_ABOVE_TOL = 2
+OT_FORM_SWEEPS, OT_FORM_LDS, OT_FORM_STREAMED, OT_FORM_FP64 = 0, 1, 2, 3
 
 # every symbol include/ot_assoc.h declares
 EXPORTS = [
@@ -35,7 +36,8 @@ EXPORTS = [
     "ot_assoc_solve_static", "ot_assoc_solve", "ot_assoc_plan", "ot_assoc_set_plan_output", "ot_assoc_potentials",
     "ot_assoc_set_potentials", "ot_assoc_cost_median", "ot_assoc_materialize_cost", "ot_assoc_time_sweep", "ot_assoc_time_read",
     "ot_assoc_test_hold_exchange",
-    "ot_assoc_fast_phase_time", "ot_assoc_rrh_loads", "ot_assoc_evaluate", "ot_assoc_maxsinr", "ot_assoc_adaptive",
+    "ot_assoc_fast_phase_time", "ot_assoc_solve_form", "ot_assoc_batch_teams", "ot_serve_teams",
+    "ot_assoc_rrh_loads", "ot_assoc_evaluate", "ot_assoc_maxsinr", "ot_assoc_adaptive",
     "ot_assoc_destroy", "ot_assoc_last_error", "ot_assoc_solve_batch", "ot_assoc_batch_config",
     "ot_assoc_batch_potentials", "ot_assoc_solve_snapshots", "ot_assoc_snapshot_potentials",
     "ot_assoc_batch_plan", "ot_serve_default_options", "ot_serve_create", "ot_serve_submit", "ot_serve_progress",
@@ -129,6 +131,9 @@ def lib():
         L.ot_assoc_time_read.argtypes = [vp, vp, ct.c_size_t, ct.c_int32, ct.POINTER(d)]
         L.ot_assoc_test_hold_exchange.argtypes = [ct.c_int32]
         L.ot_assoc_fast_phase_time.argtypes = [vp, ct.POINTER(d), ct.POINTER(ct.c_int32)]
+        L.ot_assoc_solve_form.argtypes = [vp, ct.POINTER(ct.c_int32)]
+        L.ot_assoc_batch_teams.argtypes = [vp, ct.POINTER(ct.c_int32)]
+        L.ot_serve_teams.argtypes = [vp, ct.POINTER(i64)]
         L.ot_assoc_rrh_loads.argtypes = [vp, vp, ct.c_int]
         L.ot_assoc_evaluate.argtypes = [vp, d, d, vp, vp, ct.c_int, ct.POINTER(ot_eval_result)]
         L.ot_assoc_maxsinr.argtypes = [vp, ct.POINTER(ot_cost_desc), vp, vp, vp]
@@ -276,6 +281,20 @@ def ot_assoc_fast_phase_time(h):
     return ms.value, it.value
 
 
+def ot_assoc_solve_form(h) -> int:
+    """OT_FORM_* of the last successful solve."""
+    form = ct.c_int32()
+    _check(h, lib().ot_assoc_solve_form(h, ct.byref(form)))
+    return form.value
+
+
+def ot_assoc_batch_teams(h) -> int:
+    """Instances of the last batch that teams solved to the end."""
+    n = ct.c_int32()
+    _check(h, lib().ot_assoc_batch_teams(h, ct.byref(n)))
+    return n.value
+
+
 def ot_assoc_destroy(h):
     if h:
         lib().ot_assoc_destroy(h)
@@ -361,6 +380,13 @@ def ot_serve_counts(s):
     q, r, k, b = ct.c_int(), ct.c_int(), ct.c_int(), ct.c_double()
     _scheck(s, lib().ot_serve_counts(s, ct.byref(q), ct.byref(r), ct.byref(k), ct.byref(b)))
     return q.value, r.value, k.value, b.value
+
+
+def ot_serve_teams(s) -> int:
+    """Requests that teams have solved to the end so far."""
+    n = ct.c_int64()
+    _scheck(s, lib().ot_serve_teams(s, ct.byref(n)))
+    return n.value
 
 
 def ot_serve_potentials(s, key, f_ptr, g_ptr, mem):

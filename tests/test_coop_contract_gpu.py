@@ -240,7 +240,7 @@ def test_team_memory_counts_in_the_budget(A):
             for k in range(2):
                 srv.submit(C, a, b, 0.05, 1e-8, user_tag=k)
             done = serve(srv, 2)
-            assert [c.result.status for c in done] == [st, st]
+            assert [c.result.status for c in done] == [st, st] and A.ot_serve_teams(srv.s) == 0
             assert srv.counts()[3] == 0
 
 
