@@ -64,7 +64,6 @@ struct ot_assoc {
     double* xch = nullptr;     // exchange block of the cooperative FP32 phase
     double* loads = nullptr;   // J_max: RRH loads summed by the last check (when fused)
     int lds_max = 0;           // LDS bytes a workgroup may allocate
-    bool xch_zeroed = false;       // this solve's init launch zeroed the exchange block
     bool stop_recorded = false;    // ev_stop was recorded with the last control-block copy
     int last_form = OT_FORM_SWEEPS;  // how the last solve's iterations ran
     int last_fast_iters = 0;       // ... and the FP32 iterations it ran

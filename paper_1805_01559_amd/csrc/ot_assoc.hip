@@ -767,14 +767,6 @@ ot_status run_persist(ot_assoc* h, const Src& src, int64_t I, int J, const Persi
     A.plan_f64 = h->plan_dtype == OT_F64 ? 1 : 0;
     h->loads_fresh = A.loads != nullptr;
     h->plan_fresh = A.plan_out != nullptr;
-    // (the solve's init launch has zeroed the exchange block, unless it
-    // could not know that this launch would follow)
-    if (!h->xch_zeroed) {
-        const size_t nx = persist_exchange_doubles(p.nb, J);
-        hipLaunchKernelGGL(k_xch_clear, dim3((unsigned)std::min<size_t>(512, (nx + 255) / 256)), dim3(256), 0,
-                           h->stream, h->xch, p.nb, J, h->ctl);
-    }
-    h->xch_zeroed = false;
     Src sv = src;
     void* args[] = {(void*)&A, (void*)&sv};
     if (h->ev_coop[0]) HIPCHK(h, hipEventRecord(h->ev_coop[0], h->stream));
@@ -1195,13 +1187,11 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
     ia.groups = I <= kInitSingle ? 1 : (int)std::min<int64_t>(kInitGroups, (I + 4095) / 4096);
     ia.part = h->stat_part;  // (written by checks only, behind this launch)
     unsigned init_groups = (unsigned)ia.groups;
-    h->xch_zeroed = false;
     h->stop_recorded = false;
     if (h->opt.persistent && h->xch && h->num_cu > 0) {
         ia.xch = h->xch;
         ia.nx = (int64_t)persist_exchange_doubles(std::min(h->num_cu, kMaxCoopGroups), (int)J);
         init_groups += (unsigned)std::min<int64_t>(32, (ia.nx + 4095) / 4096);
-        h->xch_zeroed = true;
     }
     hipLaunchKernelGGL(k_solve_init, dim3(init_groups), dim3(1024), 0, h->stream, ia);
     if (ia.groups > 1) hipLaunchKernelGGL(k_solve_init_fin, dim3(1), dim3(256), 0, h->stream, ia);
@@ -1221,7 +1211,6 @@ static ot_status solve_impl(ot_assoc* h, const ot_cost_desc* cost, const double*
         return st;
     }
     float ms = 0.0f;
-    h->xch_zeroed = false;
     if (h->ev_start) {
         if (!h->stop_recorded) HIPCHK(h, hipEventRecord(h->ev_stop, h->stream));
         HIPCHK(h, hipEventSynchronize(h->ev_stop));

@@ -1186,21 +1186,6 @@ __global__ __launch_bounds__(WAVES * kWave) void k_persist(PersistArgs A, Src sr
     persist_run<Src, CPL, LPR, WAVES, GM, false, F64>(A, src, (int)gridDim.x, (int)blockIdx.x, ps);
 }
 
-// Prepares the exchange block and clears the stop flag before a persistent
-// launch (grid-stride; any grid): every exchanged slot gets the tag of
-// iteration k0 + 3, which neither of the first two iterations (k0 + 1,
-// k0 + 2, one per buffer parity) waits for; decision and abort words start at
-// zero.
-static __global__ void k_xch_clear(double* xch, int nb, int J, Ctl* ctl) {
-    const XchLayout X = persist_xch_layout(nb, J);
-    const int k0 = ctl->iter;
-    const double empty = tag_value(0.0, k0 + 3);
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < X.total; q += stride)
-        xch[q] = q < X.dec ? empty : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->stop = 0;
-}
-
 // ------------------------------------------------------------ solve set-up --
 // Checks the marginals (positive and finite, equal masses), copies them into
 // the solver's buffers, zeroes g for a cold start and writes the solve
