@@ -276,3 +276,55 @@ def test_batch_of_several_launches(A):
                 s.solve_batch([C], [a], [b], [eps[k]], 1e-6)
                 f1, g1 = s.batch_potentials(0)
                 assert np.array_equal(f, f1) and np.array_equal(g, g1)
+
+
+def test_solver_batch_and_server_in_threads(A):
+    """Cooperative launches of three handles, each on its own stream and thread:
+    the same results as one after the other, bit for bit."""
+    import threading
+    import torch
+    print("\n[case] solver, batch and server side by side", flush=True)
+    xs = [tuple(torch.from_numpy(x).cuda() for x in instance(I, J, I)) for I, J in ((9000, 300), (700, 40), (3000, 130))]
+
+    def single(n):
+        with A.Solver(9000, 300) as s:
+            for _ in range(n):
+                st, res = s.solve_dense(*xs[0], 0.05, 1e-8)
+                assert st == A.OT_OK
+            return s.potentials()
+
+    def batch(n):
+        with A.Solver(16, 16, batch_tune=0) as s:
+            for _ in range(n):
+                st, _ = s.solve_batch(*([x[q] for x in xs] for q in range(3)), 0.05, 1e-8)
+                assert st == A.OT_OK and A.ot_assoc_batch_teams(s.h) == 3
+            return sum((s.batch_potentials(k) for k in range(3)), ())
+
+    def server(n):
+        with A.Server() as srv:
+            for k in range(n):
+                for x in xs[:2]:
+                    srv.submit(*x, 0.05, 1e-8, 2000)
+                srv.submit(*xs[2], 0.05, 1e-8, 2000, layout_key=k + 1)
+                assert all(c.result.status == A.OT_OK for c in serve(srv, 3))
+            return srv.potentials(n, 3000, 130)
+
+    jobs = (single, batch, server)
+    want = [job(1) for job in jobs]
+    got = [None] * 3
+    torch.cuda.synchronize()
+
+    def work(k):
+        try:
+            got[k] = jobs[k](40)
+        except Exception as e:  # (reported by the comparison below)
+            got[k] = e
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for x, y in zip(want, got):
+        assert not isinstance(y, Exception), y
+        assert all(np.array_equal(p, q) for p, q in zip(x, y))
