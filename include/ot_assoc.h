@@ -131,7 +131,8 @@ typedef struct {
                            another is 3 % faster; the choice is cached for the process and, when
                            the environment variable OT_ASSOC_TUNE_CACHE names a file, read from
                            and appended to it, so a later process takes it without timing (a
-                           batch's results are bitwise reproducible for one choice); 0 uses 8, 128 */
+                           batch's results are bitwise reproducible for one choice); 0 uses 8, 128.
+                           With `persistent` only instances that teams leave to sweeps run in it */
     int persistent;     /* ot_assoc_solve: 1 (default) runs iterations, exact check and plan as one
                            cooperative launch whose stabilised kernel is held in LDS when it fits
                            (FP32: about I * J <= 9.8e6 cells on 256 CUs; every cost but FP64
@@ -152,11 +153,13 @@ typedef struct {
                            maxSINR and Alg. 2 calls and the timers) is carved from it, so those
                            calls allocate no device memory; bytes beyond the required size stage
                            host-memory DENSE / RATES matrices (a host matrix that does not fit
-                           gives OT_ENOMEM) and hold the FP64 cost of a GEOMETRY solve (8 I J bytes;
-                           where it does not fit, every pass regenerates it). NULL (default): the
-                           library allocates one block of that size itself, and those two on
-                           demand. The batch, snapshot and serving engines keep their own device
-                           pools either way. */
+                           gives OT_ENOMEM), hold the FP64 cost of a GEOMETRY solve (8 I J bytes;
+                           where it does not fit, every pass regenerates it) and behind either
+                           the kernel of a solve too large for LDS (4 I J bytes, J rounded up to
+                           4; else it runs in sweeps) or the blocks of a plan to host memory
+                           (else through the work region). NULL (default): the library allocates
+                           one block of that size itself, and those on demand. The batch,
+                           snapshot and serving engines keep their own device pools either way. */
     size_t workspace_bytes; /* size of `workspace` (0 when workspace is NULL) */
     int snapshot_k_split;   /* ot_assoc_solve_snapshots: 1 (default) holds the stabilised kernel
                                in BF16 high and low parts (three BF16 products per GEMM step,
@@ -198,10 +201,12 @@ ot_status ot_assoc_workspace_size(int64_t I_max, int64_t J_max, size_t *bytes);
 /* Creates a handle able to solve instances up to I_max x J_max on
  * opt->device (opt NULL = defaults). Takes its device buffers from
  * opt->workspace when given, else allocates one block of
- * ot_assoc_workspace_size() bytes, plus (only without a caller workspace) an
- * I x ld staging matrix when a host-memory dense or rate cost is later passed
- * and the 8 I J bytes of a geometry solve's cost (at most half of the memory
- * free at that time; else the cost is regenerated in every pass).
+ * ot_assoc_workspace_size() bytes, plus (only without a caller workspace) on
+ * demand, kept until ot_assoc_destroy: an I x ld staging matrix when a host-memory
+ * dense or rate cost is passed; the 8 I J bytes of a geometry solve's cost; and one
+ * buffer for the 4 I J bytes (J rounded up to 4) of a kernel too large for LDS and for
+ * up to 64 MB of a plan to host memory. The last two take at most half of the
+ * memory free at that time each; else the solve or call does without.
  * Errors: OT_EINVAL (I_max or J_max out of range, a workspace that is too
  * small or misaligned, check_every < 0), OT_ENOMEM, OT_EDEVICE. */
 ot_status ot_assoc_create(ot_assoc **h, int64_t I_max, int64_t J_max, const ot_assoc_options *opt);
@@ -299,9 +304,9 @@ ot_status ot_assoc_materialize_cost(ot_assoc *h, const ot_cost_desc *cost, float
 
 /* Per-RRH load of the last successful solve's plan: load_j = sum_i C_ij x_ij
  * in FP64 (the FP64 cost, x = exp((f + g - C)/eps)). loads: J doubles in
- * `mem`. After ot_assoc_adaptive (J <= 416, or 512 without the cooperative launch) the loads were summed by the
- * solves' final exact checks and are copied out; otherwise they take one
- * pass over the cost. Errors: OT_ESTATE before a successful solve (or after
+ * `mem`. After ot_assoc_adaptive (J <= 416, or 512 without the cooperative
+ * launch) the loads were summed by the solves' final exact checks and are
+ * copied out; otherwise they take one pass over the cost. Errors: OT_ESTATE before a successful solve (or after
  * a call that replaced the handle's cost). */
 ot_status ot_assoc_rrh_loads(ot_assoc *h, double *loads, ot_mem mem);
 

@@ -1703,7 +1703,7 @@ ot_status ot_assoc_maxsinr(ot_assoc* h, const ot_cost_desc* cost, const double* 
     h->solved = h->loads_valid = h->plan_valid = false;  // the handle's retained cost is replaced below
     HIPCHK(h, hipMemcpyAsync(h->a, ah.data(), sizeof(double) * I, hipMemcpyHostToDevice, h->stream));
     if ((st = upload_cost(h, cost, kCheckNow))) return st;
-    // rows per workgroup: a multiple of the 64-row chunk, at most kMaxNb workgroups
+    // rows per workgroup: a multiple of the rule's row chunk, at most kMaxNb workgroups
     int64_t rpb = std::max<int64_t>(kMaxsinrRows, (I + kMaxNb - 1) / kMaxNb);
     rpb = (rpb + kMaxsinrRows - 1) / kMaxsinrRows * kMaxsinrRows;
     const int nb = (int)((I + rpb - 1) / rpb);
@@ -1755,7 +1755,8 @@ ot_status ot_assoc_adaptive(ot_assoc* h, const ot_cost_desc* cost, const double*
     double* fb = q_d + h->J_max;
     double* gb = fb + h->I_max;
     auto release = [&]() {};
-    // the solves' final checks also sum the RRH loads (J <= 512), so that
+    // the solves' final checks also sum the RRH loads (up to 416 columns in the cooperative launch, 512
+    // in sweeps), so that
     // reading them needs no pass over the cost of its own
     struct WantLoads {
         ot_assoc* h;

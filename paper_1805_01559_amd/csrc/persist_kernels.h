@@ -38,11 +38,11 @@
 // What bounds it: the exchange. With the cost in LDS and an exponential per cell
 // the row update alone took 4.8 us of the 9.6 us per iteration at 20000 x 400;
 // now an iteration takes 5.8 us, 1.7 of them the row update. The whole solve
-// with its plan went 577 -> 400 us, and the distance cost at that size (about
-// 1250 iterations, 200 of them FP64 sweeps before) 15.7 -> 6.5 ms.
+// with its plan went 590 -> 436 us, and the distance cost at that size (about
+// 1250 iterations, 200 of them FP64 sweeps before) 16.3 -> 7.6 ms.
 //
 // Only O(I + J) scalings and O(nb J) partials move per iteration; the I x J cost
-// is read two or three times per launch instead of once per iteration.
+// is read two to four times per launch instead of once per iteration.
 //
 // Exchange without fences or barriers. On this GPU the L2 of an XCD is not
 // coherent with the other XCDs' L2s, and an agent-scope release writes a
@@ -232,13 +232,14 @@ enum : int { kItRef = 0, kItPlain = 1, kItRefDelta = 2, kItDelta = 3 };
 constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2, kDecSkip = 4;
 // Delta sums begin once the residual is below this: the scalings
 // then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
-// residuals down to about 1e-12, far below the FP32 noise (4e-8) of the plain
+// residuals down to about 1e-12, far below the FP32 noise (2e-8) of the plain
 // sums; an earlier switch would buy nothing, a later one comes too close to
 // that noise.
 constexpr double kDeltaBelow = 1e-5;
 // A reference for plain sums is renewed when a scaling leaves [2^-40, 2^40]: an entry
 // flushed to zero in FP32 (below 2^-126 of its row's largest) then stands for
-// less than 2^-46 of any row or column sum.
+// less than 2^-46 of its row's sum, and for 2^-46 a_i of the sum of its column, so
+// that all of them together move the column sums by less than 2^-46 of the mass.
 constexpr double kScaleMax = 0x1p40;
 // The final check sums RRH loads up to this many cells per lane (416 columns):
 // the second set of FP64 column sums takes wider rows past the registers.
@@ -256,8 +257,8 @@ constexpr double kDeltaMax = 0.125;
 //
 // The solve then ends, as one in sweeps does, with `polish` FP64 iterations,
 // unless its residual met a target above the noise: iterations that take a
-// reference, whose exponentials and sums are FP64 throughout. (One costs 5 % of a
-// solve of 20000 x 400.) `polishing` counts those still to come.
+// reference, whose exponentials and sums are FP64 throughout (one costs 25 us at
+// 20000 x 400, 5 % of a solve). `polishing` counts those still to come.
 __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, int polish,
                                              int& polishing, double& r_ref, int& k_ref) {
     const int k = c->iter + 1;
@@ -327,8 +328,8 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
 // references take FP64 exponentials, and the stop rule is that of the
 // FP64 sweeps: the iterate before the one just computed is returned once its
 // residual is below tol. Bound by the exchange, too: a solve of 2999 x 197 with
-// 72 iterations takes 324 us, with a sweep and a fold launch per iteration
-// (7.2 + 4.3 us) it took 969.
+// 72 iterations takes 351 us, with a sweep and a fold launch per iteration
+// (7.2 + 4.3 us) it took 1038.
 template <class Src, int CPL, int LPR, int WAVES, bool GM, bool LEAN = false, bool F64 = false>
 __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src, const int nb, const int blk,
                                             PersistShared& ps) {

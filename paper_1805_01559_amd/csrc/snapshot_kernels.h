@@ -579,8 +579,7 @@ __global__ void k_snap_all_potentials(SnapArgs S, const double* fbar, const doub
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // A lane's four cells (i, j) of the stabilised kernel in FP64, with C Kbar:
-// step moves from one to the next (di, dj); outside the instance both are 0,
-// and so is the product of a cell whose kernel entry is 0 (an infinite cost).
+// step moves from one to the next (di, dj); outside the instance both are 0.
 __device__ __forceinline__ void snap_cells(const float* C, int64_t ldc, int64_t I, int J, int64_t i, int j, int di,
                                            int dj, const double* fbar, const double* gbar, double kk,
                                            const double* tab, double (&p)[4], double (&cp)[4]) {
