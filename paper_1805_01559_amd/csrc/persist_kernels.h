@@ -258,20 +258,20 @@ constexpr double kDeltaMax = 0.125;
 // The solve then ends, as one in sweeps does, with `polish` FP64 iterations,
 // unless its residual met a target above the noise: iterations that take a
 // reference, whose exponentials and sums are FP64 throughout (one costs 25 us at
-// 20000 x 400, 5 % of a solve). `polishing` counts those still to come.
+// 20000 x 400, 5 % of a solve). polish_left counts those still to come.
 __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, double stall_below, int polish,
-                                             int& polishing, double& r_ref, int& k_ref) {
+                                             double& r_ref, int& k_ref) {
     const int k = c->iter + 1;
     const double r = c->has_prev ? rsum / c->mass : pinf64();
     const bool bad = c->numeric_bad || (c->has_prev && !isfinite(r));
     c->r_last = r;
     c->iter = k;
     c->has_prev = 1;
-    c->last_fp64 = polishing > 0 ? 1 : 0;
+    c->last_fp64 = c->polish_left > 0 ? 1 : 0;
     int code = 0;
-    if (polishing > 0) {
+    if (c->polish_left > 0) {
         c->fp64_iters += 1;
-        code = --polishing > 0 ? kDecRefDelta : kDecStop;
+        code = --c->polish_left > 0 ? kDecRefDelta : kDecStop;
     } else {
         const double target = c->tol_fast > 0.0 ? c->tol_fast : c->tol;
         const bool fine = kind == kItRefDelta || kind == kItDelta;  // residuals of delta sums
@@ -291,8 +291,8 @@ __device__ __forceinline__ int bookkeep_coop(Ctl* c, double rsum, int kind, doub
             code = kDecRefDelta;
         }
         if (at_check && (met || stall)) {
-            polishing = r < target && target >= stall_below ? 0 : polish;
-            code = polishing > 0 ? kDecRefDelta : kDecStop;
+            c->polish_left = r < target && target >= stall_below ? 0 : polish;
+            code = c->polish_left > 0 ? kDecRefDelta : kDecStop;
         }
     }
     if (k >= c->max_iter) code = kDecStop;
@@ -422,15 +422,16 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
     const int dblk = nb - 1;
     if (blk == dblk && tid == 0) cs = *ctl;
     double r_ref = ctl->r_last;  // (the deciding lane's)
-    int k_ref = k0, polishing = 0;
+    int k_ref = k0;
 
     const int steps = rpw / (WAVES * R);
     [[maybe_unused]] volatile int bad_before = 0;
     double res = 0.0;  // this lane's part of the row residual of the previous iterate
     int k = k0, kind = kItRef;
-    // (an instance that a launch before this one left in delta sums)
+    // (an instance that a launch before this one left in delta sums or in its polish)
     if constexpr (!F64)
-        if (k0 > 0 && ctl->r_last < kDeltaBelow && ctl->tol_fast < A.stall_below) kind = kItRefDelta;
+        if (k0 > 0 && (ctl->polish_left > 0 || (ctl->r_last < kDeltaBelow && ctl->tol_fast < A.stall_below)))
+            kind = kItRefDelta;
 
     // Row update of an iteration that takes a new reference G = g: the kernel
     // entries E_ij = 2^(t_ij - m_i), t_ij = (G_j - C_ij) kk, m_i about the row maximum,
@@ -831,9 +832,9 @@ __device__ __forceinline__ void persist_run(const PersistArgs& A, const Src& src
                         if (cs.done && !cs.numeric_bad) code |= kDecPrev;
                     }
                 } else if (lane == 0) {
-                    code = bookkeep_coop(&cs, r, kind, A.stall_below, A.polish, polishing, r_ref, k_ref);
+                    code = bookkeep_coop(&cs, r, kind, A.stall_below, A.polish, r_ref, k_ref);
                 }
-                if (lane == 0 && k - k0 >= A.cap && !(code & kDecStop) && polishing == 0) code = kDecStop | kDecSkip;
+                if (lane == 0 && k - k0 >= A.cap && !(code & kDecStop)) code = kDecStop | kDecSkip;
                 // (every workgroup's verdict on its rows of the matrix preceded its
                 // first partials)
                 if (lane == 0 && k == k0 + 1 && (A.validate || A.batch)) {

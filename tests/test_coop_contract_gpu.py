@@ -210,6 +210,26 @@ def test_progress_runs_a_bounded_share(A, oracle_lib):
         assert x[2] == y[2] and np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1])
 
 
+def test_a_long_polish_is_shared_out_too(A):
+    """150 FP64 iterations end a request over several progress calls, and one in
+    a batch in one call; both are what the option asks for."""
+    print("\n[case] polish_iters 150 in a server and a batch", flush=True)
+    x = instance(900, 70, 5)
+    with A.Server(polish_iters=150) as srv:
+        srv.submit(*x, 0.05, 1e-8, 2000)
+        calls, done = 1, srv.progress()
+        assert not done and srv.counts()[1] == 1
+        while not done:
+            done = srv.progress()
+            calls += 1
+        a = done[0].result
+        assert A.ot_serve_teams(srv.s) == 1
+    with A.Solver(16, 16, batch_tune=0, polish_iters=150) as s:
+        b = s.solve_batch(*([y] for y in x), 0.05, 1e-8, 2000)[1][0]
+    assert a.status == b.status == A.OT_OK and calls >= 3
+    assert a.fp64_iterations == b.fp64_iterations == 150 and a.iterations == b.iterations
+
+
 def slot_bytes(I, J):
     """A server request's own device memory: padded FP32 cost, marginals, two
     sets of potentials, sweep partials of 64 rows, each part 256-byte aligned."""
