@@ -58,7 +58,7 @@
 // workgroup's contribution of the iteration in between). The exchange is laid
 // out for the memory system: a producer's column partials are one contiguous
 // row (whole cache lines), the owner of eight consecutive columns reads whole
-// lines, and the new g and the stop decision are written in several replicas
+// lines, and the new v and the stop decision are written in several replicas
 // so that the 256 polling workgroups do not all wait on the same lines.
 // Every poll is bounded: a workgroup that waits too long sets an abort word
 // that releases every other poller, and the launch ends with its control
@@ -90,14 +90,14 @@ __device__ __forceinline__ double tag_value(double v, int k) {
 __device__ __forceinline__ bool has_tag(double v, int k) { return (__double_as_longlong(v) & 3) == (long long)(k & 3); }
 
 constexpr int kColBlock = 8;        // columns per owner block: one 64-byte line of doubles
-constexpr int kReplicas = 8;        // copies of the new g and of the decision word
+constexpr int kReplicas = 8;        // copies of the new v and of the decision word
 constexpr int kMaxCoopGroups = 256; // workgroups of a cooperative launch (an owner polls 4 per thread)
 
 // Layout of the exchange block (offsets in doubles, each part 64-byte aligned):
 //   part  [2][nb][Jp]      column partials by iteration parity; a producer's
 //                          row is contiguous, Jp = J rounded up to kColBlock
 //   rpart [2][nb]          row-residual partials by parity (padded to a line)
-//   gx    [2][kReplicas][Gs]  new g by parity, Gs = Jp rounded up to 512 (4 KiB
+//   gx    [2][kReplicas][Gs]  new v by parity, Gs = Jp rounded up to 512 (4 KiB
 //                          between replicas)
 //   dec   [2][kReplicas][8]   (iteration << 3) | decision code, as uint64, one line per replica
 //   abort [8]              uint64, nonzero once a poll gave up
@@ -227,8 +227,8 @@ __host__ __device__ inline size_t persist_lds_bytes(int rpw, int J, int Jp, int 
 // a reference taken for plain sums, plain sums, one taken for delta sums,
 // delta sums.
 enum : int { kItRef = 0, kItPlain = 1, kItRefDelta = 2, kItDelta = 3 };
-// Decision codes: bit 0 stop, bit 1 take a reference for delta sums next.
-// (in FP64: the iterate before is the returned one), bit 2 leave without the check.
+// Decision codes: bit 0 stop, bit 1 take a reference for delta sums next (in
+// FP64: the iterate before is the returned one), bit 2 leave without the check.
 constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2, kDecSkip = 4;
 // Delta sums begin once the residual is below this: the scalings
 // then stay within about 1e-5 / (1 - rate) of 1, so the FP32 delta sums resolve
@@ -238,8 +238,8 @@ constexpr int kDecStop = 1, kDecRefDelta = 2, kDecPrev = 2, kDecSkip = 4;
 constexpr double kDeltaBelow = 1e-5;
 // A reference for plain sums is renewed when a scaling leaves [2^-40, 2^40]: an entry
 // flushed to zero in FP32 (below 2^-126 of its row's largest) then stands for
-// less than 2^-46 of its row's sum, and for 2^-46 a_i of the sum of its column, so
-// that all of them together move the column sums by less than 2^-46 of the mass.
+// less than 2^-46 of its row's sum, and so for 2^-46 a_i of its column's, which all
+// of them together move by less than 2^-46 of the mass.
 constexpr double kScaleMax = 0x1p40;
 // The final check sums RRH loads up to this many cells per lane (416 columns):
 // the second set of FP64 column sums takes wider rows past the registers.
